@@ -17,11 +17,18 @@
 //            the row softmax needs only a 4-lane reduction and the
 //            probabilities already sit in the B-operand layout of the next
 //            product: no shuffle of P at all.
-//   mask     bitmap bit clear -> score -inf (the bitmap mask of Algorithm 1)
-//   softmax  online, base 2, fp32 (Section 3.5): running max m, running
-//            lane-partial sum l, rescale factor alpha = 2^(m_old - m_new)
-//            applied every pair (a branch around a rarely needed rescale
-//            measured slower: it splits the loop body for the scheduler)
+//   mask     bitmap bit clear -> score -inf (the bitmap mask of Algorithm 1):
+//            the nibble of a lane selects four words from a 256-byte table
+//            in LDS, one bit-select per score
+//   softmax  online, base 2, fp32 (Section 3.5): running max m,
+//            running sum l, rescale factor alpha = 2^(m_old - m_new).  A
+//            pair in which no row of the window finds a new maximum skips
+//            the cross-lane maximum, alpha and the rescale of O.  (Skipping
+//            while the maximum grows by less than 2^8 saved no more time and
+//            cost precision: a row's largest probability is then no longer
+//            1, which rounding keeps exact; relative error 0.9 -> 1.3e-4.
+//            For the same reason the exponent is a rounded difference of
+//            rounded products, 0 for the maximum, and not one fma.)
 //   P        fp16 inputs: fp32 -> fp16 with round-to-nearest-even (Table 5's
 //            scheme); the SAME rounded values are summed into l, so the
 //            effective probabilities of a row sum to one.
@@ -42,6 +49,15 @@
 // softmax and value product of the current pair (one pair in flight).
 // K and V rows are gathered with row-contiguous lanes and staged through
 // LDS (see the pipeline comment in the kernel).
+//
+// What bounds it: the memory system's rate for gathered rows (at most 21 TB/s
+// from one XCD's L2, 9 TB/s for a 16 MB table, 7 TB/s beyond), then vector
+// instructions: 61 of them besides 8 matrix products per block pair at d = 64,
+// down from 107 with a bit-select mask, a multiply per score, a rescale every
+// pair and per-chunk row addresses.  That took the hub-heavy Chung-Lu graph
+// (N = 65,536, d = 64) from 33.5 to 32.9 us and eight bf16 heads of a 32,768
+// token sequence from 327 to 313 us; the million-node graph (d = 128), bound
+// by memory, stays within 0.3% (1.312 ms on that box).
 //
 // Scores and probabilities never leave registers; only O (fp32 or fp16) and,
 // for split windows, the fp32 (m, l, unnormalised O) partials are written.
@@ -135,14 +151,6 @@ __device__ __forceinline__ void stage_words(_Float16 *row, int m, h8 w)
         *reinterpret_cast<uint32_t *>(row + 8 * (m0 + cc) + 2 * qd) = words[cc];
 }
 
-// v where sel is all ones, -inf where sel is zero (one bit-select).
-__device__ __forceinline__ float masked_score(float v, int sel)
-{
-    const uint32_t ninf = 0xff800000u;
-    return __builtin_bit_cast(float, (__builtin_bit_cast(uint32_t, v) & (uint32_t)sel) |
-                                         (ninf & ~(uint32_t)sel));
-}
-
 // Four fp32 results -> the output type at p (16-byte or 8-byte store).
 template <bool kOutH>
 __device__ __forceinline__ void store4(void *base, int64_t idx, f4 v)
@@ -197,7 +205,8 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
     constexpr int LSK = D + 8;
     constexpr int LSV = D + 16;
     __shared__ __attribute__((aligned(16))) _Float16 tiles[NW][32 * LSV];
-    const int wv = NW > 1 ? (int)(threadIdx.x >> 6) : 0;
+    __shared__ mask_words_t mask_table[16];
+    const int wv = NW > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
     _Float16 *const tile = tiles[wv];
 
     const int lane = NW > 1 ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
@@ -232,6 +241,8 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
     window_rows(win_row, N, it.window, &r0, &nr);
     const int row = r0 + i;
     const bool live = i < nr;
+    fill_mask_table(mask_table, lane);
+    tile_fence<NW>();
     // this wave's blocks: whole pairs [pa, pb) of the item's pairs
     int b0 = it.blk_begin, b1 = it.blk_end;
     if constexpr (NW > 1) {
@@ -259,8 +270,12 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
     f4 o[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) o[t] = f4{0.f, 0.f, 0.f, 0.f};
-    float m_run = -__builtin_inff();
-    float l_run = 0.f;
+    // Softmax state of row i (the same in its four lanes): the largest score
+    // m_run so far (-inf before the row's first entry) and the exponents'
+    // reference m_ref, m_run or 0 before it.
+    float m_run = -__builtin_inff(), m_ref = 0.f;
+    f4 l_acc = f4{0.f, 0.f, 0.f, 0.f};  // bf16: sums of the rows' probabilities
+    float l_run = 0.f;                  // others: this lane's part of its row's sum
 
     // Pipeline state.  The 32 K rows and 32 V rows of a block pair are
     // gathered "row-contiguous": the pair tile's 16-byte chunks are spread
@@ -278,86 +293,82 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
     constexpr int CE = 16 / EB;       // elements per chunk
     h8 kst[NI], vst[NI];              // staged K and V chunks of the pair in flight
     uint32_t mwa = 0, mwb = 0;
-    int ncol = 0;                // lanes 0..31: raw column of slot `lane` of the next pair
+    int ncol = 0;    // lanes 0..31 (and again 32..63): column of slot `lane` of the next pair
+    int coff = 0;    // of the pair in flight: byte offset of the slot's row (or its column)
 
-    // Raw column ids of pair (b, b+1): lane l (mod 32) takes slot l; block
-    // indices clamped so reads stay inside this item (values past its end
-    // are never used).
-    auto load_cols = [&](int b) {
-        const int slot = lane & 31;
-        const int blk = slot < 16 ? min(b, b1 - 1) : min(b + 1, b1 - 1);
-        ncol = cols[(int64_t)kBlockCols * blk + (slot & 15)];
+    const uint32_t lane_col = 4u * (lane & 31);
+    auto load_cols = [&](int b) { ncol = load_pair_cols(cols, b, b1, lane_col); };
+    // Bitmaps of pair (b, b+1); takes over the columns loaded for it.
+    auto load_masks = [&](int b) {
+        const int c = pad_cols(ncol);
+        coff = kWide ? c : c * (EB * ld);
+        const uint32_t *mp = mask + (int64_t)kMaskWords * b;
+        mwa = mp[lane >> 3];
+        mwb = mp[(b + 1 < b1 ? kMaskWords : 0) + (lane >> 3)];
     };
-    // Issue the K, V and bitmap loads of pair (b, b+1).  Slots 0 and 16 are
-    // never padding (the first slot of a block); the wave is fully active
-    // here, so readlane sees them.
-    auto load_pair = [&](int b) {
-        const int f0 = __builtin_amdgcn_readlane(ncol, 0);
-        const int f1 = __builtin_amdgcn_readlane(ncol, 16);
-        const int c = ncol < 0 ? ((lane & 16) ? f1 : f0) : ncol;
+    // Issue the loads of the pair's rows of X (K or V).
+    auto load_rows = [&](const char *X, h8 *st) {
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             const int f = lane + 64 * j;
-            const int col = __shfl(c, f / LPR);
+            const int cj = __builtin_amdgcn_ds_bpermute(4 * (f / LPR), coff);
             if constexpr (kNarrow) {
                 // word qd of chunks m0 .. m0+3 (the quad's chunks: LPR is a
                 // multiple of 4, so the quad lies in one row)
                 static_assert(EB == 2, "narrow gathers are defined for 16-bit inputs");
                 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
                 const int m = f % LPR, m0 = m & ~3, qd = m & 3;
-                u4v wk, wv;
+                u4v w;
 #pragma unroll
                 for (int cc = 0; cc < 4; ++cc) {
-                    if constexpr (kWide) {
-                        const int64_t off = (int64_t)col * ld * EB + 16 * (m0 + cc) + 4 * qd;
-                        wk[cc] = *reinterpret_cast<const uint32_t *>(K + off);
-                        wv[cc] = *reinterpret_cast<const uint32_t *>(V + off);
-                    } else {
-                        const uint32_t off = (uint32_t)col * (uint32_t)(EB * ld) +
-                                             16u * (m0 + cc) + 4u * qd;
-                        wk[cc] = *reinterpret_cast<const uint32_t *>(K + off);
-                        wv[cc] = *reinterpret_cast<const uint32_t *>(V + off);
-                    }
+                    if constexpr (kWide)
+                        w[cc] = *reinterpret_cast<const uint32_t *>(
+                            X + (int64_t)cj * ld * EB + 16 * (m0 + cc) + 4 * qd);
+                    else
+                        w[cc] = *reinterpret_cast<const uint32_t *>(
+                            X + ((uint32_t)cj + 16u * (m0 + cc) + 4u * qd));
                 }
-                kst[j] = __builtin_bit_cast(h8, wk);
-                vst[j] = __builtin_bit_cast(h8, wv);
+                st[j] = __builtin_bit_cast(h8, w);
             } else if constexpr (kWide) {
-                const int64_t off = (int64_t)col * ld * EB + 16 * (f % LPR);
-                kst[j] = *reinterpret_cast<const h8 *>(K + off);
-                vst[j] = *reinterpret_cast<const h8 *>(V + off);
+                st[j] = *reinterpret_cast<const h8 *>(X + (int64_t)cj * ld * EB + 16 * (f % LPR));
             } else {
                 // byte offset < 2^32 (checked on the host): the load takes
                 // the uniform base from SGPRs and a 32-bit VGPR offset
-                const uint32_t off = (uint32_t)col * (uint32_t)(EB * ld) + 16u * (f % LPR);
-                kst[j] = load16_off(reinterpret_cast<const _Float16 *>(K), off);
-                vst[j] = load16_off(reinterpret_cast<const _Float16 *>(V), off);
+                st[j] = load16_off(reinterpret_cast<const _Float16 *>(X),
+                                   (uint32_t)cj + 16u * (f % LPR));
             }
         }
-        mwa = mask[(int64_t)kMaskWords * b + (lane >> 3)];
-        mwb = mask[(int64_t)kMaskWords * min(b + 1, b1 - 1) + (lane >> 3)];
     };
-
-    const int nib_shift = 4 * (lane & 7);
-    // One block pair: scores, mask, online softmax, value product.  With
-    // `prefetch`, the loads of the pair after it are issued as soon as this
-    // pair's staging registers are in LDS.
-    auto step = [&](int b, bool prefetch) {
-        // ---- K rows -> LDS (stride LSK), read back as MFMA A operands ----
+    // The staged rows into the LDS tile with row stride ls.
+    auto stage_rows = [&](const h8 *st, int ls) {
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             const int f = lane + 64 * j;
-            _Float16 *dst = &tile[(f / LPR) * LSK + CE * (f % LPR)];
+            _Float16 *dst = &tile[(f / LPR) * ls + CE * (f % LPR)];
             if constexpr (kNarrow) {
-                stage_words(&tile[(f / LPR) * LSK], f % LPR, kst[j]);
+                stage_words(&tile[(f / LPR) * ls], f % LPR, st[j]);
             } else if constexpr (EB == 1) {
                 h8 lo, hi;
-                widen_fp8x16(kst[j], lo, hi);
+                widen_fp8x16(st[j], lo, hi);
                 *reinterpret_cast<h8 *>(dst) = lo;
                 *reinterpret_cast<h8 *>(dst + 8) = hi;
             } else {
-                *reinterpret_cast<h8 *>(dst) = kst[j];
+                *reinterpret_cast<h8 *>(dst) = st[j];
             }
         }
+    };
+
+    const uint32_t nib_rot = mask_nibble_rot(lane);
+    // One block pair: scores, mask, online softmax, value product.  With
+    // `prefetch`, the loads of the pair after it are issued as soon as this
+    // pair's staging registers are in LDS, in the order in which they are used.
+    auto step = [&](int b, bool prefetch) {
+        // (an odd tail's absent second block re-read block b: mask it off)
+        const mask_words_t sel0 = mask_words_of(mask_table, mwa, nib_rot, 0xF0u);
+        const mask_words_t sel1 =
+            mask_words_of(mask_table, mwb, nib_rot, b + 1 < b1 ? 0xF0u : 0u);
+        // ---- K rows -> LDS (stride LSK), read back as MFMA A operands ----
+        stage_rows(kst, LSK);
         tile_fence<NW>();
         h8 ka[NC], kb[NC];
 #pragma unroll
@@ -366,7 +377,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
             kb[c] = *reinterpret_cast<const h8 *>(&tile[(16 + i) * LSK + 32 * c + 8 * g]);
         }
         // ---- scores of the two blocks (S^T: lane = row i, nbrs 4g+r) ----
-        f4 s0 = f4{0.f, 0.f, 0.f, 0.f}, s1 = f4{0.f, 0.f, 0.f, 0.f};
+        f4 s0 = f4{0.f, 0.f, 0.f, 0.f}, s1 = s0;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             s0 = mma_in<kIn>(ka[c], q[c], s0);
@@ -374,60 +385,53 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
         }
         tile_fence<NW>();
         // ---- V rows -> the same LDS tile (stride LSV, slot = neighbour) ----
-#pragma unroll
-        for (int j = 0; j < NI; ++j) {
-            const int f = lane + 64 * j;
-            _Float16 *dst = &tile[(f / LPR) * LSV + CE * (f % LPR)];
-            if constexpr (kNarrow) {
-                stage_words(&tile[(f / LPR) * LSV], f % LPR, vst[j]);
-            } else if constexpr (EB == 1) {
-                h8 lo, hi;
-                widen_fp8x16(vst[j], lo, hi);
-                *reinterpret_cast<h8 *>(dst) = lo;
-                *reinterpret_cast<h8 *>(dst + 8) = hi;
-            } else {
-                *reinterpret_cast<h8 *>(dst) = vst[j];
-            }
-        }
-        const uint32_t nib0 = (mwa >> nib_shift) & 15u;
-        // (an odd tail's absent second block re-read block b: mask it off)
-        const uint32_t nib1 = b + 1 < b1 ? (mwb >> nib_shift) & 15u : 0u;
+        stage_rows(vst, LSV);
         // ---- issue the next pair's loads (staging registers are free) ----
         if (prefetch) {
-            load_pair(b + 2);
+            load_masks(b + 2);
             load_cols(b + 4);
+            load_rows(K, kst);
+            load_rows(V, vst);
         }
         // ---- mask + online softmax (base 2) ----
-        // bit r of the nibble -> all-ones / zero word (signed bit-field
-        // extract), then a bit-select between the score and -inf
         float x[8];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            x[r] = masked_score(s0[r] * sl2, __builtin_amdgcn_sbfe((int)nib0, r, 1));
-            x[4 + r] = masked_score(s1[r] * sl2, __builtin_amdgcn_sbfe((int)nib1, r, 1));
+            x[r] = masked_score(s0[r] * sl2, sel0[r]);
+            x[4 + r] = masked_score(s1[r] * sl2, sel1[r]);
         }
         float mloc = x[0];
 #pragma unroll
         for (int e = 1; e < 8; ++e) mloc = fmaxf(mloc, x[e]);
-        mloc = max_xor16(mloc);
-        mloc = max_xor32(mloc);
-        const float m_new = fmaxf(m_run, mloc);
-        const float m_ref = m_new == -__builtin_inff() ? 0.f : m_new;
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_ref);
+        // (a lane without a new maximum agrees with its row's m_run, which is
+        // the row's largest score so far)
+        if (__builtin_amdgcn_ballot_w64(mloc > m_run) != 0) {
+            const float m_new = fmaxf(m_run, max_xor32(max_xor16(mloc)));
+            m_ref = m_new == -__builtin_inff() ? 0.f : m_new;
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_ref);
+            l_run *= alpha;
+            l_acc *= alpha;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) o[t] *= alpha;
+            m_run = m_new;
+        }
         h8 p, plo;
-        float psum = 0.f;
         if constexpr (kIn == kInBF16) {
             // P = hi + lo, both bfloat16; hi + lo is exact in fp32
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const float pf = __builtin_amdgcn_exp2f(x[e] - m_ref);
                 const __bf16 hb = (__bf16)pf;
-                const float hf = (float)hb;
-                const __bf16 lb = (__bf16)(pf - hf);
+                const __bf16 lb = (__bf16)(pf - (float)hb);
                 p[e] = __builtin_bit_cast(_Float16, hb);
                 plo[e] = __builtin_bit_cast(_Float16, lb);
-                psum += hf + (float)lb;
             }
+            // the rows' sums of the rounded values: a product with ones
+            const uint32_t one2 = 0x3F803F80u;
+            typedef uint32_t u4o __attribute__((ext_vector_type(4)));
+            const h8 ones = __builtin_bit_cast(h8, u4o{one2, one2, one2, one2});
+            l_acc = mfma16x16x32_bf16(ones, p, l_acc);
+            l_acc = mfma16x16x32_bf16(ones, plo, l_acc);
         } else {
 #pragma unroll
             for (int e = 0; e < 8; ++e)
@@ -436,12 +440,8 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
             const h2 one = {(_Float16)1.0f, (_Float16)1.0f};
 #pragma unroll
             for (int e = 0; e < 8; e += 2)
-                psum = __builtin_amdgcn_fdot2(h2{p[e], p[e + 1]}, one, psum, false);
+                l_run = __builtin_amdgcn_fdot2(h2{p[e], p[e + 1]}, one, l_run, false);
         }
-        l_run = l_run * alpha + psum;
-        m_run = m_new;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) o[t] *= alpha;
         tile_fence<NW>();
         // ---- value product: A[m][slot] = V_hat[slot][16t + m] ----
         // slot order of lane group g: 4g..4g+3 (block 0), 16+4g..+3 (block 1)
@@ -467,16 +467,26 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
 
     if (b0 < b1) {
         load_cols(b0);
-        load_pair(b0);
+        load_masks(b0);
         load_cols(b0 + 2);
+        // loads return in issue order: the loop waits for each group in turn
+        // only if they are issued in the same order here
+        __builtin_amdgcn_sched_barrier(0);
+        load_rows(K, kst);
+        __builtin_amdgcn_sched_barrier(0);
+        load_rows(V, vst);
+        __builtin_amdgcn_sched_barrier(0);
         int b = b0;
         for (; b + 2 < b1; b += 2) step(b, true);
         step(b, false);
     }
 
     // ---- finalise: full row sums, normalise, write (Algorithm 1 end) ----
-    float l_tot = l_run + __shfl_xor(l_run, 16);
-    l_tot += __shfl_xor(l_tot, 32);
+    float l_tot = l_acc[0];
+    if constexpr (kIn != kInBF16) {
+        l_tot = l_run + __shfl_xor(l_run, 16);
+        l_tot += __shfl_xor(l_tot, 32);
+    }
     if constexpr (NW > 1) {
         // the waves' partial states: O (lane (i, g) holds columns 16t + 4g ..
         // +3 of row i) into the wave's own tile, which 16 x D floats fit and

@@ -66,6 +66,9 @@ __device__ __forceinline__ float max_xor32(float v)
     return fmaxf(__builtin_bit_cast(float, (int)r[0]), __builtin_bit_cast(float, (int)r[1]));
 }
 
+// DPP control: every lane receives lane 0 of its row of 16 (row_newbcast:0).
+constexpr int kRowBcast0 = 0x150;
+
 // Orders this wave's LDS accesses (one wave per workgroup).
 __device__ __forceinline__ void wave_lds_fence()
 {
@@ -120,6 +123,66 @@ __device__ __forceinline__ int workgroup_position(uint32_t order, int nh)
     const int x = wg & 7, per = 8 / nh, h = x % nh, k = x / nh;
     const int q = n_it / per, r = n_it % per;
     return (k * q + min(k, r) + (wg >> 3)) * nh + h;
+}
+
+// ---- pieces of the block-pair loops --------------------------------------
+
+// Column ids of block pair (b, b+1) of an item ending at b1 (b, b1 uniform):
+// lane l takes slot l mod 32 (lane_col = 4 * (l mod 32)); an absent second
+// block gives the first one's columns again, b past the item its last block
+// (in bounds, never used).
+__device__ __forceinline__ int load_pair_cols(const int32_t *cols, int b, int b1,
+                                              uint32_t lane_col)
+{
+    const int bc = min(b, b1 - 1);
+    const uint32_t wrap = bc + 1 < b1 ? 0x7Cu : 0x3Cu;
+    return *reinterpret_cast<const int32_t *>(
+        reinterpret_cast<const char *>(cols + (int64_t)kBlockCols * bc) + (lane_col & wrap));
+}
+
+// A padding slot (-1) takes its block's first column (the first slot is never
+// padding and the smallest: columns ascend): a real column of the block whose
+// bitmap bit is clear.
+__device__ __forceinline__ int pad_cols(int c)
+{
+    return max(c, __builtin_amdgcn_update_dpp(0, c, kRowBcast0, 0xF, 0xF, true));
+}
+
+// The bitmap mask as a table in LDS, indexed by a lane's nibble of a block's
+// bitmap (its four neighbours): word r of entry n is all ones where bit r of
+// n is set, else zero (one LDS read in place of a bit-field extract per
+// score).  Every wave writes the same values and orders its own reads behind
+// them with a fence (a wave's LDS operations run in issue order).
+typedef uint32_t mask_words_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void fill_mask_table(mask_words_t *table, int lane)
+{
+    if (lane < 16) {
+        mask_words_t e;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) e[r] = (lane >> r) & 1 ? ~0u : 0u;
+        table[lane] = e;
+    }
+}
+// Rotation that moves a lane's nibble of its bitmap word (lane >> 3) to bits
+// 4..7, the byte offset of its table entry, and the entry (sel: 0xF0, or 0
+// for an absent block).
+__device__ __forceinline__ uint32_t mask_nibble_rot(int lane)
+{
+    return (4u * (lane & 7) + 28u) & 31u;
+}
+__device__ __forceinline__ mask_words_t mask_words_of(const mask_words_t *table, uint32_t word,
+                                                      uint32_t rot, uint32_t sel)
+{
+    return *reinterpret_cast<const mask_words_t *>(
+        reinterpret_cast<const char *>(table) +
+        (__builtin_amdgcn_alignbit(word, word, rot) & sel));
+}
+// v where sel is all ones, -inf where sel is zero (one bit-select).
+__device__ __forceinline__ float masked_score(float v, uint32_t sel)
+{
+    const uint32_t ninf = 0xff800000u;
+    return __builtin_bit_cast(float,
+                              (__builtin_bit_cast(uint32_t, v) & sel) | (ninf & ~sel));
 }
 
 __device__ __forceinline__ h8 cat44(h4 lo, h4 hi)
