@@ -81,7 +81,9 @@ typedef struct {
  * Build a plan from a CSR pattern that lives in DEVICE memory.
  * Environment (read at plan time; for ablations):
  *   F3S_PIECE_BLOCKS=<even n>  piece size of split windows (capped at the
- *                              largest window)
+ *                              largest window).  Unset, windows far above
+ *                              the mean are split, none of a nearly uniform
+ *                              pattern below 128 blocks
  *   F3S_NO_REORDER=1           work list in window order instead of
  *                              decreasing block count (Section 3.2);
  *                              =0 always sorts.  Unset, plans of nearly
@@ -191,11 +193,14 @@ f3s_status_t f3s_run(f3s_plan_t plan, const void *Q, const void *K, const void *
  * the plan's windows are nearly uniform (then each XCD takes consecutive
  * ranges of one head's work list at a time), window-major otherwise
  * (environment F3S_HEAD_MAJOR_BYTES=<bytes> replaces these tests with a K/V
- * size threshold; results are identical either way).  When a launch would have fewer waves than the GPU has SIMDs
- * (work items x heads < 1024) four waves share each work item, and two when
- * twice the waves still fit the GPU at once; they combine their partial
- * softmax states (environment F3S_WAVES_PER_ITEM=1, 2 or 4 forces the
- * count; the rounding of the combination differs).
+ * size threshold; results are identical either way).  On nearly
+ * uniform plans four waves share each work item when a launch would have
+ * fewer waves than the GPU has SIMDs (work items x heads < 1024), and two
+ * when twice the waves still fit the GPU at once; on skewed plans four waves
+ * share each item that holds more blocks than a resident wave's even share.
+ * Sharing waves combine their partial softmax states (environment
+ * F3S_WAVES_PER_ITEM=1, 2 or 4 forces one count for all items; the rounding
+ * of the combination differs).
  */
 f3s_status_t f3s_run_mh(f3s_plan_t plan, const void *Q, const void *K, const void *V,
                         void *O, int32_t n_heads, int32_t d, float scale,

@@ -132,7 +132,7 @@ __attribute__((amdgpu_waves_per_eu(BwdDqWaves<D>::value, 8))) void k_bwd_dq(
     const _Float16 *__restrict__ V, const _Float16 *__restrict__ G,
     const float *__restrict__ O, const float *__restrict__ lse, float2 *__restrict__ stats,
     float *__restrict__ dQ, float *__restrict__ part, int32_t N, int32_t ld, int32_t h0,
-    int32_t nh, float sl2, float scale, uint32_t order)
+    int32_t nh, float sl2, float scale, uint32_t order, int32_t n_items, int32_t shared_items)
 {
     constexpr int NC = D / 32, NT = D / 16, NI = D / 16;
     constexpr int LSK = D + 16;  // K tile: operand reads and transposed reads
@@ -141,7 +141,7 @@ __attribute__((amdgpu_waves_per_eu(BwdDqWaves<D>::value, 8))) void k_bwd_dq(
     __shared__ __attribute__((aligned(16))) _Float16 tVs[NW][32 * LSV];
     // NW waves may share the work item (as in the forward): wave wv takes a
     // contiguous share of its block pairs; the partial dQ sums meet in LDS
-    const int wv = NW > 1 ? (int)(threadIdx.x >> 6) : 0;
+    const int wv = NW > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
     _Float16 *const tK = tKs[wv];
     _Float16 *const tV = tVs[wv];
 
@@ -149,10 +149,13 @@ __attribute__((amdgpu_waves_per_eu(BwdDqWaves<D>::value, 8))) void k_bwd_dq(
     const int i = lane & 15, g = lane >> 4;
     // window-major, or head by head when K and V exceed the caches (as in
     // the forward)
-    const int n_it = gridDim.x / nh;
+    const int n_gr = gridDim.x / nh;
     const int wg = workgroup_position(order, nh);
-    const int hl = (order & kOrderHead) ? wg / n_it : wg % nh;
-    const int item = (order & kOrderHead) ? wg - hl * n_it : wg / nh;
+    const int hl = (order & kOrderHead) ? wg / n_gr : wg % nh;
+    const int group = (order & kOrderHead) ? wg - hl * n_gr : wg / nh;
+    int item;
+    bool shared;
+    if (!wave_item<NW>(group, wv, shared_items, n_items, &item, &shared)) return;
     const int head = h0 + hl, H = ld / D;
     const WorkItem it = items[item];
     Q += (int64_t)head * D;
@@ -169,7 +172,7 @@ __attribute__((amdgpu_waves_per_eu(BwdDqWaves<D>::value, 8))) void k_bwd_dq(
     const bool live = i < nr;
     const int rrow = live ? row : r0;
     int b0 = it.blk_begin, b1 = it.blk_end;
-    if constexpr (NW > 1) {
+    if (NW > 1 && shared) {
         const int pairs = (b1 - b0 + 1) >> 1;
         const int pa = pairs * wv / NW, pb = pairs * (wv + 1) / NW;
         b1 = min(b1, b0 + 2 * pb);
@@ -200,7 +203,7 @@ __attribute__((amdgpu_waves_per_eu(BwdDqWaves<D>::value, 8))) void k_bwd_dq(
     dl += __shfl_xor(dl, 32);
     // one 8-byte record per row and head for the dK/dV pass, which gathers
     // it for every attending row: (base-2 log-sum-exp, delta)
-    if (g == 0 && live && wv == 0) stats[(int64_t)row * H + head] = float2{lse2, dl};
+    if (g == 0 && live && (wv == 0 || !shared)) stats[(int64_t)row * H + head] = float2{lse2, dl};
 
     f4 acc[NT];
 #pragma unroll
@@ -280,7 +283,7 @@ __attribute__((amdgpu_waves_per_eu(BwdDqWaves<D>::value, 8))) void k_bwd_dq(
         for (; b + 2 < b1; b += 2) step(b, true);
         step(b, false);
     }
-    if constexpr (NW > 1) {
+    if (NW > 1 && shared) {
         // partial sums into the waves' own K tiles (16 x D floats fit), then
         // wave 0 adds them (lane (i, g) holds columns 16t + 4g .. +3 of row i)
         float *ot = reinterpret_cast<float *>(tK);
@@ -325,7 +328,7 @@ __attribute__((amdgpu_waves_per_eu(BwdWaves<D>::value, 8))) void k_bwd_dkdv(
     const _Float16 *__restrict__ G, const float2 *__restrict__ stats,
     float *__restrict__ dK, float *__restrict__ dV,
     float *__restrict__ part, int32_t N, int32_t ld, int32_t h0, int32_t nh, float sl2,
-    float scale, uint32_t order)
+    float scale, uint32_t order, int32_t n_items, int32_t shared_items)
 {
     constexpr int NC = D / 32, NT = D / 16, NI = D / 16;
     constexpr int LS = D + 16;  // operand reads and transposed reads
@@ -334,7 +337,7 @@ __attribute__((amdgpu_waves_per_eu(BwdWaves<D>::value, 8))) void k_bwd_dkdv(
     __shared__ float slses[NW][32], sdels[NW][32];
     // NW waves may share the work item (as in the forward): wave wv takes a
     // contiguous share of its block pairs; the partial dK, dV sums meet in LDS
-    const int wv = NW > 1 ? (int)(threadIdx.x >> 6) : 0;
+    const int wv = NW > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
     _Float16 *const tQ = tQs[wv];
     _Float16 *const tG = tGs[wv];
     float *const slse = slses[wv];
@@ -344,10 +347,13 @@ __attribute__((amdgpu_waves_per_eu(BwdWaves<D>::value, 8))) void k_bwd_dkdv(
     const int i = lane & 15, g = lane >> 4;
     // window-major, or head by head when K and V exceed the caches (as in
     // the forward)
-    const int n_it = gridDim.x / nh;
+    const int n_gr = gridDim.x / nh;
     const int wg = workgroup_position(order, nh);
-    const int hl = (order & kOrderHead) ? wg / n_it : wg % nh;
-    const int item = (order & kOrderHead) ? wg - hl * n_it : wg / nh;
+    const int hl = (order & kOrderHead) ? wg / n_gr : wg % nh;
+    const int group = (order & kOrderHead) ? wg - hl * n_gr : wg / nh;
+    int item;
+    bool shared;
+    if (!wave_item<NW>(group, wv, shared_items, n_items, &item, &shared)) return;
     const int head = h0 + hl, H = ld / D;
     const WorkItem it = items[item];
     Q += (int64_t)head * D;
@@ -359,7 +365,7 @@ __attribute__((amdgpu_waves_per_eu(BwdWaves<D>::value, 8))) void k_bwd_dkdv(
     const int key = it.window * kWindowRows + i;
     const int rkey = min(key, N - 1);
     int b0 = it.blk_begin, b1 = it.blk_end;
-    if constexpr (NW > 1) {
+    if (NW > 1 && shared) {
         const int pairs = (b1 - b0 + 1) >> 1;
         const int pa = pairs * wv / NW, pb = pairs * (wv + 1) / NW;
         b1 = min(b1, b0 + 2 * pb);
@@ -483,7 +489,7 @@ __attribute__((amdgpu_waves_per_eu(BwdWaves<D>::value, 8))) void k_bwd_dkdv(
         for (; b + 2 < b1; b += 2) step(b, true);
         step(b, false);
     }
-    if constexpr (NW > 1) {
+    if (NW > 1 && shared) {
         // partial sums into the waves' own Q and G tiles (16 x D floats each
         // fit), then wave 0 adds them
         float *okt = reinterpret_cast<float *>(tQ);
@@ -591,19 +597,20 @@ hipError_t launch_bwd_d(const f3s_plan_s &p, const f3s_plan_s &pt, const void *Q
     };
     // dQ: windows of A; partials need 16*D floats per (piece, head)
     {
-        const int nw = waves_per_item(p.n_blocks, p.n_items, H,
-                                      (int64_t)BwdDqWaves<D>::value * 1024);
+        const WaveSplit ws = wave_split(p, H, (int64_t)BwdDqWaves<D>::value * 1024);
+        const int nw = ws.nw;
         auto kern = nw == 4   ? (wide ? k_bwd_dq<D, true, kBF16, 4> : k_bwd_dq<D, false, kBF16, 4>)
                     : nw == 2 ? (wide ? k_bwd_dq<D, true, kBF16, 2> : k_bwd_dq<D, false, kBF16, 2>)
                               : (wide ? k_bwd_dq<D, true, kBF16> : k_bwd_dq<D, false, kBF16>);
-        const int32_t group = p.n_split > 0 ? (kMaxD / D < H ? kMaxD / D : H) : H;
+        const int32_t group = p.n_split > 0 ? (p.part_row / D < H ? p.part_row / D : H) : H;
         for (int32_t h0 = 0; h0 < H; h0 += group) {
             const int32_t nh = H - h0 < group ? H - h0 : group;
-            if (p.n_split > 0 && (int64_t)nh * D > kMaxD) return hipErrorInvalidValue;
+            if (p.n_split > 0 && (int64_t)nh * D > p.part_row) return hipErrorInvalidValue;
             if (p.n_items > 0) {
-                kern<<<(unsigned)((uint64_t)p.n_items * nh), 64 * nw, 0, s>>>(
+                kern<<<(unsigned)(wave_groups(ws, p.n_items) * nh), 64 * nw, 0, s>>>(
                     p.items, p.cols, p.mask, p.win_row, q, k, v, gr, O, lse, stats, dQ,
-                    p.part_o, p.N, ld, h0, nh, sl2, scale, order_of(p, nh));
+                    p.part_o, p.N, ld, h0, nh, sl2, scale, order_of(p, nh), p.n_items,
+                    ws.shared);
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
             if (p.n_split > 0) {
@@ -615,8 +622,8 @@ hipError_t launch_bwd_d(const f3s_plan_s &p, const f3s_plan_s &pt, const void *Q
     }
     // dK, dV: windows of A^T; partials need 2*16*D floats per (piece, head)
     {
-        const int nw = waves_per_item(pt.n_blocks, pt.n_items, H,
-                                      (int64_t)BwdWaves<D>::value * 1024);
+        const WaveSplit ws = wave_split(pt, H, (int64_t)BwdWaves<D>::value * 1024);
+        const int nw = ws.nw;
         auto kern = nw == 4
                         ? (wide ? k_bwd_dkdv<D, true, kBF16, 4> : k_bwd_dkdv<D, false, kBF16, 4>)
                     : nw == 2
@@ -630,9 +637,9 @@ hipError_t launch_bwd_d(const f3s_plan_s &p, const f3s_plan_s &pt, const void *Q
             const int32_t nh = H - h0 < group ? H - h0 : group;
             if (pt.n_split > 0 && (int64_t)nh * 2 * D > pt.part_row) return hipErrorInvalidValue;
             if (pt.n_items > 0) {
-                kern<<<(unsigned)((uint64_t)pt.n_items * nh), 64 * nw, 0, s>>>(
+                kern<<<(unsigned)(wave_groups(ws, pt.n_items) * nh), 64 * nw, 0, s>>>(
                     pt.items, pt.cols, pt.mask, q, k, v, gr, stats, dK, dV, pt.part_o,
-                    pt.N, ld, h0, nh, sl2, scale, order_of(pt, nh));
+                    pt.N, ld, h0, nh, sl2, scale, order_of(pt, nh), pt.n_items, ws.shared);
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
             if (pt.n_split > 0) {

@@ -90,11 +90,17 @@ void free_plan_arrays(f3s_plan_s *p)
     p->part_ml = nullptr;
 }
 
+// Pieces up to which the partial buffers hold four launch groups' heads at
+// once (at most 33 MB, 67 MB for a transposed plan).
+constexpr int32_t kWidePartPieces = 512;
+
 // Partial-result buffers of split windows: part_row floats per piece row
 // for O (kMaxD for a plan, 2 * kMaxD for a transposed plan, which holds the
-// dK and dV partials), and the (m, l) records.  Replaces any previous ones.
+// dK and dV partials; four times that with few pieces, so that more heads
+// go in one launch), and the (m, l) records.  Replaces any previous ones.
 hipError_t alloc_parts(f3s_plan_s *p, int32_t part_row)
 {
+    if (p->n_pieces <= kWidePartPieces) part_row *= 4;
     if (p->part_store) {
         (void)hipFree(p->part_store);
         p->device_bytes -= (int64_t)p->part_bytes;
@@ -107,15 +113,15 @@ hipError_t alloc_parts(f3s_plan_s *p, int32_t part_row)
     Arena a;
     a.add<float>((int64_t)p->n_pieces * f3s::kWindowRows * part_row);
     // one (m, l) record of 16 + 16 floats per piece and head of a launch
-    // group; a group holds at most kMaxD / 32 heads (nh * d <= kMaxD)
-    a.add<float>((int64_t)p->n_pieces * 32 * (f3s::kMaxD / 32));
+    // group; a group holds at most part_row / 32 heads (nh * d <= part_row)
+    a.add<float>((int64_t)p->n_pieces * 32 * (part_row / 32));
     hipError_t e = a.alloc();
     if (e != hipSuccess) return e;
     p->part_store = a.base;
     p->part_bytes = (int64_t)a.cap;
     p->device_bytes += (int64_t)a.cap;
     p->part_o = a.take<float>((int64_t)p->n_pieces * f3s::kWindowRows * part_row);
-    p->part_ml = a.take<float>((int64_t)p->n_pieces * 32 * (f3s::kMaxD / 32));
+    p->part_ml = a.take<float>((int64_t)p->n_pieces * 32 * (part_row / 32));
     return hipSuccess;
 }
 
@@ -195,6 +201,7 @@ struct BuildStats {
     int32_t n_split;
     int32_t n_items;              // item count from the work-list scan
     int32_t invalid;              // plan integrity check
+    int32_t heavy[f3s::kHeavySteps];  // items above kHeavyBlocks << j blocks
 };
 
 // Pointers into the plan build's scratch.
@@ -340,7 +347,8 @@ f3s_status_t build_plan(f3s_plan_s *p, const int32_t *row_ptr, const int32_t *co
                (env_int("F3S_SPLIT_ROW", 0) ? 8 : 0);
     HIP_TRY(launch_bin_keys(nb, T, &st->n_blocks, &st->max_blocks,
                             env_int("F3S_PIECE_BLOCKS", 0), slots, reorder,
-                            &st->piece, npieces, key, split_pieces, split_one, s));
+                            &st->piece, npieces, key, split_pieces, split_one, st->heavy,
+                            s));
     {
         ScanArray sp, so;
         sp.in = sp.out = split_pieces;
@@ -361,6 +369,7 @@ f3s_status_t build_plan(f3s_plan_s *p, const int32_t *row_ptr, const int32_t *co
     p->piece = piece;
     p->n_pieces = hs.n_pieces;
     p->n_split = hs.n_split;
+    memcpy(p->heavy, hs.heavy, sizeof p->heavy);
     const int64_t n_items = (int64_t)T - p->n_split + p->n_pieces;
     if (n_items > INT32_MAX) return F3S_ERR_UNSUPPORTED;
     p->n_items = (int32_t)n_items;

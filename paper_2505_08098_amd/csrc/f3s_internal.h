@@ -29,6 +29,11 @@ struct WorkItem {
 };
 static_assert(sizeof(WorkItem) == 16, "WorkItem must be 16 bytes");
 
+// A plan's table of heavy items: heavy[j] counts the items of windows (or
+// pieces) above heavy_blocks(j) blocks: 8, 10, 12, 14, 16, 20, 24, 28, 32, ...
+constexpr int kHeavySteps = 32;
+__host__ __device__ constexpr int32_t heavy_blocks(int j) { return (8 + 2 * (j & 3)) << (j >> 2); }
+
 }  // namespace f3s
 
 struct f3s_plan_s {
@@ -47,6 +52,8 @@ struct f3s_plan_s {
     int32_t flags = 0;           // bit 0: work list in window order; bit 1: narrow gathers;
                                  // bit 2: windows aligned to the graphs of a batch;
                                  // bit 3: split-row forward (ablation)
+    int32_t heavy[f3s::kHeavySteps] = {};  // leading items above heavy_blocks(j) blocks
+                                 // (heavy-first work lists)
     uint64_t id = 0;             // process-unique plan id
     uint64_t transpose_of = 0;   // id of the plan this one transposes (0: none)
     void *store = nullptr;       // one allocation: blk_off, cols, mask, items, merges
@@ -61,11 +68,12 @@ struct f3s_plan_s {
                                  // windows follow the graphs of a batch; null: window w
                                  // is rows 16 w .. 16 w + 15)
     // Partial results of split windows for one launch group of nh heads
-    // (nh * d <= kMaxD): slot (piece, head) = piece * nh + head.
+    // (nh * d <= part_row): slot (piece, head) = piece * nh + head.
     float *part_o = nullptr;     // [n_pieces * 16 * part_row]
-    int32_t part_row = f3s::kMaxD;  // floats per piece row of part_o (transposed plans:
-                                 // 2 * kMaxD, for the dK and dV partials)
-    float *part_ml = nullptr;    // [n_pieces * (kMaxD/32) * 32]: 16 maxima, 16 sums
+    int32_t part_row = f3s::kMaxD;  // floats per piece row of part_o: kMaxD, or 4 kMaxD
+                                 // with few pieces (transposed plans: twice that, for
+                                 // the dK and dV partials)
+    float *part_ml = nullptr;    // [n_pieces * (part_row/32) * 32]: 16 maxima, 16 sums
     int64_t device_bytes = 0;
     int64_t bsb_bytes = 0;
     double build_ms = 0.0;
@@ -131,27 +139,65 @@ inline bool xcd_chunks(const f3s_plan_s &p, int32_t heads, bool head_major = fal
     if (e && *e) return atoi(e) != 0;
     return uniform_windows(p.n_items, p.n_blocks, p.max_blocks);
 }
-// Waves sharing one work item (forward and backward): 4 when a launch would
+// Waves per work item (forward and backward).  nw: waves of a workgroup; the
+// first `shared` items are shared by the nw waves of a workgroup each, the
+// others get one wave each, nw of them to a workgroup.
+struct WaveSplit {
+    int nw;
+    int32_t shared;
+};
+// Nearly uniform plans (the largest item at most twice the mean), and plans
+// whose list keeps window order: all items by 4 waves when a launch would
 // have fewer waves than the GPU has SIMDs (items x heads < 1024) and the
-// items average at least 4 blocks; else 2 when twice the waves still fit
-// the GPU at once (`resident`: the kernel's waves per SIMD x 1024 SIMDs) and
-// the items average at least 8 blocks (two pairs per wave); else 1.  More
-// waves than fit at once would run as a second round, whose tail and the
-// extra per-wave Q loads and combination cost more than the parallelism
-// gains (4 waves measured 18% slower on the 2048-window sequence workload).
-// F3S_WAVES_PER_ITEM=1, 2 or 4 forces it (read at launch).
-inline int waves_per_item(int64_t n_blocks, int64_t n_items, int32_t heads, int64_t resident)
+// items average at least 4 blocks; else all by 2 when twice the waves still
+// fit the GPU at once (`resident`: the kernel's waves per SIMD x 1024 SIMDs)
+// and the items average at least 8 blocks (two pairs per wave); else one
+// each.  More waves than fit at once would run as a second round, whose tail
+// and the extra per-wave Q loads and combination cost more than the
+// parallelism gains (4 waves measured 18% slower on the 2048-window sequence
+// workload).
+// Skewed plans: an item above a resident wave's even share of all blocks
+// would outlast the launch, so 4 waves share it; the lighter ones take one
+// wave each.  (Threshold of the share times 0.75, 1, 1.25, 2 on the hub-heavy
+// graph of 65,536 nodes at d = 64: 31.2, 29.5, 30.0, 33.3 us with one head;
+// on a 200,000-node one of exponent 2.2, forward and backward: 307, 306, 313,
+// 332 us.)
+// F3S_WAVES_PER_ITEM=1, 2 or 4 forces one count for all items (read at launch).
+inline WaveSplit wave_split(const f3s_plan_s &p, int32_t heads, int64_t resident)
 {
     const char *e = getenv("F3S_WAVES_PER_ITEM");
     if (e && *e) {
         const int v = atoi(e);
-        return v == 4 ? 4 : v == 2 ? 2 : 1;
+        return WaveSplit{v == 4 ? 4 : v == 2 ? 2 : 1, p.n_items};
     }
-    if (n_items <= 0) return 1;
-    const int64_t waves = n_items * heads;
-    if (waves < 1024 && n_blocks >= 4 * n_items) return 4;
-    if (2 * waves <= resident && n_blocks >= 8 * n_items) return 2;
-    return 1;
+    if (p.n_items <= 0) return WaveSplit{1, p.n_items};
+    if ((p.flags & 1) || (int64_t)p.max_blocks * p.n_items <= 2 * p.n_blocks) {
+        const int64_t waves = (int64_t)p.n_items * heads;
+        if (waves < 1024 && p.n_blocks >= 4ll * p.n_items) return WaveSplit{4, p.n_items};
+        if (2 * waves <= resident && p.n_blocks >= 8ll * p.n_items)
+            return WaveSplit{2, p.n_items};
+        return WaveSplit{1, p.n_items};
+    }
+    const int64_t share = p.n_blocks * heads / resident;
+    int j = 0;
+    while (j < kHeavySteps && heavy_blocks(j) < share) ++j;
+    if (j < kHeavySteps && p.heavy[j] > 0) return WaveSplit{4, p.heavy[j]};
+    return WaveSplit{1, p.n_items};
+}
+// Workgroups per head of such a launch.
+inline int64_t wave_groups(const WaveSplit &ws, int32_t n_items)
+{
+    return ws.shared + ((int64_t)n_items - ws.shared + ws.nw - 1) / ws.nw;
+}
+// The item of wave wv of group g (workgroup / heads), and whether the
+// workgroup's nw waves share it; false: no such item (device code).
+template <int NW>
+__device__ __forceinline__ bool wave_item(int g, int wv, int32_t shared_items, int32_t n_items,
+                                          int *item, bool *shared)
+{
+    *shared = NW == 1 || g < shared_items;
+    *item = *shared ? g : shared_items + (g - shared_items) * NW + wv;
+    return *item < n_items;
 }
 // First row and row count of window w: rows 16 w .. 16 w + 15 (the last
 // window clipped at N), or those given by win_row (device code).
@@ -241,7 +287,7 @@ hipError_t launch_bin_keys(const int32_t *nb, int32_t T, const int32_t *n_blocks
                            const int32_t *max_blocks, int32_t forced, int32_t slots,
                            bool reorder, int32_t *piece_out, int32_t *npieces,
                            int32_t *key, int32_t *split_pieces, int32_t *split_one,
-                           hipStream_t s);
+                           int32_t *heavy, hipStream_t s);
 // Pieces of the split windows: items[split_item[s] + k] for piece k of
 // split window s (merges[3s..3s+2] = window, first slot, pieces).
 hipError_t launch_split_items(const int32_t *merges, const int32_t *split_item,

@@ -174,14 +174,17 @@ __device__ __forceinline__ void store4(void *base, int64_t idx, f4 v)
 // words of a row, each lane taking one word of each of the quad's four
 // 16-byte chunks -- instead of one 16-byte chunk per lane, i.e. the access
 // granularity without the register remapping of Section 3.4.  NW: waves
-// per workgroup sharing one work item -- each takes a contiguous share of
-// its block pairs, and the (m, l, O) partials are combined through LDS at
-// the end (the paper's split-column partition of a window among warps; used
-// for long windows, where one wave per window leaves the GPU with too few
-// waves).  kTrace (a measurement instance): the first thread of each
-// workgroup also records, after its outputs, when the workgroup started and
-// ended (the 100 MHz constant clock) and on which compute unit it ran, as
-// one 32-byte record per workgroup in `trace` (ordinary vector stores).
+// per workgroup.  The first shared_items items are shared by a workgroup's
+// waves -- each takes a contiguous share of the item's block pairs, and the
+// (m, l, O) partials are combined through LDS at the end (the paper's
+// split-column partition of a window among warps; used for long windows,
+// where one wave per window leaves the GPU with too few waves) -- and of the
+// others each wave takes one.
+// kTrace (a measurement instance): the first thread of each
+// item (its first wave) also records, after its outputs, when the item's work
+// started and ended (the 100 MHz constant clock) and on which compute unit it
+// ran, as one 32-byte record per item, in launch order, in `trace` (ordinary
+// vector stores).
 template <int D, bool kWide, int kIn, bool kOutH, bool kNarrow = false, int NW = 1,
           bool kTrace = false>
 __global__ __launch_bounds__(64 * NW)
@@ -191,7 +194,8 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
     const void *__restrict__ Qv, const void *__restrict__ Kv, const void *__restrict__ Vv,
     void *__restrict__ O, float *__restrict__ part_o,
     float *__restrict__ part_ml, float *__restrict__ lse, int32_t N, int32_t ld,
-    int32_t h0, int32_t nh, float sl2, uint32_t order, uint32_t *__restrict__ trace)
+    int32_t h0, int32_t nh, float sl2, uint32_t order, int32_t n_items, int32_t shared_items,
+    uint32_t *__restrict__ trace)
 {
     uint64_t t_start = 0;
     if constexpr (kTrace) t_start = wall_clock64();
@@ -218,15 +222,18 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
     // list per head: with K and V far larger than the caches each head's
     // gathers then stream like a single head's).
     const int wg = workgroup_position(order, nh);
-    int item, hl;
+    int group, hl;
     if (order & kOrderHead) {
-        const int n_it = gridDim.x / nh;
-        hl = wg / n_it;
-        item = wg - hl * n_it;
+        const int n_gr = gridDim.x / nh;
+        hl = wg / n_gr;
+        group = wg - hl * n_gr;
     } else {
-        item = wg / nh;
-        hl = wg - item * nh;
+        group = wg / nh;
+        hl = wg - group * nh;
     }
+    int item;
+    bool shared;
+    if (!wave_item<NW>(group, wv, shared_items, n_items, &item, &shared)) return;
     const int head = h0 + hl;
     const WorkItem it = items[item];
     // Row r of head h starts at r * ld + h * D (elements) in Q, K, V and O.
@@ -245,7 +252,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
     tile_fence<NW>();
     // this wave's blocks: whole pairs [pa, pb) of the item's pairs
     int b0 = it.blk_begin, b1 = it.blk_end;
-    if constexpr (NW > 1) {
+    if (NW > 1 && shared) {
         const int pairs = (b1 - b0 + 1) >> 1;
         const int pa = pairs * wv / NW, pb = pairs * (wv + 1) / NW;
         b1 = min(b1, b0 + 2 * pb);
@@ -487,7 +494,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
         l_tot = l_run + __shfl_xor(l_run, 16);
         l_tot += __shfl_xor(l_tot, 32);
     }
-    if constexpr (NW > 1) {
+    if (NW > 1 && shared) {
         // the waves' partial states: O (lane (i, g) holds columns 16t + 4g ..
         // +3 of row i) into the wave's own tile, which 16 x D floats fit and
         // no longer serves; then wave 0 combines them as the online softmax
@@ -544,7 +551,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
         }
     }
     if constexpr (kTrace) {
-        if (threadIdx.x == 0) {
+        if (lane == 0) {  // (of a shared item only wave 0 gets here)
             const uint64_t t_end = wall_clock64();
             // HW_ID (compute unit, shader array and engine of this wave) and
             // XCC_ID (which of the accelerator complex dies): s_getreg of
@@ -552,10 +559,11 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
             const uint32_t hw = __builtin_amdgcn_s_getreg((31 << 11) | 4);
             const uint32_t xcc = __builtin_amdgcn_s_getreg((15 << 11) | 20);
             typedef uint32_t u4t __attribute__((ext_vector_type(4)));
-            u4t *rec = reinterpret_cast<u4t *>(trace + 8 * (int64_t)blockIdx.x);
+            const uint32_t k = shared ? blockIdx.x : (uint32_t)item;
+            u4t *rec = reinterpret_cast<u4t *>(trace + 8 * (int64_t)k);
             rec[0] = u4t{(uint32_t)t_start, (uint32_t)(t_start >> 32), (uint32_t)t_end,
                          (uint32_t)(t_end >> 32)};
-            rec[1] = u4t{hw, xcc, (uint32_t)blockIdx.x, 0u};
+            rec[1] = u4t{hw, xcc, k, 0u};
         }
     }
 }
@@ -635,7 +643,7 @@ __global__ __launch_bounds__(256) void k_merge(const int32_t *__restrict__ merge
 }
 
 // Heads are launched in groups whose partial results fit the plan's scratch
-// (nh * D <= 256 floats per piece row); without split windows all heads go
+// (nh * D <= part_row floats per piece row); without split windows all heads go
 // in one launch.
 // trace (the measurement instance, fp16 -> fp32 with 32-bit addressing and
 // one head only): one 32-byte record per workgroup.
@@ -647,10 +655,11 @@ hipError_t launch_d(const f3s_plan_s &p, const void *Q, const void *K,
     const int32_t ld = H * D;
     const bool wide = (uint64_t)p.N * ld * elem_bytes<kIn>() > 0xFFFFFFF0ull;
     // the narrow-gather ablation keeps one wave per item
-    const int nw =
-        kNarrow ? 1
-                : waves_per_item(p.n_blocks, p.n_items, H,
-                                 (int64_t)waves_per_simd<D, kIn, kNarrow>() * 1024);
+    // the narrow-gather ablation keeps one wave per item
+    const WaveSplit ws =
+        kNarrow ? WaveSplit{1, p.n_items}
+                : wave_split(p, H, (int64_t)waves_per_simd<D, kIn, kNarrow>() * 1024);
+    const int nw = ws.nw;
     constexpr int W2 = kNarrow ? 1 : 2, W4 = kNarrow ? 1 : 4;
     auto kern = nw == 4   ? (wide ? k_fused3s<D, true, kIn, kOutH, kNarrow, W4>
                                   : k_fused3s<D, false, kIn, kOutH, kNarrow, W4>)
@@ -668,13 +677,13 @@ hipError_t launch_d(const f3s_plan_s &p, const void *Q, const void *K,
             return hipErrorInvalidValue;
         }
     }
-    const int32_t group = p.n_split > 0 ? (kMaxD / D < H ? kMaxD / D : H) : H;
+    const int32_t group = p.n_split > 0 ? (p.part_row / D < H ? p.part_row / D : H) : H;
     for (int32_t h0 = 0; h0 < H; h0 += group) {
         const int32_t nh = H - h0 < group ? H - h0 : group;
-        // the plan's partial buffers hold n_pieces * kMaxD / D head slots
-        if (p.n_split > 0 && (int64_t)nh * D > kMaxD) return hipErrorInvalidValue;
+        // the plan's partial buffers hold n_pieces * part_row / D head slots
+        if (p.n_split > 0 && (int64_t)nh * D > p.part_row) return hipErrorInvalidValue;
         if (p.n_items > 0) {
-            const uint64_t grid = (uint64_t)p.n_items * nh;
+            const uint64_t grid = (uint64_t)wave_groups(ws, p.n_items) * nh;
             if (grid > 0x7FFFFFFFull) return hipErrorInvalidConfiguration;
             const bool head_major =
                 head_major_order(p, nh, 2ull * p.N * ld * elem_bytes<kIn>());
@@ -682,7 +691,7 @@ hipError_t launch_d(const f3s_plan_s &p, const void *Q, const void *K,
                                    (xcd_chunks(p, nh, head_major) ? kOrderXcd : 0u);
             kern<<<(unsigned)grid, 64 * nw, 0, s>>>(p.items, p.cols, p.mask, p.win_row, Q, K,
                                                V, O, p.part_o, p.part_ml, lse, p.N, ld, h0,
-                                               nh, sl2, order, trace);
+                                               nh, sl2, order, p.n_items, ws.shared, trace);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }

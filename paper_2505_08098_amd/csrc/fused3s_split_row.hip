@@ -251,7 +251,7 @@ hipError_t launch_split_row_d(const f3s_plan_s &p, const void *Q, const void *K,
     constexpr int NW = SplitRowWaves<D>::value;
     const int32_t ld = H * D;
     if ((uint64_t)p.N * ld * 2 > 0xFFFFFFF0ull) return hipErrorInvalidValue;
-    const int32_t group = p.n_split > 0 ? (kMaxD / D < H ? kMaxD / D : H) : H;
+    const int32_t group = p.n_split > 0 ? (p.part_row / D < H ? p.part_row / D : H) : H;
     for (int32_t h0 = 0; h0 < H; h0 += group) {
         const int32_t nh = H - h0 < group ? H - h0 : group;
         if (p.n_items > 0) {

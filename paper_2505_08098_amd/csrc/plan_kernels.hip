@@ -796,13 +796,22 @@ __global__ __launch_bounds__(256) void k_fill_windows(
     for (int k = threadIdx.x; k < kMaskWords * nbw; k += 256) mdst[k] = msrc[k];
 }
 
-// Work-list piece size (even): about n_blocks / slots blocks (slots = 8 per
-// CU), so the work list has of the order of 8 items per CU, at least 16
-// blocks (smaller pieces help the forward on tiny graphs a little but add
-// merge launches to the backward); never above the largest window (a larger
-// value splits nothing and only widens the bucket histogram of the work-list
-// sort).  forced >= 2 overrides the estimate.
-__device__ int32_t plan_piece(int64_t n_blocks, int32_t max_blocks, int32_t forced,
+// Work-list piece size (even).  Pieces cost a partial result of 16 rows
+// through memory and a merge launch (6 to 18 us a call on the hub-heavy
+// graph when the pieces were a quarter of this), so a window stays whole as
+// long as the 4 waves of a workgroup get through it while the launch runs:
+// about 4 n_blocks / slots blocks (slots = 8 per CU), twice a resident wave's
+// even share for each of the 4 waves; at least 64 blocks and 1.5 times the
+// mean window, and 128 for nearly uniform windows (the largest at most twice
+// the mean: all are as long and splitting balances nothing).  Never above the largest window (a larger
+// value splits nothing and only widens the histogram of the work-list sort),
+// nor a little below it.  forced >= 2 overrides the estimate.  Measured
+// against pieces of n_blocks / slots, at least 16, and one wave per item:
+// hub-heavy graph, N = 65,536, d = 64, forward 33.5 -> 29.3 us, 4 bf16 heads
+// forward and backward 421 -> 372 us; sequence of 16,001 tokens, 2 heads of
+// d = 128, forward and backward 303 -> 233 us; ER graph of 10,007 nodes, 16
+// neighbours, 2 heads 56 -> 37 us.
+__device__ int32_t plan_piece(int64_t n_blocks, int32_t max_blocks, int32_t T, int32_t forced,
                               int32_t slots)
 {
     const int64_t cap = ((int64_t)(max_blocks > 2 ? max_blocks : 2) + 1) & ~1LL;
@@ -810,29 +819,45 @@ __device__ int32_t plan_piece(int64_t n_blocks, int32_t max_blocks, int32_t forc
     if (forced >= 2) {
         piece = forced & ~1;
     } else {
-        piece = (n_blocks + slots - 1) / slots;
-        if (piece < 16) piece = 16;
+        const bool uniform = (int64_t)max_blocks * T <= 2 * n_blocks;
+        int64_t least = uniform ? 128 : 64;
+        if (2 * least * T < 3 * n_blocks) least = 3 * n_blocks / (2 * (int64_t)T);
+        piece = (4 * n_blocks + slots - 1) / slots;
+        if (piece < least) piece = least;
         piece = (piece + 1) & ~1LL;
+        if (2 * cap <= 3 * piece) piece = cap;
     }
     return (int32_t)(piece < cap ? piece : cap);
 }
 
-__global__ void k_bin_keys(const int32_t *nb, int32_t T, const int32_t *n_blocks,
-                           const int32_t *max_blocks, int32_t forced, int32_t slots,
-                           bool reorder, int32_t *piece_out, int32_t *npieces,
-                           int32_t *key, int32_t *split_pieces, int32_t *split_one)
+// Keys, pieces and split flags per window, and the table of heavy items
+// (heavy[j]: items of windows whose key exceeds heavy_blocks(j), zeroed by
+// the caller).
+__global__ __launch_bounds__(256) void k_bin_keys(
+    const int32_t *nb, int32_t T, const int32_t *n_blocks, const int32_t *max_blocks,
+    int32_t forced, int32_t slots, bool reorder, int32_t *piece_out, int32_t *npieces,
+    int32_t *key, int32_t *split_pieces, int32_t *split_one, int32_t *heavy)
 {
+    __shared__ int32_t cnt[kHeavySteps];
     const int w = blockIdx.x * blockDim.x + threadIdx.x;
-    const int32_t piece = plan_piece(*n_blocks, *max_blocks, forced, slots);
+    if (threadIdx.x < kHeavySteps) cnt[threadIdx.x] = 0;
+    __syncthreads();
+    const int32_t piece = plan_piece(*n_blocks, *max_blocks, T, forced, slots);
     if (w == 0) *piece_out = piece;
-    if (w >= T) return;
-    const int n = nb[w];
-    const bool split = n > piece;
-    const int np = split ? (n + piece - 1) / piece : 1;
-    npieces[w] = np;
-    key[w] = reorder ? (split ? piece : n) : 0;
-    split_pieces[w] = split ? np : 0;
-    split_one[w] = split ? 1 : 0;
+    if (w < T) {
+        const int n = nb[w];
+        const bool split = n > piece;
+        const int np = split ? (n + piece - 1) / piece : 1;
+        const int k = split ? piece : n;
+        npieces[w] = np;
+        key[w] = reorder ? k : 0;
+        split_pieces[w] = split ? np : 0;
+        split_one[w] = split ? 1 : 0;
+        for (int j = 0; j < kHeavySteps && k > heavy_blocks(j); ++j) atomicAdd(&cnt[j], np);
+    }
+    __syncthreads();
+    if (threadIdx.x < kHeavySteps && cnt[threadIdx.x])
+        atomicAdd(&heavy[threadIdx.x], cnt[threadIdx.x]);
 }
 
 // Work items of the pieces of split window s (one wavefront per split
@@ -1039,11 +1064,11 @@ hipError_t launch_bin_keys(const int32_t *nb, int32_t T, const int32_t *n_blocks
                            const int32_t *max_blocks, int32_t forced, int32_t slots,
                            bool reorder, int32_t *piece_out, int32_t *npieces,
                            int32_t *key, int32_t *split_pieces, int32_t *split_one,
-                           hipStream_t s)
+                           int32_t *heavy, hipStream_t s)
 {
     k_bin_keys<<<grid_for(T, 256), 256, 0, s>>>(nb, T, n_blocks, max_blocks, forced, slots,
                                                 reorder, piece_out, npieces, key,
-                                                split_pieces, split_one);
+                                                split_pieces, split_one, heavy);
     return hipGetLastError();
 }
 

@@ -90,3 +90,73 @@ def test_masked_overflow_stays_with_its_row(gpu, dtype):
             p = np.exp(s - s.max())
             ref[i] = (p / p.sum()) @ v[rows[i]]
     _check(O[keep], ref[keep])
+
+
+def _skewed(rng, N, hubs, hub_deg, deg):
+    """Rows of up to ``deg`` random entries, the rows of every ``hubs``-th
+    window of up to ``hub_deg``: a heavy-first list with both kinds of item."""
+    rows = []
+    for i in range(N):
+        top = hub_deg if (i // 16) % hubs == 0 else deg
+        rows.append(np.sort(rng.choice(N, size=int(rng.integers(1, top + 1)), replace=False)))
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    return rp, np.concatenate(rows).astype(np.int32)
+
+
+# windows on either side of the waves' grouping: a last workgroup of one, two
+# and three single-wave items; hub windows below and above the piece size
+@pytest.mark.parametrize("N,hubs,hub_deg", [(16 * 61, 7, 300), (16 * 62 + 5, 9, 900),
+                                            (16 * 150 + 1, 40, 1500)])
+@pytest.mark.parametrize("H,d,dtype", [(1, 64, "f16"), (3, 32, "bf16"), (2, 128, "f16")])
+def test_heavy_items_shared_by_four_waves(gpu, N, hubs, hub_deg, H, d, dtype, monkeypatch):
+    """Heavy items shared by a workgroup's waves beside light ones of one wave
+    each, forward and backward, against the oracle and one wave per item."""
+    rng = np.random.default_rng(N + d)
+    rp, ci = _skewed(rng, N, hubs, hub_deg, 6)
+    t = torch.float16 if dtype == "f16" else torch.bfloat16
+    Q, K, V, G = (torch.from_numpy(rng.standard_normal((N, H, d)).astype(np.float32)).to(t)
+                  for _ in range(4))
+    q, k, v, g = (x.cuda() for x in (Q, K, V, G))
+    plan = gpu.Plan(_dev(rp), _dev(ci), N)
+    plan_t = plan.transpose()
+    i = plan.info
+    assert i["max_blocks"] * i["n_items"] > 2 * i["n_blocks"]   # a skewed plan
+    assert i["max_blocks"] > 8                                  # with items to share
+
+    def both():
+        O, lse = gpu.forward_typed(plan, q, k, v, scale=0.1, want_lse=True)
+        return (O, lse) + gpu.backward(plan, plan_t, q, k, v, O, g, lse, scale=0.1)
+
+    got = both()
+    monkeypatch.setenv("F3S_WAVES_PER_ITEM", "1")
+    one = both()
+    monkeypatch.delenv("F3S_WAVES_PER_ITEM")
+    # fp32 sums in another order: about sqrt(terms) roundings of 2^-24, and
+    # 16-bit roundings of P and dS that may fall the other way (2^-11 / 2^-16)
+    bound = 1e-3 if dtype == "f16" else 2e-5
+    for a, b in zip(got, one):
+        assert float((a - b).norm()) <= bound * float(b.norm())
+    if dtype == "f16":
+        for h in range(H):
+            q1, k1, v1 = (x[:, h].numpy() for x in (Q, K, V))
+            _check(got[0][:, h], oracle.attention_f64(rp, ci, q1, k1, v1, 0.1))
+
+
+def test_uniform_windows_stay_whole(gpu):
+    """Windows of about the same size are not split for being a little above
+    the mean; one far above it is."""
+    rng = np.random.default_rng(3)
+    N = 4096
+    rows = [np.sort(rng.choice(N, size=90 + int(rng.integers(0, 8)), replace=False))
+            for _ in range(N)]
+    for heavy in (False, True):
+        if heavy:
+            for i in range(16):
+                rows[i] = np.arange(N)
+        rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+        ci = np.concatenate(rows).astype(np.int32)
+        plan = gpu.Plan(_dev(rp), _dev(ci), N)
+        assert plan.info["n_split"] == (1 if heavy else 0)
+        Q, K, V = W.features(rng, N, 64)
+        _check(gpu.run(plan, _dev(Q), _dev(K), _dev(V)),
+               oracle.attention_f64(rp, ci, Q, K, V, 0.125))
