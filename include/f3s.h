@@ -119,7 +119,7 @@ f3s_plan_t f3s_plan(const int32_t *row_ptr, const int32_t *col_idx, int32_t N);
 
 /*
  * Device bytes of scratch a build of f3s_plan_ws needs for a pattern of N
- * rows and nnz CSR entries: 6 bytes per entry plus about 110 per row
+ * rows and nnz CSR entries: 6 bytes per entry plus about 100 per row
  * window (0 for negative sizes).  Host-only; calls no HIP function.
  */
 size_t f3s_plan_workspace_bytes(int32_t N, int64_t nnz);
@@ -257,7 +257,8 @@ f3s_status_t f3s_forward_typed(f3s_plan_t plan, const void *Q, const void *K, co
  * (its bitmaps list A's entries).  Needed by f3s_backward: the gradients of
  * K and V are sums over the rows that attend to a key, i.e. over the rows of
  * A^T, so each window of A^T owns its keys' gradients (no atomics).  An
- * exact symmetry check first: if A^T = A the result is a copy of the plan.
+ * exact symmetry check first: if A^T = A the result shares the plan's arrays
+ * (either may be destroyed first).
  * The check runs on the plan for patterns below 8 M entries and on the
  * sorted rows of A^T above (environment F3S_SYMMETRY_SORT_FIRST=<entries>
  * moves that threshold; 0 always sorts first).  A plan of f3s_plan_segments

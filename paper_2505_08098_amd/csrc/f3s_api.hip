@@ -77,7 +77,11 @@ struct ScratchArena : Arena {
 
 void free_plan_arrays(f3s_plan_s *p)
 {
-    if (p->store) (void)hipFree(p->store);
+    if (p->store && p->store_refs->fetch_sub(1) == 1) {
+        (void)hipFree(p->store);
+        delete p->store_refs;
+    }
+    p->store_refs = nullptr;
     if (p->part_store) (void)hipFree(p->part_store);
     p->store = p->part_store = nullptr;
     p->blk_off = nullptr;
@@ -127,9 +131,9 @@ hipError_t alloc_parts(f3s_plan_s *p, int32_t part_row)
 
 // The plan's arrays in one allocation, laid out from its counts (T, blocks,
 // items, split windows): blk_off, cols, mask, items, merges, and the window
-// rows of a plan aligned to the graphs of a batch.  Returns the allocation's
-// size in *bytes.
-hipError_t alloc_store(f3s_plan_s *p, size_t *bytes)
+// rows of a plan aligned to the graphs of a batch.  Nothing writes to them
+// once the plan is built, so plans may share the allocation.
+hipError_t alloc_store(f3s_plan_s *p)
 {
     using namespace f3s;
     const int64_t B = p->n_blocks;
@@ -140,9 +144,16 @@ hipError_t alloc_store(f3s_plan_s *p, size_t *bytes)
     a.add<WorkItem>(p->n_items);
     a.add<int32_t>(3ll * p->n_split);
     if (p->flags & 4) a.add<int32_t>((int64_t)p->T + 1);
+    p->store_refs = new (std::nothrow) std::atomic<int>(1);
+    if (!p->store_refs) return hipErrorOutOfMemory;
     hipError_t e = a.alloc();
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess) {
+        delete p->store_refs;
+        p->store_refs = nullptr;
+        return e;
+    }
     p->store = a.base;
+    p->store_bytes = (int64_t)a.cap;
     p->device_bytes += (int64_t)a.cap;
     p->blk_off = a.take<int32_t>((int64_t)p->T + 1);
     p->cols = a.take<int32_t>((int64_t)kBlockCols * B);
@@ -150,7 +161,6 @@ hipError_t alloc_store(f3s_plan_s *p, size_t *bytes)
     p->items = a.take<WorkItem>(p->n_items);
     p->merges = a.take<int32_t>(3ll * p->n_split);
     p->win_row = (p->flags & 4) ? a.take<int32_t>((int64_t)p->T + 1) : nullptr;
-    if (bytes) *bytes = a.cap;
     return hipSuccess;
 }
 
@@ -186,33 +196,15 @@ int32_t plan_slots(int device)
     return 8 * cus;
 }
 
-// Device-side statistics of a plan build, read back with one copy each
-// time the host needs them.
-struct BuildStats {
-    unsigned long long n_unique;  // sum of distinct columns over windows
-    unsigned long long nnz;       // set bits of all bitmaps
-    int32_t err;                  // malformed CSR
-    int32_t n_big;                // windows too large for one wavefront
-    int32_t n_heavy;              // windows too large for the LDS sort
-    int32_t max_blocks;
-    int32_t n_blocks;
-    int32_t piece;
-    int32_t n_pieces;
-    int32_t n_split;
-    int32_t n_items;              // item count from the work-list scan
-    int32_t invalid;              // plan integrity check
-    int32_t heavy[f3s::kHeavySteps];  // items above kHeavyBlocks << j blocks
-};
-
 // Pointers into the plan build's scratch.
 struct BuildScratch {
-    BuildStats *st;
+    f3s::BuildStats *st;
     int32_t *tmp_cols;   // sorted distinct columns per window, at its CSR offset
     uint32_t *tmp_mask;  // block bitmaps per window, staged
-    int32_t *u, *big, *is_big, *heavy, *is_heavy, *bits, *nb, *npieces, *key, *split_item;
-    int32_t *big_pos, *heavy_pos, *split_pieces, *split_one, *scan_tmp;
+    int32_t *u, *mid, *big, *heavy, *bits, *nb, *key, *pos;
+    int32_t *blk_off, *slot_base, *split_idx, *scan_tmp;
     int32_t *win_row;    // the windows' first rows (null: 16-row windows)
-    f3s::WorkListScratch wl;  // the work-list sort
+    f3s::RadixScratch radix;  // the work-list sort
 };
 
 template <typename U>
@@ -240,28 +232,44 @@ void carve_scratch(Arena &a, bool take, BuildScratch &b, int32_t T, int64_t nnz,
     b.win_row = rows ? carve<int32_t>(a, take, (int64_t)T + 1) : nullptr;
     b.tmp_cols = carve<int32_t>(a, take, nnz);
     b.tmp_mask = carve<uint32_t>(a, take, mask_stage_words(nnz, T));
-    int32_t **per_window[] = {&b.u, &b.big, &b.is_big, &b.heavy, &b.is_heavy,
-                              &b.bits, &b.nb, &b.npieces, &b.key, &b.split_item};
+    int32_t **per_window[] = {&b.u, &b.mid, &b.big, &b.heavy, &b.bits, &b.nb, &b.key, &b.pos};
     for (int32_t **q : per_window) *q = carve<int32_t>(a, take, T);
-    int32_t **per_window1[] = {&b.big_pos, &b.heavy_pos, &b.split_pieces, &b.split_one};
+    int32_t **per_window1[] = {&b.blk_off, &b.slot_base, &b.split_idx};
     for (int32_t **q : per_window1) *q = carve<int32_t>(a, take, (int64_t)T + 1);
     const int64_t rc = radix_count_ints(T);
     b.scan_tmp = carve<int32_t>(a, take, scan_tmp_ints(T > rc ? T : rc));
-    b.wl.pos = carve<int32_t>(a, take, (int64_t)T + 1);
-    int32_t **radix_arrays[] = {&b.wl.radix.keys_a, &b.wl.radix.vals_a, &b.wl.radix.keys_b,
-                                &b.wl.radix.vals_b};
+    int32_t **radix_arrays[] = {&b.radix.keys_a, &b.radix.vals_a, &b.radix.keys_b,
+                                &b.radix.vals_b};
     for (int32_t **q : radix_arrays) *q = carve<int32_t>(a, take, T);
-    b.wl.radix.counts = carve<int32_t>(a, take, rc);
-    b.wl.radix.scan_tmp = b.scan_tmp;
+    b.radix.counts = carve<int32_t>(a, take, rc);
+    b.radix.scan_tmp = b.scan_tmp;
+}
+
+size_t scratch_bytes(int32_t T, int64_t nnz, bool rows = false)
+{
+    Arena a;
+    BuildScratch b;
+    carve_scratch(a, false, b, T, nnz, rows);
+    return a.cap;
 }
 
 size_t plan_workspace_bytes(int32_t N, int64_t nnz)
 {
-    Arena a;
-    BuildScratch b;
-    const int32_t T = num_windows(N);
-    carve_scratch(a, false, b, T, nnz);
-    return a.cap;
+    return scratch_bytes(num_windows(N), nnz);
+}
+
+// The most CSR entries (below 2^31) whose scratch fits into `bytes`, -1 if
+// not even an empty pattern's does.
+int64_t scratch_capacity(int32_t T, size_t bytes)
+{
+    if (scratch_bytes(T, 0) > bytes) return -1;
+    int64_t lo = 0, hi = INT32_MAX;  // lo fits
+    while (lo < hi) {
+        const int64_t mid = lo + (hi - lo + 1) / 2;
+        if (scratch_bytes(T, mid) <= bytes) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
 }
 
 // win_rows: the windows' first rows and N (T + 1 ints, host memory), or null
@@ -275,69 +283,44 @@ f3s_status_t build_plan(f3s_plan_s *p, const int32_t *row_ptr, const int32_t *co
     const int32_t N = p->N;
     const int32_t T = p->T;
 
-    // ---- 1. nnz (row_ptr[0] == 0 and monotonicity are checked on the GPU)
-    int32_t nnz = 0;
-    HIP_TRY(hipMemcpy(&nnz, row_ptr + N, sizeof(int32_t), hipMemcpyDeviceToHost));
-    if (nnz < 0) return F3S_ERR_INVALID_CSR;
-    if (nnz > 0 && !col_idx) return F3S_ERR_INVALID_VALUE;
-    p->nnz_csr = nnz;
-
-    // all scratch of the build in one allocation (or the caller's workspace)
+    // ---- 1. scratch: in the caller's workspace, laid out for the entries
+    //         that fit it (nnz itself is read and checked on the GPU, without
+    //         a round trip), or one allocation once nnz is known -----------
     const int32_t slots = plan_slots(p->device);
     BuildScratch b;
     ScratchArena tmp;
-    carve_scratch(tmp, false, b, T, nnz, win_rows != nullptr);
+    int64_t nnz_cap;
     if (workspace) {
-        if (workspace_bytes < tmp.cap || ((uintptr_t)workspace & 255u))
-            return F3S_ERR_INVALID_VALUE;
+        if ((uintptr_t)workspace & 255u) return F3S_ERR_INVALID_VALUE;
+        nnz_cap = scratch_capacity(T, workspace_bytes);
+        if (nnz_cap < 0) return F3S_ERR_INVALID_VALUE;
         tmp.base = static_cast<char *>(workspace);
         tmp.owned = false;
     } else {
+        int32_t nnz = 0;
+        HIP_TRY(hipMemcpy(&nnz, row_ptr + N, sizeof(int32_t), hipMemcpyDeviceToHost));
+        if (nnz < 0) return F3S_ERR_INVALID_CSR;
+        if (nnz > 0 && !col_idx) return F3S_ERR_INVALID_VALUE;
+        nnz_cap = nnz;
+        carve_scratch(tmp, false, b, T, nnz_cap, win_rows != nullptr);
         HIP_TRY(tmp.alloc());
     }
-    carve_scratch(tmp, true, b, T, nnz, win_rows != nullptr);
+    carve_scratch(tmp, true, b, T, nnz_cap, win_rows != nullptr);
     const int32_t *wr = b.win_row;
     if (wr)
         HIP_TRY(hipMemcpy(b.win_row, win_rows, sizeof(int32_t) * ((size_t)T + 1),
                           hipMemcpyHostToDevice));
     BuildStats *st = b.st;
-    int32_t *tmp_cols = b.tmp_cols;
-    uint32_t *tmp_mask = b.tmp_mask;
-    int32_t *u = b.u, *big = b.big, *is_big = b.is_big, *heavy = b.heavy;
-    int32_t *is_heavy = b.is_heavy, *bits = b.bits, *nb = b.nb, *npieces = b.npieces;
-    int32_t *key = b.key, *split_item = b.split_item, *big_pos = b.big_pos;
-    int32_t *heavy_pos = b.heavy_pos, *split_pieces = b.split_pieces;
-    int32_t *split_one = b.split_one, *scan_tmp = b.scan_tmp;
     BuildStats hs;
-    HIP_TRY(hipMemsetAsync(st, 0, sizeof(BuildStats), s));
 
     // ---- 2. CSR check, distinct columns and bitmaps per window ----------
-    HIP_TRY(launch_check_row_ptr(row_ptr, N, nnz, &st->err, s));
-    HIP_TRY(launch_window_wave(row_ptr, col_idx, N, wr, T, tmp_cols, tmp_mask, u, is_big,
-                               is_heavy, bits, &st->err, s));
-    {  // the flagged windows listed in window order
-        ScanArray fb, fh;
-        fb.in = is_big;
-        fb.out = big_pos;
-        fb.total = &st->n_big;
-        fb.list = big;
-        fh.in = is_heavy;
-        fh.out = heavy_pos;
-        fh.total = &st->n_heavy;
-        fh.list = heavy;
-        HIP_TRY(launch_scan2(fb, fh, T, scan_tmp, s));
-    }
-    HIP_TRY(hipMemcpy(&hs, st, sizeof hs, hipMemcpyDeviceToHost));
-    if (hs.err) return F3S_ERR_INVALID_CSR;
-    HIP_TRY(launch_window_sort(row_ptr, col_idx, N, wr, big, hs.n_big, tmp_cols, tmp_mask,
-                               u, bits, &st->err, s));
-    HIP_TRY(launch_heavy_lds(row_ptr, col_idx, N, wr, heavy, hs.n_heavy, tmp_cols,
-                             tmp_mask, u, bits, &st->err, s));
+    HIP_TRY(launch_classify(row_ptr, N, wr, T, nnz_cap, col_idx != nullptr, st, b.mid, b.big,
+                            b.heavy, s));
+    HIP_TRY(launch_windows(row_ptr, col_idx, N, wr, T, nnz_cap, st, b.mid, b.big, b.heavy,
+                           b.tmp_cols, b.tmp_mask, b.u, b.bits, s));
 
     // ---- 3. blocks per window and statistics; work-list shape: piece size,
     //         split windows, item count (one host round trip for all) -------
-    HIP_TRY(launch_window_stats(u, bits, T, nb, &st->n_unique, &st->nnz, &st->n_blocks,
-                                &st->max_blocks, s));
     // F3S_NO_REORDER=1 keeps window order, =0 always sorts; unset, the order
     // is chosen below once the block counts are known
     const char *order_env = getenv("F3S_NO_REORDER");
@@ -345,20 +328,13 @@ f3s_status_t build_plan(f3s_plan_s *p, const int32_t *row_ptr, const int32_t *co
     const bool reorder = !order_forced || atoi(order_env) == 0;
     p->flags = (reorder ? 0 : 1) | (env_int("F3S_NARROW_GATHER", 0) ? 2 : 0) | (wr ? 4 : 0) |
                (env_int("F3S_SPLIT_ROW", 0) ? 8 : 0);
-    HIP_TRY(launch_bin_keys(nb, T, &st->n_blocks, &st->max_blocks,
-                            env_int("F3S_PIECE_BLOCKS", 0), slots, reorder,
-                            &st->piece, npieces, key, split_pieces, split_one, st->heavy,
-                            s));
-    {
-        ScanArray sp, so;
-        sp.in = sp.out = split_pieces;
-        sp.total = &st->n_pieces;
-        so.in = so.out = split_one;
-        so.total = &st->n_split;
-        HIP_TRY(launch_scan2(sp, so, T, scan_tmp, s));
-    }
+    HIP_TRY(launch_shape(b.u, b.bits, T, env_int("F3S_PIECE_BLOCKS", 0), slots,
+                         !reorder ? kOrderWindow : order_forced ? kOrderSorted : kOrderAuto, st,
+                         b.nb, b.blk_off, b.key, b.slot_base, b.split_idx, b.pos, b.scan_tmp,
+                         s));
     HIP_TRY(hipMemcpy(&hs, st, sizeof hs, hipMemcpyDeviceToHost));
-    if (hs.err) return F3S_ERR_INVALID_CSR;
+    if (hs.err) return hs.err == kBuildBadValue ? F3S_ERR_INVALID_VALUE : F3S_ERR_INVALID_CSR;
+    p->nnz_csr = hs.nnz_csr;
     const int32_t B = hs.n_blocks;
     p->n_blocks = B;
     p->n_unique = (int64_t)hs.n_unique;
@@ -369,7 +345,6 @@ f3s_status_t build_plan(f3s_plan_s *p, const int32_t *row_ptr, const int32_t *co
     p->piece = piece;
     p->n_pieces = hs.n_pieces;
     p->n_split = hs.n_split;
-    memcpy(p->heavy, hs.heavy, sizeof p->heavy);
     const int64_t n_items = (int64_t)T - p->n_split + p->n_pieces;
     if (n_items > INT32_MAX) return F3S_ERR_UNSUPPORTED;
     p->n_items = (int32_t)n_items;
@@ -382,28 +357,28 @@ f3s_status_t build_plan(f3s_plan_s *p, const int32_t *row_ptr, const int32_t *co
     const bool window_order = (p->flags & 1) != 0;
 
     // ---- 4. the plan's arrays: one allocation, plus the partial buffers --
-    HIP_TRY(alloc_store(p, nullptr));
+    HIP_TRY(alloc_store(p));
     HIP_TRY(alloc_parts(p, part_row));
-    HIP_TRY(launch_scan(nb, p->blk_off, T, scan_tmp, nullptr, s));  // window block offsets
     if (wr)
         HIP_TRY(hipMemcpyAsync(p->win_row, wr, sizeof(int32_t) * ((size_t)T + 1),
                                hipMemcpyDeviceToDevice, s));
 
-    // ---- 5. column lists and bitmaps into their blocks --------------------
-    HIP_TRY(launch_fill_windows(row_ptr, wr, T, tmp_cols, tmp_mask, u, p->blk_off, p->cols,
-                                p->mask, s));
+    // ---- 5. column lists and bitmaps into their blocks, work list: in
+    //         with them where its order is decided, else after them -----------
+    const WorkListShape shape{b.blk_off, b.slot_base, b.split_idx,
+                              piece,     p->n_pieces, p->n_split};
+    const bool placed = hs.placed || window_order;
+    HIP_TRY(launch_fill_windows(row_ptr, wr, T, b.tmp_cols, b.tmp_mask, b.u, p->blk_off,
+                                p->cols, p->mask, shape, hs.placed ? b.pos : nullptr,
+                                placed ? p->items : nullptr, p->merges, s));
+    if (!placed)
+        HIP_TRY(launch_worklist(b.key, shape, T, b.radix, p->items, p->merges, st->heavy, s));
 
-    // ---- 6. work list: windows stably sorted by key, heavy first (or kept
-    //         in window order) ----------------------------------------------
-    HIP_TRY(launch_worklist(key, nb, p->blk_off, npieces, split_pieces, split_one, T, piece,
-                            window_order, b.wl, p->items, p->merges, split_item,
-                            &st->n_items, s));
-    HIP_TRY(launch_split_items(p->merges, split_item, p->blk_off, p->n_split, p->items, s));
-
-    // ---- 7. integrity check of the finished plan ------------------------
+    // ---- 6. integrity check of the finished plan ------------------------
     HIP_TRY(launch_validate_plan(*p, &st->invalid, s));
     HIP_TRY(hipMemcpy(&hs, st, sizeof hs, hipMemcpyDeviceToHost));
-    if (hs.invalid || hs.n_items != p->n_items) return F3S_ERR_HIP;
+    if (hs.invalid) return F3S_ERR_HIP;
+    memcpy(p->heavy, hs.heavy, sizeof p->heavy);
     return F3S_OK;
 }
 
@@ -424,8 +399,8 @@ bool overlaps(const void *a, size_t na, const void *b, size_t nb)
     return x < y + nb && y < x + na;
 }
 
-// A copy of plan src (same arrays, new id) whose split-window partials hold
-// part_row floats per row.
+// A copy of plan src (the same arrays, shared with it; new id) whose
+// split-window partials hold part_row floats per row.
 f3s_plan_t clone_plan(const f3s_plan_s *src, int32_t part_row)
 {
     f3s_plan_s *t = new (std::nothrow) f3s_plan_s(*src);
@@ -434,17 +409,14 @@ f3s_plan_t clone_plan(const f3s_plan_s *src, int32_t part_row)
         return nullptr;
     }
     t->nnz_csr = t->nnz;  // the pattern without duplicate entries, like A^T's CSR
-    t->store = t->part_store = nullptr;
+    if (t->store) t->store_refs->fetch_add(1);
+    t->part_store = nullptr;
     t->part_o = t->part_ml = nullptr;
     t->part_bytes = 0;
-    t->device_bytes = 0;
+    t->device_bytes = t->store_bytes;
     t->id = g_next_plan_id.fetch_add(1);
     t->transpose_of = 0;
-    size_t bytes = 0;
-    hipError_t e = alloc_store(t, &bytes);
-    if (e == hipSuccess)
-        e = hipMemcpy(t->store, src->store, bytes, hipMemcpyDeviceToDevice);
-    if (e == hipSuccess) e = alloc_parts(t, part_row);
+    const hipError_t e = alloc_parts(t, part_row);
     if (e != hipSuccess) {
         free_plan_arrays(t);
         delete t;
@@ -477,7 +449,7 @@ f3s_plan_t make_plan(const int32_t *row_ptr, const int32_t *col_idx, int32_t N,
     f3s_status_t st = from_hip(hipGetDevice(&p->device));
     if (st == F3S_OK) {
         if (N == 0) {
-            st = from_hip(alloc_store(p, nullptr));
+            st = from_hip(alloc_store(p));
             if (st == F3S_OK) st = from_hip(hipMemset(p->blk_off, 0, sizeof(int32_t)));
             p->piece = 16;
             p->part_row = part_row;
@@ -604,10 +576,10 @@ f3s_plan_t make_transpose(f3s_plan_t src, void *workspace, size_t workspace_byte
             const bool small = src->nnz < env_int("F3S_SYMMETRY_SORT_FIRST", kSortFirstEntries);
             bool have_csr = false;
             if (!src->win_row) {
-                step(hipMemsetAsync(ts.asym, 0, sizeof(int32_t), nullptr));
                 if (small) {
                     step(f3s::launch_check_symmetric(*src, ts.win, ts.asym, nullptr));
                 } else {
+                    step(hipMemsetAsync(ts.asym, 0, sizeof(int32_t), nullptr));
                     step(f3s::launch_transpose_csr(*src, ts.tr, ts.tr_bytes, ts.rp, ts.ci,
                                                    nullptr));
                     step(f3s::launch_compare_rows(*src, ts.rp, ts.ci, ts.win, ts.pre,

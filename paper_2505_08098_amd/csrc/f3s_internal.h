@@ -5,6 +5,8 @@
 #include <stdint.h>
 #include <stdlib.h>
 
+#include <atomic>
+
 #include "f3s.h"
 
 namespace f3s {
@@ -33,6 +35,13 @@ static_assert(sizeof(WorkItem) == 16, "WorkItem must be 16 bytes");
 // pieces) above heavy_blocks(j) blocks: 8, 10, 12, 14, 16, 20, 24, 28, 32, ...
 constexpr int kHeavySteps = 32;
 __host__ __device__ constexpr int32_t heavy_blocks(int j) { return (8 + 2 * (j & 3)) << (j >> 2); }
+// Steps that k blocks exceed.
+__host__ __device__ inline int heavy_level(int32_t k)
+{
+    int level = 0;
+    while (level < kHeavySteps && k > heavy_blocks(level)) ++level;
+    return level;
+}
 
 }  // namespace f3s
 
@@ -56,7 +65,10 @@ struct f3s_plan_s {
                                  // (heavy-first work lists)
     uint64_t id = 0;             // process-unique plan id
     uint64_t transpose_of = 0;   // id of the plan this one transposes (0: none)
-    void *store = nullptr;       // one allocation: blk_off, cols, mask, items, merges
+    void *store = nullptr;       // one allocation: blk_off, cols, mask, items, merges,
+                                 // shared with the transposed plan of a symmetric pattern
+    std::atomic<int> *store_refs = nullptr;  // plans that hold it
+    int64_t store_bytes = 0;
     void *part_store = nullptr;  // one allocation: part_o, part_ml
     int64_t part_bytes = 0;
     int32_t *blk_off = nullptr;  // [T + 1]
@@ -82,6 +94,44 @@ struct f3s_plan_s {
 namespace f3s {
 
 // ---- plan kernels (plan_kernels.hip) ------------------------------------
+// What places the items of a window in the work list.  Window w, R-th in the
+// list's window order, starts at item
+//   R + slot_base[w] - split_idx[w]    if its key is the largest (the split
+//                                      windows', or all keys are equal)
+//   R + n_pieces - n_split             otherwise:
+// of the windows before it, the split ones have taken their pieces, the
+// others one item each.
+struct WorkListShape {
+    const int32_t *blk_off;    // [T + 1]
+    const int32_t *slot_base;  // [T + 1] pieces of the split windows before w
+    const int32_t *split_idx;  // [T + 1] split windows before w
+    int32_t piece, n_pieces, n_split;
+};
+// Writes window w's items from position pos on, one wavefront's lanes (or a
+// workgroup's threads) sharing the pieces: piece k of np covers the block
+// pairs [floor(k pairs / np), floor((k + 1) pairs / np)).
+__device__ __forceinline__ void place_window(const WorkListShape &sh, int32_t w, int32_t pos,
+                                             int tid, int threads, WorkItem *items,
+                                             int32_t *merges)
+{
+    const int32_t b0 = sh.blk_off[w], n = sh.blk_off[w + 1] - b0;
+    if (n <= sh.piece) {
+        if (tid == 0) items[pos] = WorkItem{w, b0, b0 + n, -1};
+        return;
+    }
+    const int32_t s = sh.split_idx[w], slot = sh.slot_base[w];
+    const int32_t np = (n + sh.piece - 1) / sh.piece;
+    if (tid == 0) {
+        merges[3 * s + 0] = w;
+        merges[3 * s + 1] = slot;
+        merges[3 * s + 2] = np;
+    }
+    const int64_t pairs = (n + 1) / 2;
+    for (int k = tid; k < np; k += threads) {
+        const int a = (int)((k * pairs) / np), b = (int)(((k + 1) * pairs) / np);
+        items[pos + k] = WorkItem{w, b0 + 2 * a, b0 + min(n, 2 * b), slot + k};
+    }
+}
 // Workgroup order flags of the fused kernels: heads outermost (one pass over
 // the work list per head), and consecutive ranges of the order per XCD.
 constexpr uint32_t kOrderHead = 1u;
@@ -90,7 +140,7 @@ constexpr uint32_t kOrderXcd = 2u;
 // holding at most twice the mean block count.  Their work list keeps window
 // order (heavy-first sorting has nothing to balance), and launches of 1, 2,
 // 4 or 8 heads give each XCD a consecutive range of it.
-inline bool uniform_windows(int64_t windows, int64_t blocks, int64_t max_blocks)
+__host__ __device__ inline bool uniform_windows(int64_t windows, int64_t blocks, int64_t max_blocks)
 {
     return windows >= 2048 && max_blocks * windows <= 2 * blocks;
 }
@@ -212,49 +262,59 @@ __device__ __forceinline__ void window_rows(const int32_t *win_row, int32_t N, i
         *nr = min(kWindowRows, N - *r0);
     }
 }
-// Inclusive sum over the lanes of a wavefront (device code).
+// Inclusive sum over the 64 lanes of a wavefront (all active), with DPP row
+// shifts (within rows of 16 lanes, out-of-row sources read 0) and the first
+// three row totals by readlane (device code).
 __device__ __forceinline__ int wave_inclusive_sum(int x, int lane)
 {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int t = __shfl_up(x, off, 64);
-        if (lane >= off) x += t;
-    }
-    return x;
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);  // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);  // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);  // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);  // row_shr:8
+    const int r0 = __builtin_amdgcn_readlane(x, 15), r1 = __builtin_amdgcn_readlane(x, 31);
+    const int r2 = __builtin_amdgcn_readlane(x, 47);
+    const int row = lane >> 4;
+    return x + (row >= 1 ? r0 : 0) + (row >= 2 ? r1 : 0) + (row >= 3 ? r2 : 0);
 }
 
-hipError_t launch_check_row_ptr(const int32_t *row_ptr, int32_t N, int32_t nnz,
-                                int32_t *err, hipStream_t s);
+// Device-side statistics of a plan build, read back with one copy each
+// time the host needs them.
+struct BuildStats {
+    unsigned long long n_unique;  // sum of distinct columns over windows
+    unsigned long long nnz;       // set bits of all bitmaps
+    int32_t err;                  // kBuildBadCsr or kBuildBadValue
+    int32_t bad_rows;             // err before any column was read
+    int32_t nnz_csr;              // row_ptr[N]
+    int32_t n_mid, n_big, n_heavy;  // windows listed by launch_classify
+    int32_t max_blocks;
+    int32_t n_blocks;
+    int32_t piece;
+    int32_t n_pieces;
+    int32_t n_split;
+    int32_t placed;               // see launch_shape
+    int32_t invalid;              // plan integrity check
+    int32_t heavy[kHeavySteps];   // items above heavy_blocks(j) blocks
+};
+constexpr int kBuildBadCsr = 1;    // malformed pattern
+constexpr int kBuildBadValue = 2;  // entries but no col_idx, or more than nnz_cap
+// Zeroes *st, reads nnz into it and checks it (also against the nnz_cap
+// entries the scratch holds; has_cols: col_idx was given); then checks
+// row_ptr and lists the windows with more than 512 CSR entries: mid up to
+// 1024, big up to 4096, heavy above.
+// win_row: the windows' first rows (null: 16-row windows); also below.
+hipError_t launch_classify(const int32_t *row_ptr, int32_t N, const int32_t *win_row, int32_t T,
+                           int64_t nnz_cap, bool has_cols, BuildStats *st, int32_t *mid,
+                           int32_t *big, int32_t *heavy, hipStream_t s);
 // Staging area of the window bitmaps, in 32-bit words, for nnz CSR entries.
 int64_t mask_stage_words(int64_t nnz, int32_t T);
-// Per window of at most 512 entries (one wavefront each): sorted distinct
-// columns into tmp_cols at the window's CSR offset, their count into u, the
-// block bitmaps into the staging area, their set bits into bits.  Larger
-// windows get is_big = 1 (up to 4096 entries) or is_heavy = 1.
-// win_row: the windows' first rows (null: 16-row windows); also below.
-hipError_t launch_window_wave(const int32_t *row_ptr, const int32_t *col_idx, int32_t N,
-                              const int32_t *win_row, int32_t T, int32_t *tmp_cols,
-                              uint32_t *tmp_mask, int32_t *u, int32_t *is_big,
-                              int32_t *is_heavy, int32_t *bits, int32_t *err, hipStream_t s);
-// The windows big[0 .. n_big): sorted distinct columns, u, bitmaps and bits
-// as above (one wavefront with 16 keys per lane up to 1024 entries, else an
-// LDS sort).
-hipError_t launch_window_sort(const int32_t *row_ptr, const int32_t *col_idx,
-                              int32_t N, const int32_t *win_row, const int32_t *big,
-                              int32_t n_big, int32_t *tmp_cols, uint32_t *tmp_mask,
-                              int32_t *u, int32_t *bits, int32_t *err, hipStream_t s);
-// Heavy windows (more than 4096 entries): columns, u, bitmaps and bits as
-// above, one workgroup per window (column bitmap in LDS, walked in chunks).
-hipError_t launch_heavy_lds(const int32_t *row_ptr, const int32_t *col_idx, int32_t N,
-                            const int32_t *win_row, const int32_t *heavy, int32_t n_heavy,
-                            int32_t *tmp_cols, uint32_t *tmp_mask, int32_t *u,
-                            int32_t *bits, int32_t *err, hipStream_t s);
-// nb[w] = ceil(u[w] / 16) and the sums of u, bits and nb and the largest nb
-// (added / max-ed into the four outputs, zeroed by the caller).
-hipError_t launch_window_stats(const int32_t *u, const int32_t *bits, int32_t T,
-                               int32_t *nb, unsigned long long *sum_u,
-                               unsigned long long *sum_bits, int32_t *sum_nb,
-                               int32_t *max_nb, hipStream_t s);
+// Per window: sorted distinct columns into tmp_cols at the window's CSR
+// offset, their count into u, the block bitmaps into the staging area, their
+// set bits into bits.  Nothing if *st already holds an error.
+hipError_t launch_windows(const int32_t *row_ptr, const int32_t *col_idx, int32_t N,
+                          const int32_t *win_row, int32_t T, int64_t nnz_cap, BuildStats *st,
+                          const int32_t *mid, const int32_t *big, const int32_t *heavy,
+                          int32_t *tmp_cols, uint32_t *tmp_mask, int32_t *u, int32_t *bits,
+                          hipStream_t s);
 // Exclusive scan of n int32 into out[0..n], out[n] = total (in == out ok).
 // Element i is in[i], or in[gather[i]] when gather is given.  With list
 // given, every nonzero element i is also listed: list[out[i]] = i (flag
@@ -274,25 +334,31 @@ hipError_t launch_scan(const int32_t *in, int32_t *out, int32_t n, int32_t *tmp,
                        int32_t *total_out, hipStream_t s);
 // Two independent scans of n ints each (one launch when n is small).
 hipError_t launch_scan2(ScanArray a0, ScanArray a1, int32_t n, int32_t *tmp, hipStream_t s);
-// Padded column lists and block bitmaps of the plan from the staging areas.
+// The plan's blk_off, padded column lists and block bitmaps from the scratch;
+// with `items` also the work list, window w's items from pos[w] on (pos null:
+// in window order).
 hipError_t launch_fill_windows(const int32_t *row_ptr, const int32_t *win_row, int32_t T,
                                const int32_t *tmp_cols, const uint32_t *tmp_mask,
-                               const int32_t *u, const int32_t *blk_off, int32_t *cols,
-                               uint32_t *mask, hipStream_t s);
-// Work list: the piece size (from the block count and largest window on the
-// device, see plan_piece; forced >= 2 overrides it; slots = 8 per CU) into
-// *piece_out, then per window piece count, bucket key, split flags.
-// reorder == false gives every window the same key (window order kept).
-hipError_t launch_bin_keys(const int32_t *nb, int32_t T, const int32_t *n_blocks,
-                           const int32_t *max_blocks, int32_t forced, int32_t slots,
-                           bool reorder, int32_t *piece_out, int32_t *npieces,
-                           int32_t *key, int32_t *split_pieces, int32_t *split_one,
-                           int32_t *heavy, hipStream_t s);
-// Pieces of the split windows: items[split_item[s] + k] for piece k of
-// split window s (merges[3s..3s+2] = window, first slot, pieces).
-hipError_t launch_split_items(const int32_t *merges, const int32_t *split_item,
-                              const int32_t *blk_off, int32_t n_split, WorkItem *items,
-                              hipStream_t s);
+                               const int32_t *u, int32_t *plan_off, int32_t *cols,
+                               uint32_t *mask, const WorkListShape &shape,
+                               const int32_t *pos, WorkItem *items, int32_t *merges,
+                               hipStream_t s);
+// Blocks per window and the shape of the work list, from u and bits: nb[w] =
+// ceil(u[w] / 16) and its prefix blk_off[0..T]; the statistics (st->n_unique,
+// nnz, n_blocks, max_blocks); the piece size (see plan_piece; forced >= 2
+// overrides it; slots = 8 per CU) in st->piece; per window the sort key, and
+// over the split windows the prefixes of their pieces (slot_base[0..T]) and
+// of their number (split_idx[0..T]); st->n_pieces and n_split.  order:
+// kOrderAuto keeps window order for nearly uniform windows and sorts others,
+// heavy first.  st->placed != 0: the list's order is decided, pos[w] is
+// window w's first item and st->heavy is set (plans of up to kOnePlace
+// windows, keys below kPlaceKeys); else launch_worklist has to follow.
+// scan_tmp: scan_tmp_ints(T) ints.
+constexpr int kOrderAuto = 0, kOrderSorted = 1, kOrderWindow = 2;
+hipError_t launch_shape(const int32_t *u, const int32_t *bits, int32_t T, int32_t forced,
+                        int32_t slots, int order, BuildStats *st, int32_t *nb,
+                        int32_t *blk_off, int32_t *key, int32_t *slot_base, int32_t *split_idx,
+                        int32_t *pos, int32_t *scan_tmp, hipStream_t s);
 
 // ---- radix sort (radix.hip) -------------------------------------------------
 // Stable sort of n (key, value) int32 pairs, keys in [0, max_key], ascending
@@ -315,21 +381,13 @@ hipError_t launch_radix_pairs(const int32_t *keys, const int32_t *vals, int32_t 
                               hipStream_t s);
 
 // ---- work list (worklist.hip) ----------------------------------------------
-struct WorkListScratch {
-    int32_t *pos;        // [T + 1] first item of each window in sorted order
-    RadixScratch radix;  // for n = T
-};
-// Heavy-first work list from the keys of launch_bin_keys: whole windows as
-// items, split windows as merge records plus split_item (their pieces:
-// launch_split_items); the item count goes to *n_items_out.  window_order:
-// the list keeps window order (what the stable sort gives when every key
-// is equal), so key is not read and no sort is launched.
-hipError_t launch_worklist(const int32_t *key, const int32_t *nb, const int32_t *blk_off,
-                           const int32_t *npieces, const int32_t *slot_base,
-                           const int32_t *split_idx, int32_t T, int32_t piece,
-                           bool window_order, const WorkListScratch &ws, WorkItem *items,
-                           int32_t *merges, int32_t *split_item, int32_t *n_items_out,
-                           hipStream_t s);
+// Heavy-first work list from the keys of launch_shape where it did not place
+// the windows itself: the windows stably sorted by key, largest first; whole
+// windows as items, split windows as merge records and their pieces as
+// items.  heavy: the table of heavy items (zeroed).
+hipError_t launch_worklist(const int32_t *key, const WorkListShape &shape, int32_t T,
+                           const RadixScratch &radix, WorkItem *items, int32_t *merges,
+                           int32_t *heavy, hipStream_t s);
 
 // ---- transposed pattern (transpose.hip) ----------------------------------
 // CSR of A^T (rp[N+1], ci[nnz], each row in increasing column order) from a
@@ -337,12 +395,12 @@ hipError_t launch_worklist(const int32_t *key, const int32_t *nb, const int32_t 
 size_t transpose_scratch_bytes(const f3s_plan_s &p);
 hipError_t launch_transpose_csr(const f3s_plan_s &p, void *scratch, size_t scratch_bytes,
                                 int32_t *rp, int32_t *ci, hipStream_t s);
-// Sets *asym (zeroed by the caller) unless the plan's pattern is symmetric,
+// Sets *asym to 0 if the plan's pattern is symmetric, to 1 otherwise,
 // from the plan alone (binary searches in the windows' column lists; cheap
 // on small patterns); win: scratch of n_blocks ints.
 hipError_t launch_check_symmetric(const f3s_plan_s &p, int32_t *win, int32_t *asym,
                                   hipStream_t s);
-// The same decision given the CSR of A^T (every row of A compared with the
+// The same decision given the CSR of A^T, *asym zeroed by the caller (every row of A compared with the
 // same row of A^T, position by position; cheaper on large patterns once A^T
 // is sorted anyway).  win: n_blocks ints, pre: 16 * n_blocks ints of scratch.
 hipError_t launch_compare_rows(const f3s_plan_s &p, const int32_t *rpt, const int32_t *cit,

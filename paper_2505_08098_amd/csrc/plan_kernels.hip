@@ -1,21 +1,29 @@
 // Plan construction on the GPU: CSR -> Binary Sparse Block layout
 // (Section 3.1) and the heavy-first work list (Section 3.2).
 //
-//  1. row_ptr validation
+//  1. row_ptr validation, windows classified by their entries
 //  2. per row window: sorted distinct columns and the window's 256-bit block
 //     bitmaps, staged at offsets fixed by the CSR (one wavefront per window
 //     with a register bitonic sort; larger windows a workgroup LDS sort;
 //     heavier windows a column bitmap in LDS with popcount ranks, walked in
 //     chunks of 2^17 columns)
-//  3. blocks per window (ceil(u/16)) and their exclusive prefix (tro)
-//  4. padded column lists (sptd) and bitmaps copied to their final blocks
-//  5. work list keys: block count per window (the stable sort, largest
-//     first, is worklist.hip's), windows above `piece` blocks split into
-//     pieces of whole block pairs
+//  3. blocks per window (ceil(u/16)) and their exclusive prefix (tro), work
+//     list keys (block count per window; windows above `piece` blocks are
+//     split into pieces of whole block pairs) and positions: the windows
+//     stably sorted, largest first (worklist.hip for large plans)
+//  4. padded column lists (sptd), bitmaps and work items copied to their
+//     final places
+//
+// A build is launches of a few microseconds each between two waits of the
+// host (the array sizes, the final check), so what bounds a small one is
+// their number: 7 launches and 2 waits where it took 14 and 4.  Plan, forward,
+// transposed plan and backward of a batch of 4,096 molecules (d = 64): 298 ->
+// 225 us; of 256 (4 heads of 32): 250 -> 180 us.
 //
 // Every kernel is deterministic: integer atomics only commute (bitwise OR,
-// counters whose final value is all that is read), and every position in
-// the output is owned by exactly one thread.
+// counters whose final value is all that is read, the order of lists whose
+// entries' results have their own places), and every position in the output
+// is owned by exactly one thread.
 #include <limits.h>
 
 #include "f3s_internal.h"
@@ -129,9 +137,10 @@ __device__ __forceinline__ void wave_bitonic(int (&x)[E], int lane)
 }
 
 // Entries a window may have for the one-wave path over all windows (8 keys
-// per lane); windows up to kWaveCap16 entries get a second one-wave pass with
-// 16 keys per lane, launched over the larger windows only (its registers
-// would cut the occupancy of the first pass threefold).
+// per lane, 31 registers; with 16 keys per lane they are 103 and the
+// occupancy falls: 47 -> 70 us over the 262,147-node graph).  Windows up to
+// kWaveCap16 entries go, listed, to waves with 16 keys per lane in the launch
+// over the larger windows.
 constexpr int kWaveCap = 512;
 constexpr int kWaveCap16 = 1024;
 
@@ -236,79 +245,8 @@ __device__ __forceinline__ int32_t window_row_starts(const int32_t *row_ptr, int
     return rp;
 }
 
-// One wavefront (one workgroup) per window.  Windows with more than kWaveCap
-// entries are flagged in is_big (up to kSortCap entries) or is_heavy for the
-// later passes.  (No counter shared by all windows: atomics on one address
-// serialise, tens of ns each.)
-__global__ __launch_bounds__(64) void k_window_wave(
-    const int32_t *row_ptr, const int32_t *col_idx, int32_t N, const int32_t *win_row,
-    int32_t *tmp_cols, uint32_t *tmp_mask, int32_t *u, int32_t *is_big, int32_t *is_heavy,
-    int32_t *bits_out, int32_t *err)
-{
-    __shared__ int32_t s_cols[kWaveCap];
-    __shared__ uint32_t s_mask[kWaveCap / kBlockCols * kMaskWords];
-    const int lane = threadIdx.x;
-    const int w = blockIdx.x;
-    // k_check_row_ptr ran before on the same stream: a malformed row_ptr
-    // stops every wave here, before any column is read (is_big stays valid
-    // for the scan that follows)
-    if (*(volatile int32_t *)err) {
-        if (lane == 0) is_big[w] = is_heavy[w] = 0;
-        return;
-    }
-    int32_t beg, n;
-    const int32_t rp = window_row_starts(row_ptr, N, win_row, w, lane, &beg, &n);
-    if (lane == 0) {
-        is_big[w] = n > kWaveCap && n <= kSortCap;
-        is_heavy[w] = n > kSortCap;
-    }
-    if (n > kWaveCap) return;
-    if (n <= 64)
-        window_wave<1>(col_idx, N, w, beg, n, rp, lane, s_cols, s_mask, tmp_cols,
-                       tmp_mask, u, bits_out, err);
-    else if (n <= 128)
-        window_wave<2>(col_idx, N, w, beg, n, rp, lane, s_cols, s_mask, tmp_cols,
-                       tmp_mask, u, bits_out, err);
-    else if (n <= 256)
-        window_wave<4>(col_idx, N, w, beg, n, rp, lane, s_cols, s_mask, tmp_cols,
-                       tmp_mask, u, bits_out, err);
-    else
-        window_wave<8>(col_idx, N, w, beg, n, rp, lane, s_cols, s_mask, tmp_cols,
-                       tmp_mask, u, bits_out, err);
-}
-
-// The windows of `big` with kWaveCap < n <= kWaveCap16 entries, one wavefront
-// each with 16 keys per lane; the others are left to k_window_sort.
-__global__ __launch_bounds__(64) void k_window_wave16(
-    const int32_t *row_ptr, const int32_t *col_idx, int32_t N, const int32_t *win_row,
-    const int32_t *big, int32_t *tmp_cols, uint32_t *tmp_mask, int32_t *u,
-    int32_t *bits_out, int32_t *err)
-{
-    __shared__ int32_t s_cols[kWaveCap16];
-    __shared__ uint32_t s_mask[kWaveCap16 / kBlockCols * kMaskWords];
-    const int lane = threadIdx.x;
-    const int w = big[blockIdx.x];
-    int32_t beg, n;
-    const int32_t rp = window_row_starts(row_ptr, N, win_row, w, lane, &beg, &n);
-    if (n <= kWaveCap || n > kWaveCap16) return;
-    window_wave<16>(col_idx, N, w, beg, n, rp, lane, s_cols, s_mask, tmp_cols, tmp_mask,
-                    u, bits_out, err);
-}
-
-__global__ void k_check_row_ptr(const int32_t *row_ptr, int32_t N, int32_t nnz,
-                                int32_t *err)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i > N) return;
-    const int32_t a = row_ptr[i];
-    bool bad = a < 0 || a > nnz;
-    if (i == 0) bad |= a != 0;
-    if (i < N) bad |= row_ptr[i + 1] < a;
-    if (bad) atomicOr(err, 1);
-}
-
-// Windows of the list `big` with more than kWaveCap16 entries (at most
-// kSortCap), one workgroup each: bitonic sort of kSortCap keys (the window's
+// A window of the list `big` (more than kWaveCap entries, at most
+// kSortCap), by one workgroup: bitonic sort of kSortCap keys (the window's
 // columns padded with INT_MAX), 4 per thread in registers -- key t = 4 tid +
 // i -- so compare distances 1 and 2 stay in a thread, 4 .. 128 pair lanes of
 // a wavefront (xchg_lanes) and only the 10 steps of distance 256 and more go
@@ -337,24 +275,20 @@ __device__ int block_excl_scan_sort(int v, int *lds, int *total)
     return before + x;
 }
 
-__global__ __launch_bounds__(kSortThreads) void k_window_sort(
-    const int32_t *row_ptr, const int32_t *col_idx, int32_t N, const int32_t *win_row,
-    const int32_t *big, int32_t *tmp_cols, uint32_t *tmp_mask, int32_t *u,
-    int32_t *bits_out, int32_t *err)
+__device__ void window_sort(const int32_t *row_ptr, const int32_t *col_idx, int32_t N,
+                            const int32_t *win_row, int32_t w, uint32_t *lds, int *scan,
+                            int32_t *edge, int32_t *s_rp, int32_t *tmp_cols,
+                            uint32_t *tmp_mask, int32_t *u, int32_t *bits_out, int32_t *err)
 {
     static_assert(kSortPer == 4, "the register network assumes 4 keys per thread");
-    __shared__ int32_t xbuf[2][kSortCap];  // cross-wave exchanges, then the distinct list
-    __shared__ int scan[kSortThreads / 64];
-    __shared__ int32_t edge[kSortThreads / 64];
-    __shared__ uint32_t s_mask[kSortCap / kBlockCols * kMaskWords];
-    __shared__ int32_t s_rp[kWindowRows + 1];
+    // cross-wave exchanges, then the distinct list; the block bitmaps
+    int32_t (*xbuf)[kSortCap] = reinterpret_cast<int32_t (*)[kSortCap]>(lds);
+    uint32_t *s_mask = lds + 2 * kSortCap;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int w = big[blockIdx.x];
     int32_t r0, nr;
     window_rows(win_row, N, w, &r0, &nr);
     const int beg = row_ptr[r0];
     const int n = row_ptr[r0 + nr] - beg;
-    if (n <= kWaveCap16 || n > kSortCap) return;  // k_window_wave16 / heavy paths
     if (tid <= nr) s_rp[tid] = row_ptr[r0 + tid];
     int x[kSortPer];
 #pragma unroll
@@ -469,7 +403,7 @@ __global__ __launch_bounds__(kSortThreads) void k_window_sort(
     }
 }
 
-// Heavy windows (more than kSortCap entries), one workgroup each.  The column
+// A heavy window (more than kSortCap entries), by one workgroup.  The column
 // range is walked in chunks of kChunkCols: a chunk's columns are marked in a
 // bitmap in LDS and a prefix popcount over its words ranks them, so every
 // entry's compacted column is (distinct columns of earlier chunks) + rank +
@@ -484,20 +418,18 @@ constexpr int kChunkCols = 1 << 17;       // 16 KB bitmap + 16 KB ranks
 // LDS of one workgroup: two of them (2 x 1024 threads) still fit a CU.
 constexpr int kHeavyLdsBytes = 76 * 1024;
 
-__global__ __launch_bounds__(kHeavyThreads) void k_heavy_lds(
-    const int32_t *row_ptr, const int32_t *col_idx, int32_t N, const int32_t *win_row,
-    const int32_t *heavy, int32_t *tmp_cols, uint32_t *tmp_mask, int32_t *u,
-    int32_t *bits_out, int32_t *err, int32_t mask_words)
+__device__ void window_heavy(const int32_t *row_ptr, const int32_t *col_idx, int32_t N,
+                             const int32_t *win_row, int32_t w, uint32_t *lds, int *scan,
+                             int32_t *s_rp, int32_t *tmp_cols, uint32_t *tmp_mask, int32_t *u,
+                             int32_t *bits_out, int32_t *err)
 {
-    uint32_t *lds = f3s_heavy_lds_dyn;  // [cw] bitmap, [cw] ranks, [mask_words]
-    __shared__ int32_t s_rp[kWindowRows + 1];
-    __shared__ int scan[kHeavyThreads / 64];
+    // lds: [cw] bitmap, [cw] ranks, [mask_words]
     const int tid = threadIdx.x;
     const int cw = (min(N, kChunkCols) + 31) / 32;  // bitmap words of one chunk
     uint32_t *bm = lds;
     int32_t *rank = (int32_t *)(lds + cw);
     uint32_t *sm = lds + 2 * cw;
-    const int w = heavy[blockIdx.x];
+    const int mask_words = (kHeavyLdsBytes / 4 - 2 * cw) & ~(kMaskWords - 1);
     int32_t r0, nr;
     window_rows(win_row, N, w, &r0, &nr);
     if (tid <= nr) s_rp[tid] = row_ptr[r0 + tid];
@@ -628,6 +560,153 @@ __global__ __launch_bounds__(kHeavyThreads) void k_heavy_lds(
 }
 
 
+// ---- the windows -------------------------------------------------------------
+constexpr int kWindowThreads = 1024;
+constexpr int kWindowWaves = kWindowThreads / 64;
+static_assert(kWindowThreads == kSortThreads && kWindowThreads == kHeavyThreads, "");
+static_assert(4 * (2 * kSortCap + kSortCap / kBlockCols * kMaskWords) <= kHeavyLdsBytes, "");
+// Mid windows (kWaveCap < n <= kWaveCap16): the waves of a workgroup whose
+// lists fit its LDS take one each.
+constexpr int kMidLdsInts = kWaveCap16 + kWaveCap16 / kBlockCols * kMaskWords;
+constexpr int kMidWaves = kHeavyLdsBytes / 4 / kMidLdsInts;
+static_assert(kMidWaves >= 1 && kMidWaves <= kWindowWaves, "");
+
+// One wavefront (one workgroup) per window of at most kWaveCap entries.
+// (k_classify ran before on the same stream: a malformed row_ptr, or one the
+// scratch is too small for, stops every wave here, before any column is read.)
+__global__ __launch_bounds__(64) void k_windows_small(
+    const int32_t *row_ptr, const int32_t *col_idx, int32_t N, const int32_t *win_row,
+    BuildStats *st, int32_t *tmp_cols, uint32_t *tmp_mask, int32_t *u, int32_t *bits_out)
+{
+    __shared__ int32_t s_cols[kWaveCap];
+    __shared__ uint32_t s_mask[kWaveCap / kBlockCols * kMaskWords];
+    const int lane = threadIdx.x;
+    const int w = blockIdx.x;
+    if (st->bad_rows) return;
+    int32_t beg, n;
+    const int32_t rp = window_row_starts(row_ptr, N, win_row, w, lane, &beg, &n);
+    if (n > kWaveCap) return;
+    if (n <= 64)
+        window_wave<1>(col_idx, N, w, beg, n, rp, lane, s_cols, s_mask, tmp_cols,
+                       tmp_mask, u, bits_out, &st->err);
+    else if (n <= 128)
+        window_wave<2>(col_idx, N, w, beg, n, rp, lane, s_cols, s_mask, tmp_cols,
+                       tmp_mask, u, bits_out, &st->err);
+    else if (n <= 256)
+        window_wave<4>(col_idx, N, w, beg, n, rp, lane, s_cols, s_mask, tmp_cols,
+                       tmp_mask, u, bits_out, &st->err);
+    else
+        window_wave<8>(col_idx, N, w, beg, n, rp, lane, s_cols, s_mask, tmp_cols,
+                       tmp_mask, u, bits_out, &st->err);
+}
+
+// The larger windows in one launch: few, but about 30 us long each (the
+// latency of one workgroup's steps), so the three kinds run side by side.
+// The workgroups take the heavy windows, the big ones and the mid ones
+// (kMidWaves at a time) in turn.  The grid does not depend on their numbers,
+// which only the device knows; with 64 registers and 76 KB of LDS two
+// workgroups fit a compute unit.  (262,147-node graph: 30 + 32 + 29 us in
+// three launches after a wait for their numbers, 53 us in one.  The small
+// windows in the same launch lost 85 us on the million-node graph: a
+// workgroup of 16 of them lasts as long as its slowest.)
+__global__ __launch_bounds__(kWindowThreads, 8) void k_windows_large(
+    const int32_t *row_ptr, const int32_t *col_idx, int32_t N, const int32_t *win_row,
+    BuildStats *st, const int32_t *mid, const int32_t *big, const int32_t *heavy,
+    int32_t *tmp_cols, uint32_t *tmp_mask, int32_t *u, int32_t *bits_out)
+{
+    __shared__ int scan[kWindowWaves];
+    __shared__ int32_t edge[kWindowWaves];
+    __shared__ int32_t s_rp[kWindowRows + 1];
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (st->bad_rows) return;
+    const int nh = st->n_heavy, nb = st->n_big, nm = st->n_mid;
+    const int units = nh + nb + (nm + kMidWaves - 1) / kMidWaves;
+    for (int k = blockIdx.x; k < units; k += gridDim.x) {
+        if (k < nh) {
+            window_heavy(row_ptr, col_idx, N, win_row, heavy[k], f3s_heavy_lds_dyn, scan,
+                         s_rp, tmp_cols, tmp_mask, u, bits_out, &st->err);
+        } else if (k < nh + nb) {
+            window_sort(row_ptr, col_idx, N, win_row, big[k - nh], f3s_heavy_lds_dyn, scan,
+                        edge, s_rp, tmp_cols, tmp_mask, u, bits_out, &st->err);
+        } else {
+            const int m = (k - nh - nb) * kMidWaves + wv;
+            if (wv < kMidWaves && m < nm) {
+                const int w = mid[m];
+                int32_t beg, n;
+                const int32_t rp = window_row_starts(row_ptr, N, win_row, w, lane, &beg, &n);
+                int32_t *s_cols = (int32_t *)f3s_heavy_lds_dyn + wv * kMidLdsInts;
+                window_wave<16>(col_idx, N, w, beg, n, rp, lane, s_cols,
+                                (uint32_t *)s_cols + kWaveCap16, tmp_cols, tmp_mask, u,
+                                bits_out, &st->err);
+            }
+        }
+        __syncthreads();  // the next unit reuses the LDS
+    }
+}
+
+// Zeroes *st and checks the number of entries (see launch_classify).
+__global__ void k_build_init(const int32_t *row_ptr, int32_t N, int64_t nnz_cap, bool has_cols,
+                             BuildStats *st)
+{
+    for (int k = threadIdx.x; k < (int)(sizeof(BuildStats) / 4); k += blockDim.x)
+        reinterpret_cast<int32_t *>(st)[k] = 0;
+    __syncthreads();
+    if (threadIdx.x) return;
+    const int32_t nnz = row_ptr[N];
+    st->nnz_csr = nnz;
+    const int e = nnz < 0                                    ? kBuildBadCsr
+                  : nnz > nnz_cap || (nnz > 0 && !has_cols) ? kBuildBadValue
+                                                             : 0;
+    st->err = st->bad_rows = e;
+}
+
+// One thread per row: row_ptr[0] == 0, non-decreasing, within [0, nnz] (so
+// that every window's entries lie inside col_idx).  One thread per window
+// (the first T threads): the lists of large windows, a workgroup's windows
+// appended together (single appends to one counter serialise, tens of ns
+// each; the lists' order does not matter, every window's outputs have their
+// own place).  A window whose rows are malformed may be listed; nothing is
+// read of it, as the error is set before the next launch.
+__global__ __launch_bounds__(256) void k_classify(const int32_t *row_ptr, int32_t N,
+                                                  const int32_t *win_row, int32_t T,
+                                                  BuildStats *st, int32_t *mid, int32_t *big,
+                                                  int32_t *heavy)
+{
+    __shared__ int32_t cnt[3], base[3];
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (threadIdx.x < 3) cnt[threadIdx.x] = 0;
+    const int32_t nnz = st->nnz_csr;
+    if (i <= N) {
+        const int32_t a = row_ptr[i];
+        bool bad = a < 0 || a > nnz;
+        if (i == 0) bad |= a != 0;
+        if (i < N) bad |= row_ptr[i + 1] < a;
+        if (bad && !st->bad_rows) {
+            atomicMax(&st->bad_rows, kBuildBadCsr);
+            atomicMax(&st->err, kBuildBadCsr);
+        }
+    }
+    __syncthreads();
+    if ((int64_t)blockIdx.x * blockDim.x >= T) return;  // the whole workgroup
+    int cls = -1, at = 0;
+    if (i < T) {
+        int32_t r0, nr;
+        window_rows(win_row, N, (int32_t)i, &r0, &nr);
+        const int64_t n = (int64_t)row_ptr[r0 + nr] - row_ptr[r0];
+        cls = n > kSortCap ? 2 : n > kWaveCap16 ? 1 : n > kWaveCap ? 0 : -1;
+        if (cls >= 0) at = atomicAdd(&cnt[cls], 1);
+    }
+    __syncthreads();
+    if (threadIdx.x < 3 && cnt[threadIdx.x]) {
+        int32_t *total = threadIdx.x == 0 ? &st->n_mid : threadIdx.x == 1 ? &st->n_big
+                                                                          : &st->n_heavy;
+        base[threadIdx.x] = atomicAdd(total, cnt[threadIdx.x]);
+    }
+    __syncthreads();
+    if (cls >= 0) (cls == 0 ? mid : cls == 1 ? big : heavy)[base[cls] + at] = (int32_t)i;
+}
+
 // Per window: blocks nb = ceil(u/16); over all windows: sum of u (distinct
 // columns), sum of bits (distinct entries), sum of nb (blocks) and the
 // largest nb.  Grid-stride, then a workgroup reduction and one atomic per
@@ -638,7 +717,7 @@ constexpr int kStatBlocks = 64;
 __global__ __launch_bounds__(kStatThreads) void k_window_stats(
     const int32_t *u, const int32_t *bits, int32_t T, int32_t *nb,
     unsigned long long *sum_u, unsigned long long *sum_bits, int32_t *sum_nb,
-    int32_t *max_nb)
+    int32_t *max_nb, const int32_t *err)
 {
     __shared__ unsigned long long part[3][kStatThreads / 64];
     __shared__ int32_t pmax[kStatThreads / 64];
@@ -646,11 +725,11 @@ __global__ __launch_bounds__(kStatThreads) void k_window_stats(
     int32_t mx = 0;
     for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < T;
          w += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t uw = u[w];
+        const int32_t uw = *err ? 0 : u[w];  // after an error u may not be set
         const int32_t b = (uw + kBlockCols - 1) / kBlockCols;
         nb[w] = b;
         su += (unsigned long long)uw;
-        sb += (unsigned long long)bits[w];
+        sb += (unsigned long long)(*err ? 0 : bits[w]);
         sn += (unsigned long long)b;
         mx = max(mx, b);
     }
@@ -775,25 +854,33 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(ScanArray a0, ScanArray a
 }
 
 
-// Padded column lists (sptd, -1 past the window's distinct columns) and the
-// block bitmaps copied from the staging areas to the window's blocks; one
-// workgroup per window (a hub window has thousands of blocks).
+// The window's block offset, padded column list (sptd, -1 past the distinct
+// columns) and block bitmaps copied from the scratch to the plan; one
+// workgroup per window (a hub window has thousands of blocks).  With `items`
+// also the window's items, from pos[w] on (pos null: in window order).
 __global__ __launch_bounds__(256) void k_fill_windows(
-    const int32_t *row_ptr, const int32_t *win_row, const int32_t *tmp_cols,
-    const uint32_t *tmp_mask, const int32_t *u, const int32_t *blk_off, int32_t *cols,
-    uint32_t *mask)
+    const int32_t *row_ptr, const int32_t *win_row, int32_t T, const int32_t *tmp_cols,
+    const uint32_t *tmp_mask, const int32_t *u, int32_t *plan_off, int32_t *cols,
+    uint32_t *mask, WorkListShape shape, const int32_t *pos, WorkItem *items, int32_t *merges)
 {
     const int w = blockIdx.x;
     const int32_t beg = row_ptr[win_row ? win_row[w] : w * kWindowRows];
     const int uw = u[w];
-    const int64_t ob = blk_off[w];
-    const int nbw = blk_off[w + 1] - blk_off[w];
+    const int64_t ob = shape.blk_off[w];
+    const int nbw = shape.blk_off[w + 1] - shape.blk_off[w];
     const int32_t *src = tmp_cols + beg;
     const uint32_t *msrc = tmp_mask + mask_stage(beg, w);
     int32_t *dst = cols + kBlockCols * ob;
     uint32_t *mdst = mask + kMaskWords * ob;
     for (int k = threadIdx.x; k < kBlockCols * nbw; k += 256) dst[k] = k < uw ? src[k] : -1;
     for (int k = threadIdx.x; k < kMaskWords * nbw; k += 256) mdst[k] = msrc[k];
+    if (threadIdx.x == 0) {
+        plan_off[w] = (int32_t)ob;
+        if (w == T - 1) plan_off[T] = (int32_t)ob + nbw;
+    }
+    if (items)
+        place_window(shape, w, pos ? pos[w] : w + shape.slot_base[w] - shape.split_idx[w],
+                     threadIdx.x, 256, items, merges);
 }
 
 // Work-list piece size (even).  Pieces cost a partial result of 16 rows
@@ -830,54 +917,230 @@ __device__ int32_t plan_piece(int64_t n_blocks, int32_t max_blocks, int32_t T, i
     return (int32_t)(piece < cap ? piece : cap);
 }
 
-// Keys, pieces and split flags per window, and the table of heavy items
-// (heavy[j]: items of windows whose key exceeds heavy_blocks(j), zeroed by
-// the caller).
+// Keys, pieces and split flags per window.
 __global__ __launch_bounds__(256) void k_bin_keys(
     const int32_t *nb, int32_t T, const int32_t *n_blocks, const int32_t *max_blocks,
-    int32_t forced, int32_t slots, bool reorder, int32_t *piece_out, int32_t *npieces,
-    int32_t *key, int32_t *split_pieces, int32_t *split_one, int32_t *heavy)
+    int32_t forced, int32_t slots, int32_t *piece_out, int32_t *key, int32_t *split_pieces,
+    int32_t *split_one)
 {
-    __shared__ int32_t cnt[kHeavySteps];
     const int w = blockIdx.x * blockDim.x + threadIdx.x;
-    if (threadIdx.x < kHeavySteps) cnt[threadIdx.x] = 0;
-    __syncthreads();
     const int32_t piece = plan_piece(*n_blocks, *max_blocks, T, forced, slots);
     if (w == 0) *piece_out = piece;
-    if (w < T) {
-        const int n = nb[w];
-        const bool split = n > piece;
-        const int np = split ? (n + piece - 1) / piece : 1;
-        const int k = split ? piece : n;
-        npieces[w] = np;
-        key[w] = reorder ? k : 0;
-        split_pieces[w] = split ? np : 0;
-        split_one[w] = split ? 1 : 0;
-        for (int j = 0; j < kHeavySteps && k > heavy_blocks(j); ++j) atomicAdd(&cnt[j], np);
-    }
-    __syncthreads();
-    if (threadIdx.x < kHeavySteps && cnt[threadIdx.x])
-        atomicAdd(&heavy[threadIdx.x], cnt[threadIdx.x]);
+    if (w >= T) return;
+    const int n = nb[w];
+    const bool split = n > piece;
+    key[w] = split ? piece : n;
+    split_pieces[w] = split ? (n + piece - 1) / piece : 0;
+    split_one[w] = split ? 1 : 0;
 }
 
-// Work items of the pieces of split window s (one wavefront per split
-// window): piece k of np covers the block pairs [floor(k*pairs/np),
-// floor((k+1)*pairs/np)) of the window, pairs = ceil(nb/2).
-__global__ __launch_bounds__(256) void k_split_items(const int32_t *merges,
-                                                     const int32_t *split_item,
-                                                     const int32_t *blk_off,
-                                                     int32_t n_split, WorkItem *items)
+// All of launch_shape by one workgroup, for up to kOnePlace windows: wave v
+// owns the windows [v 64 E, (v + 1) 64 E), 64 at a time (coalesced), so each
+// prefix costs one barrier over the wave totals and the block counts stay in
+// registers.  Then the stable sort: each wave ranks its windows in order, a
+// window's rank among the equal keys of its 64 from ballots, added to the
+// wave's running count of that key (16 waves x kPlaceKeys counts in LDS), and
+// a scan over (key descending, wave) gives each wave its first rank of each
+// key.  Bound by the latency of its steps; it replaces eight launches
+// (statistics, keys, two scans, digit count, scan, scatter, placement).
+constexpr int kOnePlace = 32768;
+constexpr int kPlaceKeys = 2048;
+constexpr int kPlaceThreads = 1024;
+constexpr int kPlaceWaves = kPlaceThreads / 64;
+
+template <int E>
+__global__ __launch_bounds__(kPlaceThreads) void k_shape(
+    const int32_t *u, const int32_t *bits, int32_t T, int32_t forced, int32_t slots, int order,
+    BuildStats *st, int32_t *blk_off, int32_t *key, int32_t *slot_base, int32_t *split_idx,
+    int32_t *pos)
 {
-    const int s = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (s >= n_split) return;
-    const int w = merges[3 * s], slot = merges[3 * s + 1], np = merges[3 * s + 2];
-    const int pos = split_item[s];
-    const int b0 = blk_off[w], n = blk_off[w + 1] - b0;
-    const int64_t pairs = (n + 1) / 2;
-    for (int k = threadIdx.x & 63; k < np; k += 64) {
-        const int a = (int)((k * pairs) / np);
-        const int b = (int)(((k + 1) * pairs) / np);
-        items[pos + k] = WorkItem{w, b0 + 2 * a, b0 + min(n, 2 * b), slot + k};
+    __shared__ int32_t cnt[kPlaceWaves][kPlaceKeys];  // [wave][piece - key]
+    __shared__ unsigned long long ssum[2][kPlaceWaves];
+    __shared__ int32_t snb[kPlaceWaves], smax[kPlaceWaves], spc[kPlaceWaves], sone[kPlaceWaves];
+    __shared__ int32_t hist[kHeavySteps + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    if (st->err) return;  // u and bits may not be set
+    const int w0 = wv * 64 * E + lane;
+    int nb[E];
+    unsigned long long su = 0, sb = 0;
+    int sn = 0, mx = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int w = w0 + 64 * e;
+        nb[e] = w < T ? u[w] : 0;
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int w = w0 + 64 * e;
+        sb += (unsigned long long)(w < T ? bits[w] : 0);
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        su += (unsigned long long)nb[e];
+        nb[e] = (nb[e] + kBlockCols - 1) / kBlockCols;
+        sn += nb[e];
+        mx = max(mx, nb[e]);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        su += __shfl_xor(su, o);
+        sb += __shfl_xor(sb, o);
+        sn += __shfl_xor(sn, o);
+        mx = max(mx, __shfl_xor(mx, o));
+    }
+    if (lane == 0) {
+        ssum[0][wv] = su;
+        ssum[1][wv] = sb;
+        snb[wv] = sn;
+        smax[wv] = mx;
+    }
+    if (tid <= kHeavySteps) hist[tid] = 0;
+    __syncthreads();
+    int run_nb = 0, total = 0, max_nb = 0;
+#pragma unroll
+    for (int k = 0; k < kPlaceWaves; ++k) {
+        if (k < wv) run_nb += snb[k];
+        total += snb[k];
+        max_nb = max(max_nb, smax[k]);
+    }
+    const int32_t piece = plan_piece(total, max_nb, T, forced, slots);
+    // this wave's pieces of split windows
+    int run_pc = 0, run_one = 0, all_pc = 0, all_one = 0;
+    if (max_nb > piece) {  // uniform
+        int pc = 0, one = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (nb[e] > piece) {
+                pc += (nb[e] + piece - 1) / piece;
+                ++one;
+            }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            pc += __shfl_xor(pc, o);
+            one += __shfl_xor(one, o);
+        }
+        if (lane == 0) {
+            spc[wv] = pc;
+            sone[wv] = one;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kPlaceWaves; ++k) {
+            if (k < wv) {
+                run_pc += spc[k];
+                run_one += sone[k];
+            }
+            all_pc += spc[k];
+            all_one += sone[k];
+        }
+    }
+    const bool window_order =
+        order == kOrderWindow ||
+        (order == kOrderAuto && uniform_windows(T, total, max_nb));
+    const bool sorted = !window_order && piece < kPlaceKeys;
+    const int nk = piece + 1;
+    if (sorted)
+        for (int k = lane; k < nk; k += 64) cnt[wv][k] = 0;
+    const uint64_t below = (1ull << lane) - 1ull;
+    const int nbits = 32 - __clz(piece | 1);
+    int rank[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int w = w0 + 64 * e;
+        const int n = nb[e];
+        const bool split = n > piece, valid = w < T;
+        const int np = split ? (n + piece - 1) / piece : 0;
+        const int incl = wave_inclusive_sum(n, lane);
+        int ipc = 0, ione = 0;
+        if (all_one) {  // uniform
+            ipc = wave_inclusive_sum(np, lane);
+            ione = wave_inclusive_sum(split ? 1 : 0, lane);
+        }
+        // items of the split windows before w, less one for each
+        const int before = run_pc + ipc - np - (run_one + ione - (split ? 1 : 0));
+        if (valid) {
+            blk_off[w] = run_nb + incl - n;
+            slot_base[w] = run_pc + ipc - np;
+            split_idx[w] = run_one + ione - (split ? 1 : 0);
+            if (!sorted) {
+                key[w] = split ? piece : n;
+                pos[w] = w + before;
+            }
+        }
+        run_nb += __builtin_amdgcn_readlane(incl, 63);
+        run_pc += __builtin_amdgcn_readlane(ipc, 63);
+        run_one += __builtin_amdgcn_readlane(ione, 63);
+        rank[e] = 0;
+        if (sorted) {
+            const int d = max(piece - n, 0);
+            uint64_t peers = __ballot(valid);
+            for (int b = 0; b < nbits; ++b) {
+                const uint64_t bal = __ballot(valid && ((d >> b) & 1));
+                peers &= ((d >> b) & 1) ? bal : ~bal;
+            }
+            const int r = __popcll(peers & below);
+            // (a wave's LDS accesses take effect in program order: every lane
+            // reads the count before the key's first lane updates it)
+            const int prior = valid ? cnt[wv][d] : 0;
+            if (valid && r == 0) cnt[wv][d] = prior + __popcll(peers);
+            rank[e] = prior + r + (d == 0 ? before : all_pc - all_one);
+        }
+    }
+    __syncthreads();
+    if (sorted) {
+        // first rank of each key and wave: a scan over the keys, two per
+        // thread, of the waves' totals
+        int tot[2] = {0, 0};
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int k = 2 * tid + j;
+            if (k < nk)
+                for (int v = 0; v < kPlaceWaves; ++v) tot[j] += cnt[v][k];
+            const int level = k < nk ? heavy_level(piece - k) : 0;
+            if (level && tot[j]) atomicAdd(&hist[level], tot[j] + (k ? 0 : all_pc - all_one));
+        }
+        const int incl = wave_inclusive_sum(tot[0] + tot[1], lane);
+        if (lane == 63) snb[wv] = incl;
+        __syncthreads();
+        int first = incl - tot[0] - tot[1];
+        for (int v = 0; v < wv; ++v) first += snb[v];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            if (2 * tid + j < nk)
+                for (int v = 0; v < kPlaceWaves; ++v) {
+                    const int c = cnt[v][2 * tid + j];
+                    cnt[v][2 * tid + j] = first;
+                    first += c;
+                }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int w = w0 + 64 * e;
+            if (w < T) pos[w] = cnt[wv][max(piece - nb[e], 0)] + rank[e];
+        }
+        if (tid < kHeavySteps) {
+            int h = 0;
+            for (int l = tid + 1; l <= kHeavySteps; ++l) h += hist[l];
+            st->heavy[tid] = h;
+        }
+    }
+    if (tid == 0) {
+        unsigned long long a = 0, b = 0;
+        for (int k = 0; k < kPlaceWaves; ++k) {
+            a += ssum[0][k];
+            b += ssum[1][k];
+        }
+        st->n_unique = a;
+        st->nnz = b;
+        st->n_blocks = total;
+        st->max_blocks = max_nb;
+        st->piece = piece;
+        st->n_pieces = all_pc;
+        st->n_split = all_one;
+        st->placed = window_order || sorted;
+        blk_off[T] = total;
+        slot_base[T] = all_pc;
+        split_idx[T] = all_one;
     }
 }
 
@@ -921,63 +1184,36 @@ inline unsigned grid_for(int64_t n, int threads)
 
 }  // namespace
 
-hipError_t launch_check_row_ptr(const int32_t *row_ptr, int32_t N, int32_t nnz,
-                                int32_t *err, hipStream_t s)
+hipError_t launch_classify(const int32_t *row_ptr, int32_t N, const int32_t *win_row, int32_t T,
+                           int64_t nnz_cap, bool has_cols, BuildStats *st, int32_t *mid,
+                           int32_t *big, int32_t *heavy, hipStream_t s)
 {
-    k_check_row_ptr<<<grid_for((int64_t)N + 1, 256), 256, 0, s>>>(row_ptr, N, nnz, err);
+    k_build_init<<<1, 64, 0, s>>>(row_ptr, N, nnz_cap, has_cols, st);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    k_classify<<<grid_for((int64_t)N + 1, 256), 256, 0, s>>>(row_ptr, N, win_row, T, st, mid,
+                                                             big, heavy);
     return hipGetLastError();
 }
 
 int64_t mask_stage_words(int64_t nnz, int32_t T) { return (nnz >> 1) + 8ll * T + 8; }
 
-hipError_t launch_window_wave(const int32_t *row_ptr, const int32_t *col_idx, int32_t N,
-                              const int32_t *win_row, int32_t T, int32_t *tmp_cols,
-                              uint32_t *tmp_mask, int32_t *u, int32_t *is_big,
-                              int32_t *is_heavy, int32_t *bits, int32_t *err, hipStream_t s)
+hipError_t launch_windows(const int32_t *row_ptr, const int32_t *col_idx, int32_t N,
+                          const int32_t *win_row, int32_t T, int64_t nnz_cap, BuildStats *st,
+                          const int32_t *mid, const int32_t *big, const int32_t *heavy,
+                          int32_t *tmp_cols, uint32_t *tmp_mask, int32_t *u, int32_t *bits,
+                          hipStream_t s)
 {
     if (T == 0) return hipSuccess;
-    k_window_wave<<<T, 64, 0, s>>>(row_ptr, col_idx, N, win_row, tmp_cols, tmp_mask, u,
-                                   is_big, is_heavy, bits, err);
-    return hipGetLastError();
-}
-
-hipError_t launch_window_sort(const int32_t *row_ptr, const int32_t *col_idx,
-                              int32_t N, const int32_t *win_row, const int32_t *big,
-                              int32_t n_big, int32_t *tmp_cols, uint32_t *tmp_mask,
-                              int32_t *u, int32_t *bits, int32_t *err, hipStream_t s)
-{
-    if (n_big == 0) return hipSuccess;
-    k_window_wave16<<<n_big, 64, 0, s>>>(row_ptr, col_idx, N, win_row, big, tmp_cols,
-                                         tmp_mask, u, bits, err);
-    k_window_sort<<<n_big, kSortThreads, 0, s>>>(row_ptr, col_idx, N, win_row, big,
-                                                 tmp_cols, tmp_mask, u, bits, err);
-    return hipGetLastError();
-}
-
-hipError_t launch_heavy_lds(const int32_t *row_ptr, const int32_t *col_idx, int32_t N,
-                            const int32_t *win_row, const int32_t *heavy, int32_t n_heavy,
-                            int32_t *tmp_cols, uint32_t *tmp_mask, int32_t *u,
-                            int32_t *bits, int32_t *err, hipStream_t s)
-{
-    if (n_heavy == 0) return hipSuccess;
-    const int cw = (min(N, kChunkCols) + 31) / 32;
-    const int mask_words = (kHeavyLdsBytes / 4 - 2 * cw) & ~(kMaskWords - 1);
-    const size_t lds = (size_t)(2 * cw + mask_words) * 4;
-    k_heavy_lds<<<n_heavy, kHeavyThreads, lds, s>>>(row_ptr, col_idx, N, win_row, heavy,
-                                                     tmp_cols, tmp_mask, u, bits, err,
-                                                     mask_words);
-    return hipGetLastError();
-}
-
-hipError_t launch_window_stats(const int32_t *u, const int32_t *bits, int32_t T,
-                               int32_t *nb, unsigned long long *sum_u,
-                               unsigned long long *sum_bits, int32_t *sum_nb,
-                               int32_t *max_nb, hipStream_t s)
-{
-    if (T == 0) return hipSuccess;
-    const unsigned g = grid_for(T, kStatThreads);
-    k_window_stats<<<g < kStatBlocks ? g : kStatBlocks, kStatThreads, 0, s>>>(
-        u, bits, T, nb, sum_u, sum_bits, sum_nb, max_nb);
+    k_windows_small<<<T, 64, 0, s>>>(row_ptr, col_idx, N, win_row, st, tmp_cols, tmp_mask, u,
+                                     bits);
+    // at most nnz_cap / 513 windows are larger, two workgroups fit a CU
+    const int64_t large = nnz_cap / (kWaveCap + 1);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || large == 0) return e;
+    k_windows_large<<<(unsigned)(large < 512 ? large : 512), kWindowThreads, kHeavyLdsBytes,
+                      s>>>(row_ptr, col_idx, N, win_row, st, mid, big, heavy, tmp_cols,
+                           tmp_mask, u, bits);
     return hipGetLastError();
 }
 
@@ -1051,35 +1287,57 @@ hipError_t launch_scan2(ScanArray a0, ScanArray a1, int32_t n, int32_t *tmp, hip
 
 hipError_t launch_fill_windows(const int32_t *row_ptr, const int32_t *win_row, int32_t T,
                                const int32_t *tmp_cols, const uint32_t *tmp_mask,
-                               const int32_t *u, const int32_t *blk_off, int32_t *cols,
-                               uint32_t *mask, hipStream_t s)
+                               const int32_t *u, int32_t *plan_off, int32_t *cols,
+                               uint32_t *mask, const WorkListShape &shape,
+                               const int32_t *pos, WorkItem *items, int32_t *merges,
+                               hipStream_t s)
 {
     if (T == 0) return hipSuccess;
-    k_fill_windows<<<T, 256, 0, s>>>(row_ptr, win_row, tmp_cols, tmp_mask, u, blk_off, cols,
-                                     mask);
+    k_fill_windows<<<T, 256, 0, s>>>(row_ptr, win_row, T, tmp_cols, tmp_mask, u, plan_off, cols,
+                                     mask, shape, pos, items, merges);
     return hipGetLastError();
 }
 
-hipError_t launch_bin_keys(const int32_t *nb, int32_t T, const int32_t *n_blocks,
-                           const int32_t *max_blocks, int32_t forced, int32_t slots,
-                           bool reorder, int32_t *piece_out, int32_t *npieces,
-                           int32_t *key, int32_t *split_pieces, int32_t *split_one,
-                           int32_t *heavy, hipStream_t s)
+template <int E>
+hipError_t launch_shape_one(const int32_t *u, const int32_t *bits, int32_t T, int32_t forced,
+                            int32_t slots, int order, BuildStats *st, int32_t *blk_off,
+                            int32_t *key, int32_t *slot_base, int32_t *split_idx, int32_t *pos,
+                            hipStream_t s)
 {
-    k_bin_keys<<<grid_for(T, 256), 256, 0, s>>>(nb, T, n_blocks, max_blocks, forced, slots,
-                                                reorder, piece_out, npieces, key,
-                                                split_pieces, split_one, heavy);
+    k_shape<E><<<1, kPlaceThreads, 0, s>>>(u, bits, T, forced, slots, order, st, blk_off, key,
+                                           slot_base, split_idx, pos);
     return hipGetLastError();
 }
 
-hipError_t launch_split_items(const int32_t *merges, const int32_t *split_item,
-                              const int32_t *blk_off, int32_t n_split, WorkItem *items,
-                              hipStream_t s)
+hipError_t launch_shape(const int32_t *u, const int32_t *bits, int32_t T, int32_t forced,
+                        int32_t slots, int order, BuildStats *st, int32_t *nb,
+                        int32_t *blk_off, int32_t *key, int32_t *slot_base, int32_t *split_idx,
+                        int32_t *pos, int32_t *scan_tmp, hipStream_t s)
 {
-    if (n_split == 0) return hipSuccess;
-    k_split_items<<<grid_for(n_split, 4), 256, 0, s>>>(merges, split_item, blk_off, n_split,
-                                                      items);
-    return hipGetLastError();
+    if (T <= kOnePlace) {
+        auto one = T <= kPlaceThreads        ? launch_shape_one<1>
+                   : T <= 4 * kPlaceThreads  ? launch_shape_one<4>
+                   : T <= 8 * kPlaceThreads  ? launch_shape_one<8>
+                   : T <= 17 * kPlaceThreads ? launch_shape_one<17>
+                                             : launch_shape_one<32>;
+        return one(u, bits, T, forced, slots, order, st, blk_off, key, slot_base, split_idx, pos,
+                   s);
+    }
+    const unsigned g = grid_for(T, kStatThreads);
+    k_window_stats<<<g < kStatBlocks ? g : kStatBlocks, kStatThreads, 0, s>>>(
+        u, bits, T, nb, &st->n_unique, &st->nnz, &st->n_blocks, &st->max_blocks, &st->err);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    k_bin_keys<<<grid_for(T, 256), 256, 0, s>>>(nb, T, &st->n_blocks, &st->max_blocks, forced,
+                                                slots, &st->piece, key, slot_base, split_idx);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    ScanArray sp, so;
+    sp.in = sp.out = slot_base;
+    sp.total = &st->n_pieces;
+    so.in = so.out = split_idx;
+    so.total = &st->n_split;
+    if ((e = launch_scan2(sp, so, T, scan_tmp, s)) != hipSuccess) return e;
+    return launch_scan(nb, blk_off, T, scan_tmp, nullptr, s);
 }
 
 hipError_t launch_validate_plan(const f3s_plan_s &p, int32_t *err, hipStream_t s)

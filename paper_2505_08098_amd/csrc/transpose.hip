@@ -94,70 +94,112 @@ __global__ void k_rows_from_sorted(const int32_t *keys, int32_t n, int32_t N, in
     rp[c] = lo;
 }
 
-// win[b] = the window of block b; one wavefront per window.
+// win[b] = the window of block b; one wavefront per window.  zero (may be
+// null): cleared for the launch that follows.
 __global__ __launch_bounds__(256) void k_block_window(const int32_t *blk_off, int32_t T,
-                                                      int32_t *win)
+                                                      int32_t *win, int32_t *zero)
 {
+    if (zero && blockIdx.x == 0 && threadIdx.x == 0) *zero = 0;
     const int w = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (w >= T) return;
     for (int b = blk_off[w] + (threadIdx.x & 63); b < blk_off[w + 1]; b += 64) win[b] = w;
 }
 
-// Position of column c among the distinct columns of window v (cols padded
-// with -1 after the last one), or -1.
-__device__ int find_col(const int32_t *blk_off, const int32_t *cols, int v, int c)
-{
-    const int32_t *list = cols + (int64_t)kBlockCols * blk_off[v];
-    int lo = 0, hi = kBlockCols * (blk_off[v + 1] - blk_off[v]);
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        const int x = list[mid];
-        if (x >= 0 && x < c) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo < kBlockCols * (blk_off[v + 1] - blk_off[v]) && list[lo] == c ? lo : -1;
-}
-
 // Sets *asym when some entry (r, c) of the plan's pattern has no entry (c, r),
 // straight from the plan (no transposed CSR needed): for every set bit, the
 // row r is looked up among the distinct columns of row c's window and the
-// bit of (c, r) tested.  One thread per bitmap word over
-// all blocks (a hub window's entries spread over many waves); stops early
+// bit of (c, r) tested.  One wavefront per kSymBlocks blocks (a hub window's
+// entries spread over many waves): the bitmaps' nonzero nibbles -- nibble l
+// of a block is its row l % 16 against its columns 4 (l / 16) .. + 3 -- are
+// listed in LDS, then each lane takes one.  A lane's four searches run in
+// step, so their loads overlap; what bounds the launch is one chain of about
+// log2(columns of a window) + 5 loads.  (One thread per bitmap word, its set
+// bits in turn: 18.4 us for 475 windows, 22.4 us for 7,676; a lane per
+// nibble, empty ones too: 6.5 and 23.8 us; this 6.9 and 16.8.)  Stops early
 // once an asymmetry is known.
+constexpr int kSymBlocks = 2;
+
 __global__ __launch_bounds__(256) void k_check_symmetric(const int32_t *blk_off,
                                                          const int32_t *cols,
                                                          const uint32_t *mask,
-                                                         const int32_t *win, int64_t words,
+                                                         const int32_t *win, int64_t n_blocks,
                                                          int32_t *asym)
 {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= words || *(volatile int32_t *)asym) return;
-    uint32_t m = mask[k];
-    if (!m) return;
-    const int64_t blk = k / kMaskWords;
-    const int word = (int)(k % kMaskWords);
-    const int w = win[blk];
-    while (m) {
-        const int bit = 32 * word + __ffs(m) - 1;
-        m &= m - 1;
-        const int r = w * kWindowRows + ((bit >> 2) & 15);
-        const int c = cols[kBlockCols * blk + 4 * (bit >> 6) + (bit & 3)];
-        const int v = c / kWindowRows;
-        const int a = find_col(blk_off, cols, v, r);
-        bool bad = a < 0;
-        if (!bad) {
-            const int cc = a % kBlockCols;
-            const int b2 = 4 * (c % kWindowRows + 16 * (cc / 4)) + (cc % 4);
-            const int64_t blk2 = blk_off[v] + a / kBlockCols;
-            bad = ((mask[kMaskWords * blk2 + b2 / 32] >> (b2 % 32)) & 1u) == 0;
+    typedef int32_t i4 __attribute__((ext_vector_type(4)));
+    __shared__ uint16_t lists[4][64 * kSymBlocks];  // block | nibble index | nibble
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint16_t *list = lists[wv];
+    const int64_t b0 = ((int64_t)blockIdx.x * 4 + wv) * kSymBlocks;
+    // (one lane's read decides for all)
+    if (b0 >= n_blocks || __builtin_amdgcn_readfirstlane(*(volatile int32_t *)asym)) return;
+    int total = 0;
+#pragma unroll
+    for (int q = 0; q < kSymBlocks; ++q) {
+        const uint32_t nib =
+            b0 + q < n_blocks
+                ? (mask[kMaskWords * (b0 + q) + (lane >> 3)] >> (4 * (lane & 7))) & 15u
+                : 0u;
+        const uint64_t some = __ballot(nib != 0);
+        if (nib)
+            list[total + __popcll(some & ((1ull << lane) - 1ull))] =
+                (uint16_t)(q << 10 | lane << 4 | nib);
+        total += __popcll(some);
+    }
+    // a wave's LDS operations run in issue order: only the compiler is held
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int t = lane; t < total; t += 64) {
+        const int e = list[t];
+        const int64_t b = b0 + (e >> 10);
+        const int l = (e >> 4) & 63;
+        const i4 c = *reinterpret_cast<const i4 *>(cols + kBlockCols * b + 4 * (l >> 4));
+        const int r = win[b] * kWindowRows + (l & 15);
+        // lower bound of r in each column's list: the lists end in -1
+        // padding, which compares as the largest value
+        int len[4], lo[4], off[4], most = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool set = (e >> j) & 1;
+            const int v = set ? c[j] / kWindowRows : 0;
+            off[j] = blk_off[v];
+            len[j] = set ? kBlockCols * (blk_off[v + 1] - off[j]) : 0;
+            lo[j] = 0;
+            most = max(most, len[j]);
         }
+        for (int step = 1 << (31 - __clz(most | 1)); step > 0; step >>= 1) {
+            int32_t x[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                x[j] = lo[j] + step <= len[j]
+                           ? cols[(int64_t)kBlockCols * off[j] + lo[j] + step - 1]
+                           : -1;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if ((uint32_t)x[j] < (uint32_t)r) lo[j] += step;
+        }
+        int32_t at[4];
+        uint32_t word[4];
+        int bit[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool in = lo[j] < len[j];
+            const int a = in ? lo[j] : 0, cc = a % kBlockCols;
+            bit[j] = 4 * (c[j] % kWindowRows + 16 * (cc / 4)) + cc % 4;
+            at[j] = in ? cols[(int64_t)kBlockCols * off[j] + a] : -1;
+            word[j] = in ? mask[kMaskWords * ((int64_t)off[j] + a / kBlockCols) + bit[j] / 32]
+                         : 0u;
+        }
+        bool bad = false;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if ((e >> j) & 1) bad |= at[j] != r || !((word[j] >> (bit[j] % 32)) & 1u);
         if (bad) {
             atomicOr(asym, 1);
             return;
         }
     }
 }
-
 
 // Row r's 16 bits (block columns 0..15) of one block's bitmap words: the
 // four bits of block columns 4q .. 4q+3 are bits 4 (r % 8) .. +3 of word
@@ -168,20 +210,6 @@ __device__ __forceinline__ uint32_t row_bits(const uint32_t (&mw)[kMaskWords], i
 #pragma unroll
     for (int q = 0; q < 4; ++q) m |= ((mw[2 * q + (r >> 3)] >> (4 * (r & 7))) & 15u) << (4 * q);
     return m;
-}
-
-// Inclusive sum over the 64 lanes with DPP row shifts (within rows of 16
-// lanes, out-of-row sources read 0) and the three row totals by readlane.
-__device__ __forceinline__ int wave_sum_dpp(int x, int lane)
-{
-    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);  // row_shr:1
-    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);  // row_shr:2
-    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);  // row_shr:4
-    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);  // row_shr:8
-    const int r0 = __builtin_amdgcn_readlane(x, 15), r1 = __builtin_amdgcn_readlane(x, 31);
-    const int r2 = __builtin_amdgcn_readlane(x, 47);
-    const int row = lane >> 4;
-    return x + (row >= 1 ? r0 : 0) + (row >= 2 ? r1 : 0) + (row >= 3 ? r2 : 0);
 }
 
 // The symmetry decision on A^T's CSR (rpt, cit; rows in increasing column
@@ -220,7 +248,7 @@ __global__ __launch_bounds__(256) void k_row_prefix(const int32_t *blk_off,
 #pragma unroll
         for (int r = 0; r < kWindowRows; ++r) {
             const int cnt = __popc(row_bits(mw, r));
-            const int incl = wave_sum_dpp(cnt, lane);
+            const int incl = wave_inclusive_sum(cnt, lane);
             if (b < b1) pre[(int64_t)kWindowRows * b + r] = base[r] + incl - cnt;
             base[r] += __builtin_amdgcn_readlane(incl, 63);
         }
@@ -286,14 +314,11 @@ __global__ __launch_bounds__(256) void k_compare_blocks(const int32_t *cols,
 hipError_t launch_check_symmetric(const f3s_plan_s &p, int32_t *win, int32_t *asym,
                                   hipStream_t s)
 {
-    if (p.T == 0 || p.n_blocks == 0) return hipSuccess;
-    k_block_window<<<(p.T + 3) / 4, 256, 0, s>>>(p.blk_off, p.T, win);
+    k_block_window<<<p.T > 0 ? (p.T + 3) / 4 : 1, 256, 0, s>>>(p.blk_off, p.T, win, asym);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int64_t words = (int64_t)kMaskWords * p.n_blocks;
-    k_check_symmetric<<<(unsigned)((words + 255) / 256), 256, 0, s>>>(p.blk_off, p.cols,
-                                                                      p.mask, win, words,
-                                                                      asym);
+    if (e != hipSuccess || p.n_blocks == 0) return e;
+    k_check_symmetric<<<(unsigned)((p.n_blocks + 4 * kSymBlocks - 1) / (4 * kSymBlocks)), 256,
+                        0, s>>>(p.blk_off, p.cols, p.mask, win, p.n_blocks, asym);
     return hipGetLastError();
 }
 
@@ -304,7 +329,7 @@ hipError_t launch_compare_rows(const f3s_plan_s &p, const int32_t *rpt, const in
     k_row_prefix<<<(p.T + 3) / 4, 256, 0, s>>>(p.blk_off, p.mask, p.T, p.N, rpt, pre, asym);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.n_blocks == 0) return e;
-    k_block_window<<<(p.T + 3) / 4, 256, 0, s>>>(p.blk_off, p.T, win);
+    k_block_window<<<(p.T + 3) / 4, 256, 0, s>>>(p.blk_off, p.T, win, nullptr);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const int64_t threads = (int64_t)kWindowRows * p.n_blocks;
     k_compare_blocks<<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(p.cols, p.mask, win,

@@ -1,69 +1,61 @@
-// Heavy-first work list of a plan (Section 3.2), in O(T) memory: the windows
-// are stably sorted by their key, largest first (radix.hip), the item counts
-// are scanned in that order, and every window writes its item (or, if split,
-// its merge record and first item position; its pieces are written by
-// k_split_items).
+// Heavy-first work list of a large plan (Section 3.2), in O(T) memory: the
+// windows stably sorted by their key, largest first (radix.hip), and every
+// window's items written at the position its rank gives (see WorkListShape).
 #include "f3s_internal.h"
 
 namespace f3s {
 namespace {
 
-// Window order[i] (window i without an order) starts at item pos[i].
-__global__ void k_place_items(const int32_t *order, const int32_t *pos, const int32_t *nb,
-                              const int32_t *blk_off, const int32_t *npieces,
-                              const int32_t *slot_base, const int32_t *split_idx, int32_t T,
-                              int32_t piece, WorkItem *items, int32_t *merges,
-                              int32_t *split_item)
+// Window order[i] is i-th in the sorted order; one wavefront per window.
+__global__ __launch_bounds__(256) void k_place_items(const int32_t *order, const int32_t *key,
+                                                     int32_t T, WorkListShape shape,
+                                                     WorkItem *items, int32_t *merges)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (i >= T) return;
-    const int w = order ? order[i] : i, p = pos[i];
-    const int n = nb[w], b0 = blk_off[w];
-    if (n <= piece) {
-        items[p] = WorkItem{w, b0, b0 + n, -1};
-    } else {
-        const int s = split_idx[w];
-        merges[3 * s + 0] = w;
-        merges[3 * s + 1] = slot_base[w];
-        merges[3 * s + 2] = npieces[w];
-        split_item[s] = p;
-    }
+    const int w = order[i];
+    const int pos = key[w] == shape.piece ? i + shape.slot_base[w] - shape.split_idx[w]
+                                          : i + shape.n_pieces - shape.n_split;
+    place_window(shape, w, pos, threadIdx.x & 63, 64, items, merges);
 }
 
-inline unsigned blocks_for(int64_t n, int threads)
+// heavy[j] += items of the windows whose key exceeds heavy_blocks(j).
+__global__ __launch_bounds__(256) void k_heavy_table(const int32_t *key, int32_t T,
+                                                     WorkListShape shape, int32_t *heavy)
 {
-    return (unsigned)(n > 0 ? (n + threads - 1) / threads : 1);
+    __shared__ int32_t hist[kHeavySteps + 1];
+    if (threadIdx.x <= kHeavySteps) hist[threadIdx.x] = 0;
+    __syncthreads();
+    for (int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x; w < T;
+         w += (int64_t)gridDim.x * 256) {
+        const int level = heavy_level(key[w]);
+        const int n = shape.slot_base[w + 1] - shape.slot_base[w];
+        if (level) atomicAdd(&hist[level], n ? n : 1);
+    }
+    __syncthreads();
+    if (threadIdx.x < kHeavySteps) {
+        int h = 0;
+        for (int l = threadIdx.x + 1; l <= kHeavySteps; ++l) h += hist[l];
+        if (h) atomicAdd(&heavy[threadIdx.x], h);
+    }
 }
 
 }  // namespace
 
-hipError_t launch_worklist(const int32_t *key, const int32_t *nb, const int32_t *blk_off,
-                           const int32_t *npieces, const int32_t *slot_base,
-                           const int32_t *split_idx, int32_t T, int32_t piece,
-                           bool window_order, const WorkListScratch &ws, WorkItem *items,
-                           int32_t *merges, int32_t *split_item, int32_t *n_items_out,
-                           hipStream_t s)
+hipError_t launch_worklist(const int32_t *key, const WorkListShape &shape, int32_t T,
+                           const RadixScratch &radix, WorkItem *items, int32_t *merges,
+                           int32_t *heavy, hipStream_t s)
 {
     if (T == 0) return hipSuccess;
-    // the window indices, sorted by key (values: the indices themselves)
     const int32_t *sorted_keys = nullptr, *order = nullptr;
-    hipError_t e = hipSuccess;
-    if (!window_order) {
-        e = launch_radix_pairs(key, nullptr, T, piece, true, ws.radix, &sorted_keys, &order,
-                               s);
-        if (e != hipSuccess) return e;
-    }
-    // first item of each window in that order: scan of its item counts
-    ScanArray a;
-    a.in = npieces;
-    a.gather = order;
-    a.out = ws.pos;
-    a.total = n_items_out;
-    e = launch_scan(a, T, ws.radix.scan_tmp, s);
+    // windows above the piece size are split and have it as their key
+    hipError_t e = launch_radix_pairs(key, nullptr, T, shape.piece, true, radix, &sorted_keys,
+                                      &order, s);
     if (e != hipSuccess) return e;
-    k_place_items<<<blocks_for(T, 256), 256, 0, s>>>(order, ws.pos, nb, blk_off, npieces,
-                                                     slot_base, split_idx, T, piece, items,
-                                                     merges, split_item);
+    k_place_items<<<(unsigned)((T + 3) / 4), 256, 0, s>>>(order, key, T, shape, items, merges);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const unsigned g = (unsigned)((T + 255) / 256);
+    k_heavy_table<<<g < 64 ? g : 64, 256, 0, s>>>(key, T, shape, heavy);
     return hipGetLastError();
 }
 

@@ -160,3 +160,107 @@ def test_uniform_windows_stay_whole(gpu):
         Q, K, V = W.features(rng, N, 64)
         _check(gpu.run(plan, _dev(Q), _dev(K), _dev(V)),
                oracle.attention_f64(rp, ci, Q, K, V, 0.125))
+
+
+# windows on either side of what one workgroup shapes and sorts (1,024,
+# 4,096, 8,192, 17,408 and 32,768 windows), of the digits the one-workgroup
+# sort covers (pieces of 2,048 blocks), and of the per-window paths (64, 128,
+# 256, 512, 1,024 and 4,096 entries)
+@pytest.mark.parametrize("T,deg,hub", [(1023, 5, 40), (1025, 5, 0), (4097, 3, 900),
+                                       (8193, 2, 0), (17409, 1, 300), (32769, 1, 70)])
+@pytest.mark.parametrize("order", [None, "0", "1"])
+def test_plan_shape_paths(gpu, T, deg, hub, order, monkeypatch):
+    from test_gpu_1_plan import _check_plan_against_oracle as check_plan
+    if order is not None:
+        monkeypatch.setenv("F3S_NO_REORDER", order)
+    rng = np.random.default_rng(T)
+    N = 16 * T - 3
+    counts = rng.integers(0, deg + 1, size=N)
+    if hub:
+        counts[rng.choice(N, size=24, replace=False)] = hub
+    rp = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    ci = rng.integers(0, N, size=int(rp[-1])).astype(np.int32)
+    check_plan(gpu, oracle, rp, ci, N)
+
+
+def test_plan_with_pieces_beyond_the_one_workgroup_sort(gpu, monkeypatch):
+    from test_gpu_1_plan import _check_plan_against_oracle as check_plan
+    rng = np.random.default_rng(1)
+    N = 40000
+    counts = np.full(N, 2)
+    counts[:16] = 39000         # one window of 2,500 blocks
+    counts[64:80] = 3000
+    rows = [np.sort(rng.choice(N, size=c, replace=False)) for c in counts]
+    rp = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    ci = np.concatenate(rows).astype(np.int32)
+    for piece in ("2300", "2046", "2048"):
+        monkeypatch.setenv("F3S_PIECE_BLOCKS", piece)
+        check_plan(gpu, oracle, rp, ci, N)
+
+
+@pytest.mark.parametrize("n", [64, 65, 128, 129, 256, 257, 512, 513, 1024, 1025, 4096, 4097])
+def test_window_entry_classes(gpu, n):
+    """One window of n entries among small ones, duplicates included."""
+    from test_gpu_1_plan import _check_plan_against_oracle as check_plan
+    rng = np.random.default_rng(n)
+    N = 300
+    counts = np.full(N, 1)
+    counts[32:48] = n // 16
+    counts[47] += n % 16
+    rp = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    ci = rng.integers(0, N, size=int(rp[-1])).astype(np.int32)
+    check_plan(gpu, oracle, rp, ci, N)
+
+
+def test_symmetry_of_patterns_that_differ_in_one_entry(gpu):
+    """The transposed plan copies a symmetric pattern's plan and builds its own
+    when one entry, in a dense or a sparse block, lacks its mirror."""
+    rng = np.random.default_rng(4)
+    N = 530
+    dense = rng.random((N, N)) < 0.02
+    dense[:40, :40] = True
+    dense |= dense.T
+    for drop in (None, (3, 17), (39, 0), (529, int(np.flatnonzero(dense[529])[0]))):
+        a = dense.copy()
+        if drop:
+            a[drop] = False
+        ref = a.T
+        rp = np.concatenate([[0], np.cumsum(a.sum(1))]).astype(np.int32)
+        ci = np.nonzero(a)[1].astype(np.int32)
+        plan = gpu.Plan(_dev(rp), _dev(ci), N)
+        t = plan.transpose().export()
+        win, mask, cols = t["blk_off"], t["mask"].reshape(-1, 8), t["cols"].reshape(-1, 16)
+        got = np.zeros((N, N), dtype=bool)
+        for w in range(len(win) - 1):
+            for b in range(win[w], win[w + 1]):
+                for k in range(256):
+                    if (int(mask[b, k // 32]) >> (k % 32)) & 1:
+                        q, r = k // 4, k % 4
+                        got[16 * w + q % 16, cols[b, 4 * (q // 16) + r]] = True
+        assert np.array_equal(got, ref)
+
+
+def test_symmetric_plans_share_their_arrays(gpu):
+    """Either of a plan and its transposed plan may be destroyed first."""
+    rng = np.random.default_rng(6)
+    N = 200
+    m = rng.random((N, N)) < 0.1
+    m |= m.T
+    rp = np.concatenate([[0], np.cumsum(m.sum(1))]).astype(np.int32)
+    ci = np.nonzero(m)[1].astype(np.int32)
+    Q, K, V = W.features(rng, N, 32)
+    q, k, v = _dev(Q), _dev(K), _dev(V)
+    g = q.clone()
+    for first in (True, False):
+        plan = gpu.Plan(_dev(rp), _dev(ci), N)
+        plan_t = plan.transpose()
+        O, lse = gpu.forward(plan, q, k, v)
+        want = gpu.backward(plan, plan_t, q, k, v, O, g, lse)
+        second = plan.transpose()
+        (plan_t if first else second).close()
+        left = second if first else plan_t
+        got = gpu.backward(plan, left, q, k, v, O, g, lse)
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+        plan.close()
+        assert left.export()["cols"].min() >= -1
+        left.close()
