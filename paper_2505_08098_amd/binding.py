@@ -159,6 +159,61 @@ def _check_device_tensor(t, name, dtype, device=None):
         raise ValueError(f"{name} is on {t.device}, the operands on {device}")
 
 
+# The handle of the current stream of a device: torch's own accessor where it
+# has one (0.1 us; building a Stream object takes 1.8).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+    lambda index: torch.cuda.current_stream(index).cuda_stream)
+_TENSORS = (torch.Tensor, torch.nn.Parameter)
+
+
+def _plain(plan, dtype, *tensors):
+    """Whether the tensors are what the calls take without further ado:
+    contiguous, of ``dtype``, on the plan's device, of one [N, d] or
+    [N, H, d] shape.  False sends the caller to its own checks, which say
+    what is wrong (or accept a tensor of another class)."""
+    shape = tensors[0].shape if type(tensors[0]) in _TENSORS else ()
+    if len(shape) not in (2, 3) or shape[0] != plan.N:
+        return False
+    dev = plan.device
+    for t in tensors:
+        if (type(t) not in _TENSORS or t.dtype is not dtype or t.shape != shape
+                or t.device != dev or not t.is_contiguous()):
+            return False
+    return True
+
+
+def _empty_like(t, dtype):
+    if type(t) in _TENSORS:
+        return torch.empty_like(t, dtype=dtype, memory_format=torch.contiguous_format)
+    return torch.empty(t.shape, dtype=dtype, device=t.device)
+
+
+def _stream(stream, device):
+    return stream.cuda_stream if stream is not None else _raw_stream(device.index)
+
+
+class _BuildOn:
+    """Makes ``device`` current for a plan build, which runs on the null
+    stream: work on another current stream that the build reads or whose
+    memory its scratch reuses ends first (torch's default stream is the null
+    stream itself)."""
+
+    def __init__(self, device):
+        self.device = device
+        self.guard = None
+
+    def __enter__(self):
+        if torch.cuda.current_device() != self.device.index:
+            self.guard = torch.cuda.device(self.device)
+            self.guard.__enter__()
+        if _raw_stream(self.device.index):
+            torch.cuda.current_stream().synchronize()
+
+    def __exit__(self, *exc):
+        if self.guard is not None:
+            self.guard.__exit__(*exc)
+
+
 def _qkv_shape(Q):
     """Shape of a one-head [N, d] or multi-head [N, H, d] operand."""
     if not isinstance(Q, torch.Tensor) or Q.dim() not in (2, 3):
@@ -193,8 +248,7 @@ class Plan:
         if seg.ndim != 1 or seg.size < 1:
             raise ValueError("seg_ptr must be a non-empty 1-D sequence")
         ci = col_idx.data_ptr() if col_idx.numel() else None
-        with torch.cuda.device(row_ptr.device):
-            torch.cuda.current_stream().synchronize()
+        with _BuildOn(row_ptr.device):
             h = L.f3s_plan_segments(row_ptr.data_ptr(), ci, int(N),
                                     seg.ctypes.data_as(ctypes.c_void_p), int(seg.size - 1))
         if not h:
@@ -215,8 +269,7 @@ class Plan:
         """Plan of the transposed pattern (f3s_plan_transpose_ws, its scratch
         lent from torch's caching allocator)."""
         L = load_library()
-        with torch.cuda.device(self.device):
-            torch.cuda.current_stream().synchronize()
+        with _BuildOn(self.device):
             nbytes = L.f3s_plan_transpose_workspace_bytes(self.handle)
             ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
             h = L.f3s_plan_transpose_ws(self.handle, ws.data_ptr(), nbytes)
@@ -232,8 +285,7 @@ class Plan:
         if row_ptr.numel() != int(N) + 1:
             raise ValueError("row_ptr must hold N + 1 entries")
         ci = col_idx.data_ptr() if col_idx.numel() else None
-        with torch.cuda.device(row_ptr.device):
-            torch.cuda.current_stream().synchronize()
+        with _BuildOn(row_ptr.device):
             # the build's scratch from torch's caching allocator (the build is
             # synchronous: the memory is free again when the call returns)
             nbytes = L.f3s_plan_workspace_bytes(int(N), col_idx.numel())
@@ -308,29 +360,28 @@ def run(plan, Q, K, V, scale=None, out=None, stream=None):
     sharing the plan); out: optional fp32 tensor of the same shape; the call
     is asynchronous on ``stream`` (default: torch's current stream).
     """
-    L = load_library()
-    shape = tuple(Q.shape)
-    for t, n in ((Q, "Q"), (K, "K"), (V, "V")):
-        _check_device_tensor(t, n, torch.float16, plan.device)
-        if t.dim() not in (2, 3) or t.shape[0] != plan.N:
-            raise ValueError(f"{n} must be [N, d] or [N, H, d] with N = {plan.N}")
-        if tuple(t.shape) != shape:
-            raise ValueError("Q, K, V must share one shape")
+    if not _plain(plan, torch.float16, Q, K, V):
+        shape = tuple(Q.shape)
+        for t, n in ((Q, "Q"), (K, "K"), (V, "V")):
+            _check_device_tensor(t, n, torch.float16, plan.device)
+            if t.dim() not in (2, 3) or t.shape[0] != plan.N:
+                raise ValueError(f"{n} must be [N, d] or [N, H, d] with N = {plan.N}")
+            if tuple(t.shape) != shape:
+                raise ValueError("Q, K, V must share one shape")
+    shape = Q.shape
     H = shape[1] if len(shape) == 3 else 1
     d = shape[-1]
     if out is None:
-        out = torch.empty(shape, dtype=torch.float32, device=Q.device)
+        out = _empty_like(Q, torch.float32)
     else:
         _check_device_tensor(out, "out", torch.float32, Q.device)
-        if tuple(out.shape) != shape:
+        if out.shape != shape:
             raise ValueError("out must have the shape of Q")
     if scale is None:
         scale = 1.0 / math.sqrt(d)
-    if stream is None:
-        stream = torch.cuda.current_stream(Q.device)
-    rc = L.f3s_run_mh(plan.handle, Q.data_ptr(), K.data_ptr(), V.data_ptr(),
-                      out.data_ptr(), int(H), int(d), float(scale),
-                      ctypes.c_void_p(stream.cuda_stream))
+    rc = load_library().f3s_run_mh(plan.handle, Q.data_ptr(), K.data_ptr(), V.data_ptr(),
+                                   out.data_ptr(), H, d, float(scale),
+                                   _stream(stream, Q.device))
     if rc != F3S_OK:
         raise F3SError(rc, "f3s_run_mh")
     return out
@@ -338,30 +389,32 @@ def run(plan, Q, K, V, scale=None, out=None, stream=None):
 
 def forward(plan, Q, K, V, scale=None, out=None, lse=None, stream=None):
     """f3s_forward: returns (O, lse) with lse fp32 [N] or [N, H]."""
-    shape = _qkv_shape(Q)
+    if not _plain(plan, torch.float16, Q, K, V):
+        shape = _qkv_shape(Q)
+        for t, n in ((Q, "Q"), (K, "K"), (V, "V")):
+            _check_device_tensor(t, n, torch.float16, plan.device)
+            if tuple(t.shape) != shape or shape[0] != plan.N:
+                raise ValueError("Q, K, V must share one [N, d] / [N, H, d] shape")
+    shape = Q.shape
     H = shape[1] if len(shape) == 3 else 1
-    for t, n in ((Q, "Q"), (K, "K"), (V, "V")):
-        _check_device_tensor(t, n, torch.float16, plan.device)
-        if tuple(t.shape) != shape or shape[0] != plan.N:
-            raise ValueError("Q, K, V must share one [N, d] / [N, H, d] shape")
     if lse is None:
         lse = torch.empty(shape[:-1], dtype=torch.float32, device=Q.device)
-    _check_device_tensor(lse, "lse", torch.float32, Q.device)
-    if lse.numel() != plan.N * H:
-        raise ValueError("lse must hold N * H values")
+    else:
+        _check_device_tensor(lse, "lse", torch.float32, Q.device)
+        if lse.numel() != plan.N * H:
+            raise ValueError("lse must hold N * H values")
     if out is None:
-        out = torch.empty(shape, dtype=torch.float32, device=Q.device)
-    _check_device_tensor(out, "out", torch.float32, Q.device)
-    if tuple(out.shape) != shape:
-        raise ValueError("out must have the shape of Q")
+        out = _empty_like(Q, torch.float32)
+    else:
+        _check_device_tensor(out, "out", torch.float32, Q.device)
+        if out.shape != shape:
+            raise ValueError("out must have the shape of Q")
     d = shape[-1]
     if scale is None:
         scale = 1.0 / math.sqrt(d)
-    if stream is None:
-        stream = torch.cuda.current_stream(Q.device)
     rc = load_library().f3s_forward(plan.handle, Q.data_ptr(), K.data_ptr(), V.data_ptr(),
-                                    out.data_ptr(), lse.data_ptr(), int(H), int(d),
-                                    float(scale), ctypes.c_void_p(stream.cuda_stream))
+                                    out.data_ptr(), lse.data_ptr(), H, d, float(scale),
+                                    _stream(stream, Q.device))
     if rc != F3S_OK:
         raise F3SError(rc, "f3s_forward")
     return out, lse
@@ -378,34 +431,35 @@ def forward_typed(plan, Q, K, V, out_dtype=torch.float32, scale=None, out=None,
     [N, H, d]); O of ``out_dtype`` (fp32 or fp16).  Returns (O, lse) with lse
     None unless ``want_lse`` or an ``lse`` tensor is given."""
     shape = _qkv_shape(Q)
-    H = shape[1] if len(shape) == 3 else 1
-    if Q.dtype not in (torch.float16, torch.bfloat16, torch.float8_e4m3fn):
+    dtype = Q.dtype
+    if dtype not in (torch.float16, torch.bfloat16, torch.float8_e4m3fn):
         raise TypeError(f"Q must be float16, bfloat16 or float8_e4m3fn, got {Q.dtype}")
-    for t, n in ((Q, "Q"), (K, "K"), (V, "V")):
-        _check_device_tensor(t, n, Q.dtype, plan.device)
-        if tuple(t.shape) != shape or shape[0] != plan.N:
-            raise ValueError("Q, K, V must share one [N, d] / [N, H, d] shape")
+    if not _plain(plan, dtype, Q, K, V):
+        for t, n in ((Q, "Q"), (K, "K"), (V, "V")):
+            _check_device_tensor(t, n, dtype, plan.device)
+            if tuple(t.shape) != shape or shape[0] != plan.N:
+                raise ValueError("Q, K, V must share one [N, d] / [N, H, d] shape")
+    H = shape[1] if len(shape) == 3 else 1
     if out is None:
-        out = torch.empty(shape, dtype=out_dtype, device=Q.device)
-    _check_device_tensor(out, "out", out_dtype, Q.device)
-    if tuple(out.shape) != shape:
-        raise ValueError("out must have the shape of Q")
-    if lse is None and want_lse:
-        lse = torch.empty(shape[:-1], dtype=torch.float32, device=Q.device)
+        out = _empty_like(Q, out_dtype)
+    else:
+        _check_device_tensor(out, "out", out_dtype, Q.device)
+        if tuple(out.shape) != shape:
+            raise ValueError("out must have the shape of Q")
     if lse is not None:
         _check_device_tensor(lse, "lse", torch.float32, Q.device)
         if lse.numel() != plan.N * H:
             raise ValueError("lse must hold N * H values")
+    elif want_lse:
+        lse = torch.empty(shape[:-1], dtype=torch.float32, device=Q.device)
     d = shape[-1]
     if scale is None:
         scale = 1.0 / math.sqrt(d)
-    if stream is None:
-        stream = torch.cuda.current_stream(Q.device)
     rc = load_library().f3s_forward_typed(
-        plan.handle, Q.data_ptr(), K.data_ptr(), V.data_ptr(), _DTYPE_CODE[Q.dtype],
+        plan.handle, Q.data_ptr(), K.data_ptr(), V.data_ptr(), _DTYPE_CODE[dtype],
         out.data_ptr(), _DTYPE_CODE.get(out_dtype, -1),
-        lse.data_ptr() if lse is not None else None, int(H), int(d), float(scale),
-        ctypes.c_void_p(stream.cuda_stream))
+        lse.data_ptr() if lse is not None else None, H, d, float(scale),
+        _stream(stream, Q.device))
     if rc != F3S_OK:
         raise F3SError(rc, "f3s_forward_typed")
     return out, lse
@@ -420,25 +474,24 @@ def backward(plan, plan_t, Q, K, V, O, dO, lse, scale=None, stream=None):
     d = shape[-1]
     if Q.dtype not in (torch.float16, torch.bfloat16):
         raise TypeError("Q, K, V, dO must be float16 or bfloat16")
-    for t, n in ((Q, "Q"), (K, "K"), (V, "V"), (dO, "dO")):
-        _check_device_tensor(t, n, Q.dtype, plan.device)
-        if tuple(t.shape) != shape or shape[0] != plan.N:
-            raise ValueError(f"{n} must have the shape of Q, with N = {plan.N} rows")
+    if not _plain(plan, Q.dtype, Q, K, V, dO):
+        for t, n in ((Q, "Q"), (K, "K"), (V, "V"), (dO, "dO")):
+            _check_device_tensor(t, n, Q.dtype, plan.device)
+            if tuple(t.shape) != shape or shape[0] != plan.N:
+                raise ValueError(f"{n} must have the shape of Q, with N = {plan.N} rows")
     _check_device_tensor(O, "O", torch.float32, Q.device)
     _check_device_tensor(lse, "lse", torch.float32, Q.device)
     if tuple(O.shape) != shape or lse.numel() != plan.N * H:
         raise ValueError("O must match Q; lse must hold N * H values")
-    dQ, dK, dV = (torch.empty(shape, dtype=torch.float32, device=Q.device) for _ in range(3))
+    dQ, dK, dV = (_empty_like(Q, torch.float32) for _ in range(3))
     row_stats = torch.empty(shape[:-1] + (2,), dtype=torch.float32, device=Q.device)
     if scale is None:
         scale = 1.0 / math.sqrt(d)
-    if stream is None:
-        stream = torch.cuda.current_stream(Q.device)
     rc = load_library().f3s_backward_typed(
         plan.handle, plan_t.handle, Q.data_ptr(), K.data_ptr(), V.data_ptr(),
         _DTYPE_CODE[Q.dtype], O.data_ptr(), dO.data_ptr(), lse.data_ptr(),
-        row_stats.data_ptr(), dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(), int(H), int(d),
-        float(scale), ctypes.c_void_p(stream.cuda_stream))
+        row_stats.data_ptr(), dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(), H, d,
+        float(scale), _stream(stream, Q.device))
     if rc != F3S_OK:
         raise F3SError(rc, "f3s_backward_typed")
     return dQ, dK, dV
