@@ -20,6 +20,17 @@
 // P does in the bf16 forward, so about 16 significant bits survive.
 // (backward.hip instantiates the fp16 kernels, backward_bf16.hip the bf16
 // ones.)
+//
+// What bounds both passes: the rate of the gathered rows, with too few waves
+// resident to hide a gather's latency (registers), so each instruction between
+// a pair's arrival and the next pair's loads counts.  As in the forward the
+// mask is a table in LDS and padding one DPP maximum; the sums of dP start at
+// -delta, and the dK/dV pass reads its rows' records four at a time: 81 and 86
+// vector instructions per pair at d = 64 became 53 and 57.  Sequence of 16,001
+// tokens, 2 heads of d = 128, forward and backward 231 -> 226 us; the
+// hub-heavy graph (d = 64, 4 heads, 384 us), bound by its rows' rate, is
+// unchanged, and a fourth wave per SIMD in its dK/dV pass costs 3%: more rows
+// in flight share the same L2.
 #pragma once
 
 #include "kernel_common.h"
@@ -77,23 +88,24 @@ template <> struct BwdDqWaves<64> { static constexpr int value = 4; };
 
 // Row-contiguous gather of the 32 rows (two blocks) of a block pair from two
 // row-major fp16 matrices A and B (same rows): chunk f = lane + 64 j is row
-// f / LPR, 16-byte chunk f % LPR.  `c` holds, in lanes 0..31, the row id of
-// pair slot `lane` (already free of padding).
+// f / LPR, 16-byte chunk f % LPR.  `c` holds, in lanes 0..31, pair slot
+// `lane`'s row id (already free of padding).
 template <int D, bool kWide>
 __device__ __forceinline__ void gather_pair(const _Float16 *A, const _Float16 *B, int c,
                                             int ld, int lane, h8 *sa, h8 *sb)
 {
     constexpr int LPR = D / 8, NI = D / 16;
+    const int coff = kWide ? c : c * (2 * ld);  // the slot's byte offset (kWide: row id)
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
         const int f = lane + 64 * j;
-        const int row = __shfl(c, f / LPR);
+        const int cj = __builtin_amdgcn_ds_bpermute(4 * (f / LPR), coff);
         if constexpr (kWide) {
-            const int64_t off = (int64_t)row * ld + 8 * (f % LPR);
+            const int64_t off = (int64_t)cj * ld + 8 * (f % LPR);
             sa[j] = load16(A + off);
             sb[j] = load16(B + off);
         } else {
-            const uint32_t off = (uint32_t)row * (uint32_t)(2 * ld) + 16u * (f % LPR);
+            const uint32_t off = (uint32_t)cj + 16u * (f % LPR);
             sa[j] = load16_off(A, off);
             sb[j] = load16_off(B, off);
         }
@@ -111,13 +123,12 @@ __device__ __forceinline__ void stage_pair(_Float16 *tile, int stride, int lane,
     }
 }
 
-// Padding slots (-1) take the first slot of their block (slot 0 or 16),
-// which is never padding; its bitmap bit is clear, so it contributes 0.
-__device__ __forceinline__ int sanitize_slot(int ncol, int lane)
+// 2^x where sel is all ones, 0 where it is zero (also for a masked score
+// that overflowed).
+__device__ __forceinline__ float masked_exp2(float x, uint32_t sel)
 {
-    const int f0 = __builtin_amdgcn_readlane(ncol, 0);
-    const int f1 = __builtin_amdgcn_readlane(ncol, 16);
-    return ncol < 0 ? ((lane & 16) ? f1 : f0) : ncol;
+    return __builtin_bit_cast(
+        float, __builtin_bit_cast(uint32_t, __builtin_amdgcn_exp2f(x)) & sel);
 }
 
 // dQ over the row windows of A.  Lane (i, g): query row i of the window;
@@ -147,6 +158,8 @@ __attribute__((amdgpu_waves_per_eu(BwdDqWaves<D>::value, 8))) void k_bwd_dq(
 
     const int lane = NW > 1 ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
     const int i = lane & 15, g = lane >> 4;
+    __shared__ mask_words_t mask_table[16];
+    fill_mask_table(mask_table, lane);
     // window-major, or head by head when K and V exceed the caches (as in
     // the forward)
     const int n_gr = gridDim.x / nh;
@@ -212,22 +225,22 @@ __attribute__((amdgpu_waves_per_eu(BwdDqWaves<D>::value, 8))) void k_bwd_dq(
     h8 kst[NI], vst[NI];
     uint32_t mwa = 0, mwb = 0;
     int ncol = 0;
-    auto load_cols = [&](int b) {
-        const int slot = lane & 31;
-        const int blk = slot < 16 ? min(b, b1 - 1) : min(b + 1, b1 - 1);
-        ncol = cols[(int64_t)kBlockCols * blk + (slot & 15)];
-    };
+    const uint32_t lane_col = 4u * (lane & 31);
+    auto load_cols = [&](int b) { ncol = load_pair_cols(cols, b, b1, lane_col); };
     auto load_pair = [&](int b) {
-        gather_pair<D, kWide>(K, V, sanitize_slot(ncol, lane), ld, lane, kst, vst);
-        mwa = mask[(int64_t)kMaskWords * b + (lane >> 3)];
-        mwb = mask[(int64_t)kMaskWords * min(b + 1, b1 - 1) + (lane >> 3)];
+        gather_pair<D, kWide>(K, V, pad_cols(ncol), ld, lane, kst, vst);
+        const uint32_t *mp = mask + (int64_t)kMaskWords * b;
+        mwa = mp[lane >> 3];
+        mwb = mp[(b + 1 < b1 ? kMaskWords : 0) + (lane >> 3)];
     };
-    const int nib_shift = 4 * (lane & 7);
+    const uint32_t nib_rot = mask_nibble_rot(lane);
     auto step = [&](int b, bool prefetch) {
         stage_pair<D>(tK, LSK, lane, kst);
         stage_pair<D>(tV, LSV, lane, vst);
         tile_fence<NW>();
-        f4 s0 = f4{0.f, 0.f, 0.f, 0.f}, s1 = s0, d0 = s0, d1 = s0;
+        f4 s0 = f4{0.f, 0.f, 0.f, 0.f}, s1 = s0;
+        // dP - delta: the sums start at -delta
+        f4 d0 = f4{-dl, -dl, -dl, -dl}, d1 = d0;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             const h8 ka = *reinterpret_cast<const h8 *>(&tK[i * LSK + 32 * c + 8 * g]);
@@ -242,24 +255,26 @@ __attribute__((amdgpu_waves_per_eu(BwdDqWaves<D>::value, 8))) void k_bwd_dq(
             d0 = bmma<kBF16>(va, gq[c], d0);
             d1 = bmma<kBF16>(vb, gq[c], d1);
         }
-        const uint32_t nib0 = (mwa >> nib_shift) & 15u;
-        const uint32_t nib1 = b + 1 < b1 ? (mwb >> nib_shift) & 15u : 0u;
+        const uint32_t m0 = mask_entry(mwa, nib_rot, 0xF0u);
+        const uint32_t m1 = mask_entry(mwb, nib_rot, b + 1 < b1 ? 0xF0u : 0u);
         if (prefetch) {
             load_pair(b + 2);
             load_cols(b + 4);
         }
+        const mask_words_t sel0 = mask_words_at(mask_table, m0);
+        const mask_words_t sel1 = mask_words_at(mask_table, m1);
         h8 dsh, dsl;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const float p0 = (nib0 >> r) & 1u ? __builtin_amdgcn_exp2f(s0[r] * sl2 - lse2) : 0.f;
-            const float p1 = (nib1 >> r) & 1u ? __builtin_amdgcn_exp2f(s1[r] * sl2 - lse2) : 0.f;
+            const float p0 = masked_exp2(s0[r] * sl2 - lse2, sel0[r]);
+            const float p1 = masked_exp2(s1[r] * sl2 - lse2, sel1[r]);
             {
-                const h2 t = operand<kBF16>(p0 * (d0[r] - dl));
+                const h2 t = operand<kBF16>(p0 * d0[r]);
                 dsh[r] = t[0];
                 dsl[r] = t[1];
             }
             {
-                const h2 t = operand<kBF16>(p1 * (d1[r] - dl));
+                const h2 t = operand<kBF16>(p1 * d1[r]);
                 dsh[4 + r] = t[0];
                 dsl[4 + r] = t[1];
             }
@@ -334,7 +349,7 @@ __attribute__((amdgpu_waves_per_eu(BwdWaves<D>::value, 8))) void k_bwd_dkdv(
     constexpr int LS = D + 16;  // operand reads and transposed reads
     __shared__ __attribute__((aligned(16))) _Float16 tQs[NW][32 * LS];
     __shared__ __attribute__((aligned(16))) _Float16 tGs[NW][32 * LS];
-    __shared__ float slses[NW][32], sdels[NW][32];
+    __shared__ __attribute__((aligned(16))) float slses[NW][32], sdels[NW][32];
     // NW waves may share the work item (as in the forward): wave wv takes a
     // contiguous share of its block pairs; the partial dK, dV sums meet in LDS
     const int wv = NW > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
@@ -345,6 +360,8 @@ __attribute__((amdgpu_waves_per_eu(BwdWaves<D>::value, 8))) void k_bwd_dkdv(
 
     const int lane = NW > 1 ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
     const int i = lane & 15, g = lane >> 4;
+    __shared__ mask_words_t mask_table[16];
+    fill_mask_table(mask_table, lane);
     // window-major, or head by head when K and V exceed the caches (as in
     // the forward)
     const int n_gr = gridDim.x / nh;
@@ -386,30 +403,31 @@ __attribute__((amdgpu_waves_per_eu(BwdWaves<D>::value, 8))) void k_bwd_dkdv(
     uint32_t mwa = 0, mwb = 0;
     float lsev = 0.f, delv = 0.f;  // lanes 0..31: of pair slot `lane`
     int ncol = 0;
-    auto load_cols = [&](int b) {
-        const int slot = lane & 31;
-        const int blk = slot < 16 ? min(b, b1 - 1) : min(b + 1, b1 - 1);
-        ncol = cols[(int64_t)kBlockCols * blk + (slot & 15)];
-    };
+    const uint32_t lane_col = 4u * (lane & 31);
+    auto load_cols = [&](int b) { ncol = load_pair_cols(cols, b, b1, lane_col); };
     auto load_pair = [&](int b) {
-        const int c = sanitize_slot(ncol, lane);
+        const int c = pad_cols(ncol);
         gather_pair<D, kWide>(Q, G, c, ld, lane, qst, gst);
         const float2 st = stats[(int64_t)c * H + head];
         lsev = st.x;
         delv = st.y;
-        mwa = mask[(int64_t)kMaskWords * b + (lane >> 3)];
-        mwb = mask[(int64_t)kMaskWords * min(b + 1, b1 - 1) + (lane >> 3)];
+        const uint32_t *mp = mask + (int64_t)kMaskWords * b;
+        mwa = mp[lane >> 3];
+        mwb = mp[(b + 1 < b1 ? kMaskWords : 0) + (lane >> 3)];
     };
-    const int nib_shift = 4 * (lane & 7);
+    const uint32_t nib_rot = mask_nibble_rot(lane);
     auto step = [&](int b, bool prefetch) {
         stage_pair<D>(tQ, LS, lane, qst);
         stage_pair<D>(tG, LS, lane, gst);
         if (lane < 32) {
             slse[lane] = lsev;
-            sdel[lane] = delv;
+            sdel[lane] = -delv;
         }
         tile_fence<NW>();
-        f4 s0 = f4{0.f, 0.f, 0.f, 0.f}, s1 = s0, d0 = s0, d1 = s0;
+        f4 s0 = f4{0.f, 0.f, 0.f, 0.f}, s1 = s0;
+        // dP - delta: the sums start at -delta of their rows
+        f4 d0 = *reinterpret_cast<const f4 *>(sdel + 4 * g);
+        f4 d1 = *reinterpret_cast<const f4 *>(sdel + 16 + 4 * g);
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             const h8 qa = *reinterpret_cast<const h8 *>(&tQ[i * LS + 32 * c + 8 * g]);
@@ -424,25 +442,21 @@ __attribute__((amdgpu_waves_per_eu(BwdWaves<D>::value, 8))) void k_bwd_dkdv(
             d0 = bmma<kBF16>(ga, vw[c], d0);
             d1 = bmma<kBF16>(gb, vw[c], d1);
         }
-        const uint32_t nib0 = (mwa >> nib_shift) & 15u;
-        const uint32_t nib1 = b + 1 < b1 ? (mwb >> nib_shift) & 15u : 0u;
-        f4 l0, l1, e0, e1;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            l0[r] = slse[4 * g + r];
-            l1[r] = slse[16 + 4 * g + r];
-            e0[r] = sdel[4 * g + r];
-            e1[r] = sdel[16 + 4 * g + r];
-        }
+        const uint32_t m0 = mask_entry(mwa, nib_rot, 0xF0u);
+        const uint32_t m1 = mask_entry(mwb, nib_rot, b + 1 < b1 ? 0xF0u : 0u);
+        const f4 l0 = *reinterpret_cast<const f4 *>(slse + 4 * g);
+        const f4 l1 = *reinterpret_cast<const f4 *>(slse + 16 + 4 * g);
         if (prefetch) {
             load_pair(b + 2);
             load_cols(b + 4);
         }
+        const mask_words_t sel0 = mask_words_at(mask_table, m0);
+        const mask_words_t sel1 = mask_words_at(mask_table, m1);
         h8 ph, pl, dsh, dsl;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const float p0 = (nib0 >> r) & 1u ? __builtin_amdgcn_exp2f(s0[r] * sl2 - l0[r]) : 0.f;
-            const float p1 = (nib1 >> r) & 1u ? __builtin_amdgcn_exp2f(s1[r] * sl2 - l1[r]) : 0.f;
+            const float p0 = masked_exp2(s0[r] * sl2 - l0[r], sel0[r]);
+            const float p1 = masked_exp2(s1[r] * sl2 - l1[r], sel1[r]);
             {
                 const h2 t = operand<kBF16>(p0);
                 ph[r] = t[0];
@@ -454,12 +468,12 @@ __attribute__((amdgpu_waves_per_eu(BwdWaves<D>::value, 8))) void k_bwd_dkdv(
                 pl[4 + r] = t[1];
             }
             {
-                const h2 t = operand<kBF16>(p0 * (d0[r] - e0[r]));
+                const h2 t = operand<kBF16>(p0 * d0[r]);
                 dsh[r] = t[0];
                 dsl[r] = t[1];
             }
             {
-                const h2 t = operand<kBF16>(p1 * (d1[r] - e1[r]));
+                const h2 t = operand<kBF16>(p1 * d1[r]);
                 dsh[4 + r] = t[0];
                 dsl[4 + r] = t[1];
             }

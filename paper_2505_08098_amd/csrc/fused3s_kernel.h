@@ -371,9 +371,9 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
     // pair's staging registers are in LDS, in the order in which they are used.
     auto step = [&](int b, bool prefetch) {
         // (an odd tail's absent second block re-read block b: mask it off)
-        const mask_words_t sel0 = mask_words_of(mask_table, mwa, nib_rot, 0xF0u);
-        const mask_words_t sel1 =
-            mask_words_of(mask_table, mwb, nib_rot, b + 1 < b1 ? 0xF0u : 0u);
+        const mask_words_t sel0 = mask_words_at(mask_table, mask_entry(mwa, nib_rot, 0xF0u));
+        const mask_words_t sel1 = mask_words_at(
+            mask_table, mask_entry(mwb, nib_rot, b + 1 < b1 ? 0xF0u : 0u));
         // ---- K rows -> LDS (stride LSK), read back as MFMA A operands ----
         stage_rows(kst, LSK);
         tile_fence<NW>();

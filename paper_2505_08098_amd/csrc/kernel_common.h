@@ -164,18 +164,20 @@ __device__ __forceinline__ void fill_mask_table(mask_words_t *table, int lane)
     }
 }
 // Rotation that moves a lane's nibble of its bitmap word (lane >> 3) to bits
-// 4..7, the byte offset of its table entry, and the entry (sel: 0xF0, or 0
-// for an absent block).
+// 4..7, the byte offset of its table entry; that offset (sel: 0xF0, or 0 for
+// an absent block); and the entry.
 __device__ __forceinline__ uint32_t mask_nibble_rot(int lane)
 {
     return (4u * (lane & 7) + 28u) & 31u;
 }
-__device__ __forceinline__ mask_words_t mask_words_of(const mask_words_t *table, uint32_t word,
-                                                      uint32_t rot, uint32_t sel)
+__device__ __forceinline__ uint32_t mask_entry(uint32_t word, uint32_t rot, uint32_t sel)
 {
-    return *reinterpret_cast<const mask_words_t *>(
-        reinterpret_cast<const char *>(table) +
-        (__builtin_amdgcn_alignbit(word, word, rot) & sel));
+    return __builtin_amdgcn_alignbit(word, word, rot) & sel;
+}
+__device__ __forceinline__ mask_words_t mask_words_at(const mask_words_t *table, uint32_t entry)
+{
+    return *reinterpret_cast<const mask_words_t *>(reinterpret_cast<const char *>(table) +
+                                                   entry);
 }
 // v where sel is all ones, -inf where sel is zero (one bit-select).
 __device__ __forceinline__ float masked_score(float v, uint32_t sel)
