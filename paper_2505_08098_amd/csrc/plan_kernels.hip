@@ -28,7 +28,7 @@
 
 #include "f3s_internal.h"
 
-// Dynamic LDS of k_heavy_lds (declared at global scope: this file is also
+// Dynamic LDS of k_windows_large (declared at global scope: this file is also
 // built as relocatable device code, where a block-scope declaration inside
 // the anonymous namespace would name an undefined internal variable).
 extern __shared__ uint32_t f3s_heavy_lds_dyn[];
