@@ -1039,8 +1039,10 @@ __global__ __launch_bounds__(kPlaceThreads) void k_shape(
         (order == kOrderAuto && uniform_windows(T, total, max_nb));
     const bool sorted = !window_order && piece < kPlaceKeys;
     const int nk = piece + 1;
-    if (sorted)
+    if (sorted) {
         for (int k = lane; k < nk; k += 64) cnt[wv][k] = 0;
+        wave_lds_order();
+    }
     const uint64_t below = (1ull << lane) - 1ull;
     const int nbits = 32 - __clz(piece | 1);
     int rank[E];
@@ -1079,10 +1081,12 @@ __global__ __launch_bounds__(kPlaceThreads) void k_shape(
                 peers &= ((d >> b) & 1) ? bal : ~bal;
             }
             const int r = __popcll(peers & below);
-            // (a wave's LDS accesses take effect in program order: every lane
-            // reads the count before the key's first lane updates it)
+            // every lane reads the count before the key's first lane updates
+            // it, and the next 64 windows read it after that
             const int prior = valid ? cnt[wv][d] : 0;
+            wave_lds_order();
             if (valid && r == 0) cnt[wv][d] = prior + __popcll(peers);
+            wave_lds_order();
             rank[e] = prior + r + (d == 0 ? before : all_pc - all_one);
         }
     }

@@ -183,6 +183,24 @@ def test_plan_shape_paths(gpu, T, deg, hub, order, monkeypatch):
     check_plan(gpu, oracle, rp, ci, N)
 
 
+@pytest.mark.parametrize("T", [64, 65, 1024, 1500, 8192, 16385, 20001])
+def test_ranks_of_windows_with_few_distinct_keys(gpu, T):
+    """Windows of zero to three blocks in any order, some keys absent from
+    whole runs: equal keys within 64 windows, across them and across waves
+    keep their window order, and every window has its item."""
+    from test_gpu_1_plan import _check_plan_against_oracle as check_plan
+    rng = np.random.default_rng(T)
+    N = 16 * T
+    counts = np.zeros(N, dtype=np.int64)
+    counts[::16] = 16 * rng.integers(0, 4, size=T)
+    counts[:16 * (T // 4)] //= 3
+    counts[16 * (T // 2):16 * (T // 2 + 70):16] = 40
+    counts = np.minimum(counts, N)
+    rp = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    ci = np.concatenate([rng.choice(N, size=c, replace=False) for c in counts[counts > 0]])
+    check_plan(gpu, oracle, rp, ci.astype(np.int32), N)
+
+
 def test_plan_with_pieces_beyond_the_one_workgroup_sort(gpu, monkeypatch):
     from test_gpu_1_plan import _check_plan_against_oracle as check_plan
     rng = np.random.default_rng(1)
