@@ -372,10 +372,12 @@ f3s_status_t build_plan(f3s_plan_s *p, const int32_t *row_ptr, const int32_t *co
                                 p->cols, p->mask, shape, hs.placed ? b.pos : nullptr,
                                 placed ? p->items : nullptr, p->merges, s));
     if (!placed)
-        HIP_TRY(launch_worklist(b.key, shape, T, b.radix, p->items, p->merges, st->heavy, s));
+        HIP_TRY(launch_worklist(b.key, shape, T, b.radix, p->items, p->merges, b.pos, st->heavy,
+                                s));
 
     // ---- 6. integrity check of the finished plan ------------------------
-    HIP_TRY(launch_validate_plan(*p, &st->invalid, s));
+    HIP_TRY(launch_validate_plan(*p, shape, hs.placed || !placed ? b.pos : nullptr,
+                                 &st->invalid, s));
     HIP_TRY(hipMemcpy(&hs, st, sizeof hs, hipMemcpyDeviceToHost));
     if (hs.invalid) return F3S_ERR_HIP;
     memcpy(p->heavy, hs.heavy, sizeof p->heavy);

@@ -107,30 +107,64 @@ struct WorkListShape {
     const int32_t *split_idx;  // [T + 1] split windows before w
     int32_t piece, n_pieces, n_split;
 };
+// Items of a window of n blocks, and the k-th of them: the whole window, or
+// piece k of np, which covers the block pairs [floor(k pairs / np),
+// floor((k + 1) pairs / np)).
+__host__ __device__ inline int32_t window_items(const WorkListShape &sh, int32_t n)
+{
+    return n <= sh.piece ? 1 : (n + sh.piece - 1) / sh.piece;
+}
+__host__ __device__ inline WorkItem window_item(const WorkListShape &sh, int32_t w, int32_t b0,
+                                                int32_t n, int32_t k)
+{
+    if (n <= sh.piece) return WorkItem{w, b0, b0 + n, -1};
+    const int32_t np = window_items(sh, n);
+    const int64_t pairs = (n + 1) / 2;
+    const int32_t a = 2 * (int32_t)((k * pairs) / np), b = 2 * (int32_t)(((k + 1) * pairs) / np);
+    return WorkItem{w, b0 + a, b0 + (b < n ? b : n), sh.slot_base[w] + k};
+}
 // Writes window w's items from position pos on, one wavefront's lanes (or a
-// workgroup's threads) sharing the pieces: piece k of np covers the block
-// pairs [floor(k pairs / np), floor((k + 1) pairs / np)).
-__device__ __forceinline__ void place_window(const WorkListShape &sh, int32_t w, int32_t pos,
+// workgroup's threads) sharing the pieces.
+__host__ __device__ inline void place_window(const WorkListShape &sh, int32_t w, int32_t pos,
                                              int tid, int threads, WorkItem *items,
                                              int32_t *merges)
 {
     const int32_t b0 = sh.blk_off[w], n = sh.blk_off[w + 1] - b0;
-    if (n <= sh.piece) {
-        if (tid == 0) items[pos] = WorkItem{w, b0, b0 + n, -1};
-        return;
-    }
-    const int32_t s = sh.split_idx[w], slot = sh.slot_base[w];
-    const int32_t np = (n + sh.piece - 1) / sh.piece;
-    if (tid == 0) {
+    const int32_t np = window_items(sh, n);
+    if (n > sh.piece && tid == 0) {
+        const int32_t s = sh.split_idx[w];
         merges[3 * s + 0] = w;
-        merges[3 * s + 1] = slot;
+        merges[3 * s + 1] = sh.slot_base[w];
         merges[3 * s + 2] = np;
     }
-    const int64_t pairs = (n + 1) / 2;
-    for (int k = tid; k < np; k += threads) {
-        const int a = (int)((k * pairs) / np), b = (int)(((k + 1) * pairs) / np);
-        items[pos + k] = WorkItem{w, b0 + 2 * a, b0 + min(n, 2 * b), slot + k};
-    }
+    for (int32_t k = tid; k < np; k += threads) items[pos + k] = window_item(sh, w, b0, n, k);
+}
+// Whether item t of the list is what place_window put there, window w's items
+// starting at pos[w] (pos null: window order).  An item names its window and
+// its number among the window's items, and these name its position: if all
+// n_items items are in place no two share a window's part, and as there are
+// as many as the windows have parts, each part is in the list exactly once.
+__host__ __device__ inline bool item_in_place(const WorkListShape &sh, const int32_t *pos,
+                                              int32_t T, int32_t t, const WorkItem &it)
+{
+    const int32_t w = it.window;
+    if (w < 0 || w >= T) return false;
+    const int32_t b0 = sh.blk_off[w], n = sh.blk_off[w + 1] - b0, slot = sh.slot_base[w];
+    const int32_t first = pos ? pos[w] : w + slot - sh.split_idx[w];
+    const int32_t k = n > sh.piece ? it.slot - slot : 0;
+    if (k < 0 || k >= window_items(sh, n) || t != first + k) return false;
+    const WorkItem x = window_item(sh, w, b0, n, k);
+    return it.blk_begin == x.blk_begin && it.blk_end == x.blk_end && it.slot == x.slot;
+}
+// The same of merge record s.
+__host__ __device__ inline bool merge_in_place(const WorkListShape &sh, int32_t T, int32_t s,
+                                               const int32_t *merges)
+{
+    const int32_t w = merges[3 * s];
+    if (w < 0 || w >= T) return false;
+    const int32_t n = sh.blk_off[w + 1] - sh.blk_off[w];
+    return n > sh.piece && s == sh.split_idx[w] && merges[3 * s + 1] == sh.slot_base[w] &&
+           merges[3 * s + 2] == window_items(sh, n);
 }
 // Workgroup order flags of the fused kernels: heads outermost (one pass over
 // the work list per head), and consecutive ranges of the order per XCD.
@@ -384,10 +418,11 @@ hipError_t launch_radix_pairs(const int32_t *keys, const int32_t *vals, int32_t 
 // Heavy-first work list from the keys of launch_shape where it did not place
 // the windows itself: the windows stably sorted by key, largest first; whole
 // windows as items, split windows as merge records and their pieces as
-// items.  heavy: the table of heavy items (zeroed).
+// items; pos[w]: window w's first item.  heavy: the table of heavy items
+// (zeroed).
 hipError_t launch_worklist(const int32_t *key, const WorkListShape &shape, int32_t T,
                            const RadixScratch &radix, WorkItem *items, int32_t *merges,
-                           int32_t *heavy, hipStream_t s);
+                           int32_t *pos, int32_t *heavy, hipStream_t s);
 
 // ---- transposed pattern (transpose.hip) ----------------------------------
 // CSR of A^T (rp[N+1], ci[nnz], each row in increasing column order) from a
@@ -406,8 +441,12 @@ hipError_t launch_check_symmetric(const f3s_plan_s &p, int32_t *win, int32_t *as
 hipError_t launch_compare_rows(const f3s_plan_s &p, const int32_t *rpt, const int32_t *cit,
                                int32_t *win, int32_t *pre, int32_t *asym, hipStream_t s);
 
-// Sets *err when a finished plan is internally inconsistent.
-hipError_t launch_validate_plan(const f3s_plan_s &p, int32_t *err, hipStream_t s);
+// Sets *err when a finished plan is internally inconsistent: a block without
+// a first column, a column out of range, a work list that does not hold every
+// part of every window once (the windows' first items: pos, null for window
+// order; shape and pos are the build's scratch).
+hipError_t launch_validate_plan(const f3s_plan_s &p, const WorkListShape &shape,
+                                const int32_t *pos, int32_t *err, hipStream_t s);
 
 // ---- fused operator (fused3s.hip) ---------------------------------------
 // H heads of size d; Q, K, V, O rows hold the heads back to back (stride H*d).

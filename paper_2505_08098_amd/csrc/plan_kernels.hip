@@ -1148,35 +1148,25 @@ __global__ __launch_bounds__(kPlaceThreads) void k_shape(
     }
 }
 
-// Integrity check of a finished plan: every work item lies inside its window's
-// block range, every block's first slot is a real column and every slot is a
-// column or -1, every merge record points at existing partial slots.  Any
-// violation sets err (nothing that the fused kernel reads can then be out of
-// bounds).
-__global__ void k_validate_plan(const int32_t *blk_off, int32_t T, const int32_t *cols,
-                                int64_t n_blocks, const WorkItem *items, int32_t n_items,
-                                const int32_t *merges, int32_t n_split,
-                                int32_t n_pieces, int32_t N, int32_t *err)
+// Integrity check of a finished plan: every item of the work list in its place
+// (so the list holds every block of every window once), every block's first
+// slot a real column and every slot a column or -1, every merge record in its
+// place.  Any violation sets err (nothing that the fused kernel reads can then
+// be out of bounds, and no window is lost).
+__global__ void k_validate_plan(WorkListShape shape, const int32_t *pos, int32_t T,
+                                const int32_t *cols, int64_t n_blocks, const WorkItem *items,
+                                int32_t n_items, const int32_t *merges, int32_t N,
+                                int32_t *err)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     bool bad = false;
-    if (t < n_items) {
-        const WorkItem it = items[t];
-        bad |= it.window < 0 || it.window >= T;
-        if (!bad)
-            bad |= it.blk_begin < blk_off[it.window] || it.blk_end < it.blk_begin ||
-                   it.blk_end > blk_off[it.window + 1];
-        bad |= it.slot < -1 || it.slot >= n_pieces;
-    }
+    if (t < n_items) bad |= !item_in_place(shape, pos, T, (int32_t)t, items[t]);
     if (t < n_blocks) {
         const int32_t *c = cols + kBlockCols * t;
         bad |= c[0] < 0 || c[0] >= N;
         for (int k = 1; k < kBlockCols; ++k) bad |= c[k] < -1 || c[k] >= N;
     }
-    if (t < n_split) {
-        const int w = merges[3 * t], first = merges[3 * t + 1], np = merges[3 * t + 2];
-        bad |= w < 0 || w >= T || first < 0 || np < 1 || first + np > n_pieces;
-    }
+    if (t < shape.n_split) bad |= !merge_in_place(shape, T, (int32_t)t, merges);
     if (bad) atomicOr(err, 1);
 }
 
@@ -1344,17 +1334,18 @@ hipError_t launch_shape(const int32_t *u, const int32_t *bits, int32_t T, int32_
     return launch_scan(nb, blk_off, T, scan_tmp, nullptr, s);
 }
 
-hipError_t launch_validate_plan(const f3s_plan_s &p, int32_t *err, hipStream_t s)
+hipError_t launch_validate_plan(const f3s_plan_s &p, const WorkListShape &shape,
+                                const int32_t *pos, int32_t *err, hipStream_t s)
 {
+    WorkListShape sh = shape;
+    sh.blk_off = p.blk_off;  // the plan's own copy
     int64_t n = p.n_items;
     if (p.n_blocks > n) n = p.n_blocks;
     if (p.n_split > n) n = p.n_split;
     if (n == 0) return hipSuccess;
-    k_validate_plan<<<grid_for(n, 256), 256, 0, s>>>(p.blk_off, p.T, p.cols, p.n_blocks,
-                                                    p.items, p.n_items, p.merges,
-                                                    p.n_split, p.n_pieces, p.N, err);
+    k_validate_plan<<<grid_for(n, 256), 256, 0, s>>>(sh, pos, p.T, p.cols, p.n_blocks, p.items,
+                                                    p.n_items, p.merges, p.N, err);
     return hipGetLastError();
 }
-
 
 }  // namespace f3s

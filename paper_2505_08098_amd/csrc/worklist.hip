@@ -9,13 +9,15 @@ namespace {
 // Window order[i] is i-th in the sorted order; one wavefront per window.
 __global__ __launch_bounds__(256) void k_place_items(const int32_t *order, const int32_t *key,
                                                      int32_t T, WorkListShape shape,
-                                                     WorkItem *items, int32_t *merges)
+                                                     WorkItem *items, int32_t *merges,
+                                                    int32_t *first)
 {
     const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (i >= T) return;
     const int w = order[i];
     const int pos = key[w] == shape.piece ? i + shape.slot_base[w] - shape.split_idx[w]
                                           : i + shape.n_pieces - shape.n_split;
+    if ((threadIdx.x & 63) == 0) first[w] = pos;
     place_window(shape, w, pos, threadIdx.x & 63, 64, items, merges);
 }
 
@@ -44,7 +46,7 @@ __global__ __launch_bounds__(256) void k_heavy_table(const int32_t *key, int32_t
 
 hipError_t launch_worklist(const int32_t *key, const WorkListShape &shape, int32_t T,
                            const RadixScratch &radix, WorkItem *items, int32_t *merges,
-                           int32_t *heavy, hipStream_t s)
+                           int32_t *pos, int32_t *heavy, hipStream_t s)
 {
     if (T == 0) return hipSuccess;
     const int32_t *sorted_keys = nullptr, *order = nullptr;
@@ -52,7 +54,8 @@ hipError_t launch_worklist(const int32_t *key, const WorkListShape &shape, int32
     hipError_t e = launch_radix_pairs(key, nullptr, T, shape.piece, true, radix, &sorted_keys,
                                       &order, s);
     if (e != hipSuccess) return e;
-    k_place_items<<<(unsigned)((T + 3) / 4), 256, 0, s>>>(order, key, T, shape, items, merges);
+    k_place_items<<<(unsigned)((T + 3) / 4), 256, 0, s>>>(order, key, T, shape, items, merges,
+                                                            pos);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const unsigned g = (unsigned)((T + 255) / 256);
     k_heavy_table<<<g < 64 ? g : 64, 256, 0, s>>>(key, T, shape, heavy);
