@@ -23,7 +23,8 @@
 //   softmax  online, base 2, fp32 (Section 3.5): running max m,
 //            running sum l, rescale factor alpha = 2^(m_old - m_new).  A
 //            pair in which no row of the window finds a new maximum skips
-//            the cross-lane maximum, alpha and the rescale of O.  (Skipping
+//            the cross-lane maximum, alpha and the rescale of O (but see
+//            joint_rows).  (Skipping
 //            while the maximum grows by less than 2^8 saved no more time and
 //            cost precision: a row's largest probability is then no longer
 //            1, which rounding keeps exact; relative error 0.9 -> 1.3e-4.
@@ -87,6 +88,22 @@ constexpr int waves_per_simd()
 {
     return WavesPerSimd<D>::value - (kIn == kInBF16 && D == 32 ? 1 : 0) -
            (kNarrow && (D == 64 || D == 96 || D == 160) ? 1 : 0);
+}
+// Whether a pair's K and V rows are loaded chunk by chunk in turn, and its
+// rescale done for every pair: 16-bit rows of 256 bytes and of 384 and more.
+// There the waves wait for the memory system more than for instructions; the
+// two loads of a neighbour's chunk go out back to back, and a loop body
+// without a branch leaves the scheduler free between them.  Measured at
+// d = 128, f16, 4 heads of 48,000 tokens: 479 us, against 527 with K's rows
+// before V's and a rescale only at a new maximum (500 with the loads alone in
+// turn, 515 with the rescale alone); million-node graph 1,266 against 1,272;
+// one head of 48,000 tokens at d = 256: 253 against 268.  It costs up to 2% where
+// a sequence's rows stay in the caches (2 heads of 16,001 tokens, d = 128: 66.0
+// against 65.2), and more with narrower rows or the half-size fp8 ones (fp8,
+// d = 128, 24,000 tokens: 96.8 against 93.2; f16, d = 160: 164.5 against 161.4).
+template <int D, int kIn> constexpr bool joint_rows()
+{
+    return kIn != kInFP8 && (D == 128 || D >= 192);
 }
 // Score product for the input storage type (16-bit operands as raw bits).
 template <int kIn>
@@ -313,37 +330,51 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
         mwa = mp[lane >> 3];
         mwb = mp[(b + 1 < b1 ? kMaskWords : 0) + (lane >> 3)];
     };
+    // This lane's chunk of tile part j of X (K or V), in the row at cj (its byte
+    // offset, or its column).
+    auto load_chunk = [&](const char *X, int cj, int j) {
+        const int f = lane + 64 * j;
+        if constexpr (kNarrow) {
+            // word qd of chunks m0 .. m0+3 (the quad's chunks: LPR is a
+            // multiple of 4, so the quad lies in one row)
+            static_assert(EB == 2, "narrow gathers are defined for 16-bit inputs");
+            typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+            const int m = f % LPR, m0 = m & ~3, qd = m & 3;
+            u4v w;
+#pragma unroll
+            for (int cc = 0; cc < 4; ++cc) {
+                if constexpr (kWide)
+                    w[cc] = *reinterpret_cast<const uint32_t *>(
+                        X + (int64_t)cj * ld * EB + 16 * (m0 + cc) + 4 * qd);
+                else
+                    w[cc] = *reinterpret_cast<const uint32_t *>(
+                        X + ((uint32_t)cj + 16u * (m0 + cc) + 4u * qd));
+            }
+            return __builtin_bit_cast(h8, w);
+        } else if constexpr (kWide) {
+            return *reinterpret_cast<const h8 *>(X + (int64_t)cj * ld * EB + 16 * (f % LPR));
+        } else {
+            // byte offset < 2^32 (checked on the host): the load takes
+            // the uniform base from SGPRs and a 32-bit VGPR offset
+            return load16_off(reinterpret_cast<const _Float16 *>(X),
+                              (uint32_t)cj + 16u * (f % LPR));
+        }
+    };
+    auto chunk_row = [&](int j) {
+        return __builtin_amdgcn_ds_bpermute(4 * ((lane + 64 * j) / LPR), coff);
+    };
     // Issue the loads of the pair's rows of X (K or V).
     auto load_rows = [&](const char *X, h8 *st) {
 #pragma unroll
-        for (int j = 0; j < NI; ++j) {
-            const int f = lane + 64 * j;
-            const int cj = __builtin_amdgcn_ds_bpermute(4 * (f / LPR), coff);
-            if constexpr (kNarrow) {
-                // word qd of chunks m0 .. m0+3 (the quad's chunks: LPR is a
-                // multiple of 4, so the quad lies in one row)
-                static_assert(EB == 2, "narrow gathers are defined for 16-bit inputs");
-                typedef uint32_t u4v __attribute__((ext_vector_type(4)));
-                const int m = f % LPR, m0 = m & ~3, qd = m & 3;
-                u4v w;
+        for (int j = 0; j < NI; ++j) st[j] = load_chunk(X, chunk_row(j), j);
+    };
+    constexpr bool kJoint = joint_rows<D, kIn>();
+    auto load_joint = [&]() {
 #pragma unroll
-                for (int cc = 0; cc < 4; ++cc) {
-                    if constexpr (kWide)
-                        w[cc] = *reinterpret_cast<const uint32_t *>(
-                            X + (int64_t)cj * ld * EB + 16 * (m0 + cc) + 4 * qd);
-                    else
-                        w[cc] = *reinterpret_cast<const uint32_t *>(
-                            X + ((uint32_t)cj + 16u * (m0 + cc) + 4u * qd));
-                }
-                st[j] = __builtin_bit_cast(h8, w);
-            } else if constexpr (kWide) {
-                st[j] = *reinterpret_cast<const h8 *>(X + (int64_t)cj * ld * EB + 16 * (f % LPR));
-            } else {
-                // byte offset < 2^32 (checked on the host): the load takes
-                // the uniform base from SGPRs and a 32-bit VGPR offset
-                st[j] = load16_off(reinterpret_cast<const _Float16 *>(X),
-                                   (uint32_t)cj + 16u * (f % LPR));
-            }
+        for (int j = 0; j < NI; ++j) {
+            const int cj = chunk_row(j);
+            kst[j] = load_chunk(K, cj, j);
+            vst[j] = load_chunk(V, cj, j);
         }
     };
     // The staged rows into the LDS tile with row stride ls.
@@ -397,8 +428,12 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
         if (prefetch) {
             load_masks(b + 2);
             load_cols(b + 4);
-            load_rows(K, kst);
-            load_rows(V, vst);
+            if constexpr (kJoint) {
+                load_joint();
+            } else {
+                load_rows(K, kst);
+                load_rows(V, vst);
+            }
         }
         // ---- mask + online softmax (base 2) ----
         float x[8];
@@ -412,7 +447,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
         for (int e = 1; e < 8; ++e) mloc = fmaxf(mloc, x[e]);
         // (a lane without a new maximum agrees with its row's m_run, which is
         // the row's largest score so far)
-        if (__builtin_amdgcn_ballot_w64(mloc > m_run) != 0) {
+        if (kJoint || __builtin_amdgcn_ballot_w64(mloc > m_run) != 0) {
             const float m_new = fmaxf(m_run, max_xor32(max_xor16(mloc)));
             m_ref = m_new == -__builtin_inff() ? 0.f : m_new;
             const float alpha = __builtin_amdgcn_exp2f(m_run - m_ref);
@@ -478,10 +513,14 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
         load_cols(b0 + 2);
         // loads return in issue order: the loop waits for each group in turn
         // only if they are issued in the same order here
-        __builtin_amdgcn_sched_barrier(0);
-        load_rows(K, kst);
-        __builtin_amdgcn_sched_barrier(0);
-        load_rows(V, vst);
+        if constexpr (kJoint) {
+            load_joint();
+        } else {
+            __builtin_amdgcn_sched_barrier(0);
+            load_rows(K, kst);
+            __builtin_amdgcn_sched_barrier(0);
+            load_rows(V, vst);
+        }
         __builtin_amdgcn_sched_barrier(0);
         // while the loads are under way (a call on 1,021 nodes 4.75 -> 4.63
         // us); read behind the first fence of a step
