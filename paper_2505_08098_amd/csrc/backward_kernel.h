@@ -75,15 +75,17 @@ __device__ __forceinline__ h2 operand(float x)
     }
 }
 
-// Waves per SIMD (d >= 160: one wave, the accumulators spill into AGPRs).
+// Waves per SIMD that the registers of every instance leave room for (d >= 160:
+// one wave, the accumulators spill into AGPRs).
 template <int D> struct BwdWaves { static constexpr int value = 1; };
-template <> struct BwdWaves<32> { static constexpr int value = 4; };
-template <> struct BwdWaves<64> { static constexpr int value = 2; };
+template <> struct BwdWaves<32> { static constexpr int value = 5; };
+template <> struct BwdWaves<64> { static constexpr int value = 3; };
 template <> struct BwdWaves<96> { static constexpr int value = 2; };
 template <> struct BwdWaves<128> { static constexpr int value = 2; };
-// The dQ pass holds fewer registers than the dK/dV pass: at d = 64 it fits
-// four waves per SIMD (128 VGPRs) without spilling.
+// The dQ pass holds fewer registers than the dK/dV pass (d = 32: 80, d = 64:
+// 128).
 template <int D> struct BwdDqWaves { static constexpr int value = BwdWaves<D>::value; };
+template <> struct BwdDqWaves<32> { static constexpr int value = 6; };
 template <> struct BwdDqWaves<64> { static constexpr int value = 4; };
 
 // Row-contiguous gather of the 32 rows (two blocks) of a block pair from two
