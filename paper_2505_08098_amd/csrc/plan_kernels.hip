@@ -883,48 +883,15 @@ __global__ __launch_bounds__(256) void k_fill_windows(
                      threadIdx.x, 256, items, merges);
 }
 
-// Work-list piece size (even).  Pieces cost a partial result of 16 rows
-// through memory and a merge launch (6 to 18 us a call on the hub-heavy
-// graph when the pieces were a quarter of this), so a window stays whole as
-// long as the 4 waves of a workgroup get through it while the launch runs:
-// about 4 n_blocks / slots blocks (slots = 8 per CU), twice a resident wave's
-// even share for each of the 4 waves; at least 64 blocks and 1.5 times the
-// mean window, and 128 for nearly uniform windows (the largest at most twice
-// the mean: all are as long and splitting balances nothing).  Never above the largest window (a larger
-// value splits nothing and only widens the histogram of the work-list sort),
-// nor a little below it.  forced >= 2 overrides the estimate.  Measured
-// against pieces of n_blocks / slots, at least 16, and one wave per item:
-// hub-heavy graph, N = 65,536, d = 64, forward 33.5 -> 29.3 us, 4 bf16 heads
-// forward and backward 421 -> 372 us; sequence of 16,001 tokens, 2 heads of
-// d = 128, forward and backward 303 -> 233 us; ER graph of 10,007 nodes, 16
-// neighbours, 2 heads 56 -> 37 us.
-__device__ int32_t plan_piece(int64_t n_blocks, int32_t max_blocks, int32_t T, int32_t forced,
-                              int32_t slots)
-{
-    const int64_t cap = ((int64_t)(max_blocks > 2 ? max_blocks : 2) + 1) & ~1LL;
-    int64_t piece;
-    if (forced >= 2) {
-        piece = forced & ~1;
-    } else {
-        const bool uniform = (int64_t)max_blocks * T <= 2 * n_blocks;
-        int64_t least = uniform ? 128 : 64;
-        if (2 * least * T < 3 * n_blocks) least = 3 * n_blocks / (2 * (int64_t)T);
-        piece = (4 * n_blocks + slots - 1) / slots;
-        if (piece < least) piece = least;
-        piece = (piece + 1) & ~1LL;
-        if (2 * cap <= 3 * piece) piece = cap;
-    }
-    return (int32_t)(piece < cap ? piece : cap);
-}
-
 // Keys, pieces and split flags per window.
 __global__ __launch_bounds__(256) void k_bin_keys(
     const int32_t *nb, int32_t T, const int32_t *n_blocks, const int32_t *max_blocks,
-    int32_t forced, int32_t slots, int32_t *piece_out, int32_t *key, int32_t *split_pieces,
-    int32_t *split_one)
+    int32_t forced, int32_t slots, bool shared, bool window_order, int32_t *piece_out,
+    int32_t *key, int32_t *split_pieces, int32_t *split_one)
 {
     const int w = blockIdx.x * blockDim.x + threadIdx.x;
-    const int32_t piece = plan_piece(*n_blocks, *max_blocks, T, forced, slots);
+    const int32_t piece =
+        plan_piece(*n_blocks, *max_blocks, T, forced, slots, shared, window_order);
     if (w == 0) *piece_out = piece;
     if (w >= T) return;
     const int n = nb[w];
@@ -950,8 +917,8 @@ constexpr int kPlaceWaves = kPlaceThreads / 64;
 
 template <int E>
 __global__ __launch_bounds__(kPlaceThreads) void k_shape(
-    const int32_t *u, const int32_t *bits, int32_t T, int32_t forced, int32_t slots, int order,
-    BuildStats *st, int32_t *blk_off, int32_t *key, int32_t *slot_base, int32_t *split_idx,
+    const int32_t *u, const int32_t *bits, int32_t T, int32_t forced, int32_t slots, bool shared,
+    int order, BuildStats *st, int32_t *blk_off, int32_t *key, int32_t *slot_base, int32_t *split_idx,
     int32_t *pos)
 {
     __shared__ int32_t cnt[kPlaceWaves][kPlaceKeys];  // [wave][piece - key]
@@ -1003,7 +970,8 @@ __global__ __launch_bounds__(kPlaceThreads) void k_shape(
         total += snb[k];
         max_nb = max(max_nb, smax[k]);
     }
-    const int32_t piece = plan_piece(total, max_nb, T, forced, slots);
+    const int32_t piece =
+        plan_piece(total, max_nb, T, forced, slots, shared, order == kOrderWindow);
     // this wave's pieces of split windows
     int run_pc = 0, run_one = 0, all_pc = 0, all_one = 0;
     if (max_nb > piece) {  // uniform
@@ -1294,17 +1262,17 @@ hipError_t launch_fill_windows(const int32_t *row_ptr, const int32_t *win_row, i
 
 template <int E>
 hipError_t launch_shape_one(const int32_t *u, const int32_t *bits, int32_t T, int32_t forced,
-                            int32_t slots, int order, BuildStats *st, int32_t *blk_off,
-                            int32_t *key, int32_t *slot_base, int32_t *split_idx, int32_t *pos,
-                            hipStream_t s)
+                            int32_t slots, bool shared, int order, BuildStats *st,
+                            int32_t *blk_off, int32_t *key, int32_t *slot_base,
+                            int32_t *split_idx, int32_t *pos, hipStream_t s)
 {
-    k_shape<E><<<1, kPlaceThreads, 0, s>>>(u, bits, T, forced, slots, order, st, blk_off, key,
-                                           slot_base, split_idx, pos);
+    k_shape<E><<<1, kPlaceThreads, 0, s>>>(u, bits, T, forced, slots, shared, order, st, blk_off,
+                                           key, slot_base, split_idx, pos);
     return hipGetLastError();
 }
 
 hipError_t launch_shape(const int32_t *u, const int32_t *bits, int32_t T, int32_t forced,
-                        int32_t slots, int order, BuildStats *st, int32_t *nb,
+                        int32_t slots, bool shared, int order, BuildStats *st, int32_t *nb,
                         int32_t *blk_off, int32_t *key, int32_t *slot_base, int32_t *split_idx,
                         int32_t *pos, int32_t *scan_tmp, hipStream_t s)
 {
@@ -1314,8 +1282,8 @@ hipError_t launch_shape(const int32_t *u, const int32_t *bits, int32_t T, int32_
                    : T <= 8 * kPlaceThreads  ? launch_shape_one<8>
                    : T <= 17 * kPlaceThreads ? launch_shape_one<17>
                                              : launch_shape_one<32>;
-        return one(u, bits, T, forced, slots, order, st, blk_off, key, slot_base, split_idx, pos,
-                   s);
+        return one(u, bits, T, forced, slots, shared, order, st, blk_off, key, slot_base,
+                   split_idx, pos, s);
     }
     const unsigned g = grid_for(T, kStatThreads);
     k_window_stats<<<g < kStatBlocks ? g : kStatBlocks, kStatThreads, 0, s>>>(
@@ -1323,7 +1291,8 @@ hipError_t launch_shape(const int32_t *u, const int32_t *bits, int32_t T, int32_
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     k_bin_keys<<<grid_for(T, 256), 256, 0, s>>>(nb, T, &st->n_blocks, &st->max_blocks, forced,
-                                                slots, &st->piece, key, slot_base, split_idx);
+                                                slots, shared, order == kOrderWindow, &st->piece,
+                                                key, slot_base, split_idx);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     ScanArray sp, so;
     sp.in = sp.out = slot_base;
