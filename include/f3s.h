@@ -87,7 +87,7 @@ typedef struct {
  *   F3S_NO_REORDER=1           work list in window order instead of
  *                              decreasing block count (Section 3.2);
  *                              =0 always sorts.  Unset, plans of nearly
- *                              uniform windows (at least 2048, the largest
+ *                              uniform windows (at least 1280, the largest
  *                              at most twice the mean block count) keep
  *                              window order, which lets the forward and
  *                              backward give each XCD runs of
@@ -194,9 +194,10 @@ f3s_status_t f3s_run(f3s_plan_t plan, const void *Q, const void *K, const void *
  * ranges of one head's work list at a time), window-major otherwise
  * (environment F3S_HEAD_MAJOR_BYTES=<bytes> replaces these tests with a K/V
  * size threshold; results are identical either way).  On nearly
- * uniform plans four waves share each work item when a launch would have
- * fewer waves than the GPU has SIMDs (work items x heads < 1024), and two
- * when twice the waves still fit the GPU at once; on skewed plans four waves
+ * uniform plans four waves share each work item, or two, when a launch would
+ * otherwise have too few waves to hide its loads (work items x heads up to
+ * the GPU's 1024 SIMDs, or 1536) and as many still fit the GPU at once; on
+ * skewed plans four waves
  * share each item that holds more blocks than a resident wave's even share.
  * Sharing waves combine their partial softmax states (environment
  * F3S_WAVES_PER_ITEM=1, 2 or 4 forces one count for all items; the rounding

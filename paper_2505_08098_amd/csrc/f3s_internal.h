@@ -170,13 +170,21 @@ __host__ __device__ inline bool merge_in_place(const WorkListShape &sh, int32_t 
 // the work list per head), and consecutive ranges of the order per XCD.
 constexpr uint32_t kOrderHead = 1u;
 constexpr uint32_t kOrderXcd = 2u;
-// Plans whose windows are nearly uniform: at least 2048 windows, the largest
-// holding at most twice the mean block count.  Their work list keeps window
-// order (heavy-first sorting has nothing to balance), and launches of 1, 2,
-// 4 or 8 heads give each XCD a consecutive range of it.
+// Plans whose windows are nearly uniform: at least kUniformWindows windows,
+// the largest holding at most twice the mean block count.  Their work list
+// keeps window order (heavy-first sorting has nothing to balance, and sets
+// windows that share rows of K and V apart), and launches of 1, 2, 4 or 8 heads
+// give each XCD a consecutive range of it.  Sequences, forward and backward,
+// sorted against window order with ranges: 30,000 tokens (1,875 windows), band
+// 512, 3 heads of 64, 153.6 + 351 against 117.4 + 287 us; 24,000 (1,500), band
+// 256, 2 heads of 128, 105.9 + 252 against 100.3 + 238, 1 head of 64, 30.9 + 75.2
+// against 31.1 + 74.8; 20,000 (1,250) 4 heads of 128, 162 + 404 against 160 +
+// 386, but 1 head of 64, 25.5 + 64.2 against 26.1 + 64.6; below, the ranges
+// cost up to 0.5 us a launch and gain nothing.
+constexpr int64_t kUniformWindows = 1280;
 __host__ __device__ inline bool uniform_windows(int64_t windows, int64_t blocks, int64_t max_blocks)
 {
-    return windows >= 2048 && max_blocks * windows <= 2 * blocks;
+    return windows >= kUniformWindows && max_blocks * windows <= 2 * blocks;
 }
 // Whether a launch of nh > 1 heads over plan p, whose K and V (all heads)
 // hold kv_bytes, runs head by head instead of window-major (item * nh +
@@ -271,16 +279,25 @@ struct WaveSplit {
     int nw;
     int32_t shared;
 };
-// Nearly uniform plans (the largest item at most twice the mean), and plans
-// whose list keeps window order: all items by 4 waves when a launch would
-// have fewer waves than the GPU has SIMDs (items x heads < 1024) and the
-// items average at least 4 blocks; else all by 2 when twice the waves still
-// fit the GPU at once (`resident`: the kernel's waves per SIMD x 1024 SIMDs)
-// and the items average at least 8 blocks (two pairs per wave); else one
-// each.  More waves than fit at once would run as a second round, whose tail
-// and the extra per-wave Q loads and combination cost more than the
-// parallelism gains (4 waves measured 18% slower on the 2048-window sequence
-// workload).
+// Nearly uniform plans (the largest window at most twice the mean item), and
+// plans whose list keeps window order: all items by 4 waves while all of these
+// fit the GPU at once (`resident`: the kernel's waves per SIMD x 1024 SIMDs),
+// there are no more items x heads than SIMDs and the items average at least 4
+// blocks; else all by 2 while these fit, there are at most 1.5 items x heads
+// per SIMD and the items average at least 8 blocks (two pairs per wave); else
+// one each.  More waves than fit at once run as a second round, and more waves
+// than hide the latencies only spread the gathers over more of K and V at a
+// time: windows in flight together walk their columns in step, so whole
+// windows find each other's rows in the caches, halves and quarters of them
+// less.  (Sequences, band 256 + 64 random keys, forward, 1 / 2 / 4 waves:
+// d = 64, 1000 items x heads 23.4, 19.3, 19.3 us, 1500 30.1, 27.7, 27.9, 2000
+// 34.7, 35.2, 36.6; d = 128, 500 28.2, 21.2, 19.1, 1001 43.8, 38.5, 47.7, 1250
+// 53.3, 56.0, 64.2, 1500 55.4, 78.7, 83.8; d = 256, 375 73.1, 47.2, 54.2.)
+// A last round that is nearly empty is not split off: one wave each still beats
+// two waves or half windows as items at 24,000 tokens, 2 heads, d = 128 (3000
+// over 2048, window order: 100, 127, 116 us; backward 238, 318, 298), and at
+// 30,000 tokens, band 512, 3 heads of 64 (5625 over 4096: 117, 170, 131;
+// backward 287, 391, 390).
 // Skewed plans: an item above a resident wave's even share of all blocks
 // would outlast the launch, so 4 waves share it; the lighter ones take one
 // wave each.  (Threshold of the share times 0.75, 1, 1.25, 2 on the hub-heavy
@@ -298,8 +315,9 @@ inline WaveSplit wave_split(const f3s_plan_s &p, int32_t heads, int64_t resident
     if (p.n_items <= 0) return WaveSplit{1, p.n_items};
     if ((p.flags & 1) || (int64_t)p.max_blocks * p.n_items <= 2 * p.n_blocks) {
         const int64_t waves = (int64_t)p.n_items * heads;
-        if (waves < 1024 && p.n_blocks >= 4ll * p.n_items) return WaveSplit{4, p.n_items};
-        if (2 * waves <= resident && p.n_blocks >= 8ll * p.n_items)
+        if (waves <= 1024 && 4 * waves <= resident && p.n_blocks >= 4ll * p.n_items)
+            return WaveSplit{4, p.n_items};
+        if (waves <= 1536 && 2 * waves <= resident && p.n_blocks >= 8ll * p.n_items)
             return WaveSplit{2, p.n_items};
         return WaveSplit{1, p.n_items};
     }

@@ -132,6 +132,72 @@ static int work_list_check()
     return 0;
 }
 
+// Waves per item of a nearly uniform plan of n windows of k blocks.
+static int waves(int32_t n, int32_t k, int32_t heads, int64_t resident)
+{
+    f3s_plan_s p;
+    p.n_items = p.T = n;
+    p.n_blocks = (int64_t)n * k;
+    p.max_blocks = k;
+    const WaveSplit ws = wave_split(p, heads, resident);
+    return ws.shared == n ? ws.nw : -1;
+}
+
+static int wave_rule()
+{
+    for (int64_t per_simd : {1, 2, 3, 4, 6}) {
+        const int64_t resident = 1024 * per_simd;
+        for (int32_t heads : {1, 2, 3, 8}) {
+            int last = 4;
+            for (int32_t n = 1; n * heads < 9000; n += 1 + n / 50) {
+                const int nw = waves(n, 80, heads, resident);
+                // the launch's waves fit at once, or nothing is shared; never
+                // more waves an item for a larger launch
+                CHECK(nw == 1 || (int64_t)nw * n * heads <= resident);
+                CHECK(nw >= 1 && nw <= last);
+                last = nw;
+                // and no SIMD is left without a wave that could have one
+                if (2ll * n * heads <= (resident < 2048 ? resident : 2048)) CHECK(nw >= 2);
+                if (4ll * n * heads <= 1024) CHECK(nw == 4);
+            }
+        }
+    }
+    // one head of 16,001 tokens at d = 128: four waves a window were two rounds
+    CHECK(waves(1001, 81, 1, 2048) == 2);
+    CHECK(waves(375, 73, 1, 1024) == 2);
+    CHECK(waves(500, 60, 1, 2048) == 4);
+    // thin windows stay whole, more than one round too
+    CHECK(waves(1000, 3, 1, 4096) == 1 && waves(1000, 7, 1, 2048) == 1);
+    CHECK(waves(3000, 80, 1, 2048) == 1 && waves(1689, 24, 1, 4096) == 1);
+    f3s_plan_s none;
+    CHECK(wave_split(none, 4, 2048).nw == 1);
+    // skewed: the items above a resident wave's share, by four waves
+    f3s_plan_s p;
+    p.n_items = p.T = 4207;
+    p.n_blocks = 67341;
+    p.max_blocks = 1465;
+    for (int j = 0; j < kHeavySteps; ++j) p.heavy[j] = heavy_blocks(j) < 132 ? 161 + kHeavySteps - j : 0;
+    const WaveSplit one = wave_split(p, 1, 4096), many = wave_split(p, 8, 2048);
+    CHECK(one.nw == 4 && one.shared > 161 && wave_groups(one, p.n_items) >= 1052);
+    CHECK(many.nw == 1);
+    printf("waves per item\n");
+    return 0;
+}
+
+// Window order from 1,280 nearly uniform windows on.
+static int order_rule()
+{
+    CHECK(uniform_windows(1500, 1500 * 80, 81) && uniform_windows(1280, 2560, 4));
+    CHECK(!uniform_windows(1279, 1279 * 80, 81) && !uniform_windows(1500, 3000, 5));
+    f3s_plan_s p;
+    p.n_items = 1875;
+    p.n_blocks = 1875 * 95;
+    p.max_blocks = 96;
+    CHECK(head_major_order(p, 3, 23 << 20) && xcd_chunks(p, 3, true) && xcd_chunks(p, 1));
+    printf("window order\n");
+    return 0;
+}
+
 static int piece_rule()
 {
     const int32_t slots = 2048;
@@ -162,7 +228,7 @@ static int piece_rule()
 
 int main()
 {
-    if (work_list_check() || piece_rule()) return 1;
+    if (work_list_check() || wave_rule() || order_rule() || piece_rule()) return 1;
     printf("ok\n");
     return 0;
 }

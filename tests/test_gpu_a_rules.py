@@ -162,6 +162,66 @@ def test_uniform_windows_stay_whole(gpu):
                oracle.attention_f64(rp, ci, Q, K, V, 0.125))
 
 
+@pytest.mark.parametrize("N,H,d,dtype", [(20479, 1, 64, "f16"), (20465, 3, 32, "f16"),
+                                         (1280 * 16 + 1, 3, 32, "bf16"),
+                                         (24000, 2, 128, "f16"), (8000, 2, 64, "bf16"),
+                                         (12300, 2, 256, "f16"), (12100, 1, 32, "f16")])
+def test_sequences_around_the_wave_and_order_rules(gpu, N, H, d, dtype):
+    """Uniform windows around 1,280 of them (window order), and launches whose
+    waves are about one per SIMD, one and a half, or leave their last round
+    nearly empty: forward and gradients against the fp64 oracle."""
+    rng = np.random.default_rng(N + d)
+    far = rng.integers(0, N, size=(N, 6))
+    band = np.arange(N)[:, None] + np.arange(-60, 60)
+    rows = np.sort(np.concatenate([np.clip(band, 0, N - 1), far], 1), 1)
+    keep = np.ones(rows.shape, dtype=bool)
+    keep[:, 1:] = rows[:, 1:] != rows[:, :-1]
+    rp = np.concatenate([[0], np.cumsum(keep.sum(1))]).astype(np.int32)
+    ci = rows[keep].astype(np.int32)
+    t = torch.float16 if dtype == "f16" else torch.bfloat16
+    Q, K, V, G = (torch.from_numpy(rng.standard_normal((N, H, d)).astype(np.float32)).to(t)
+                  for _ in range(4))
+    q, k, v, g = (x.cuda() for x in (Q, K, V, G))
+    plan = gpu.Plan(_dev(rp), _dev(ci), N)
+    plan_t = plan.transpose()
+    assert plan.info["n_split"] == 0
+    assert bool(plan.info["flags"] & 1) == ((N + 15) // 16 >= 1280)
+    O, lse = gpu.forward_typed(plan, q, k, v, scale=0.1, want_lse=True)
+    grads = gpu.backward(plan, plan_t, q, k, v, O, g, lse, scale=0.1)
+    h = H - 1
+    qh, kh, vh, gh = (x[:, h].float().double().cuda() for x in (Q, K, V, G))
+    want = _attention_f64(rp, ci, qh, kh, vh, gh, 0.1)
+    for got, ref in zip((O, lse) + grads, want):
+        ref = ref.cpu().numpy()
+        bar = REL if dtype == "f16" else 2e-5  # two bf16 terms: 2^-17 each
+        got = got[:, h].double().cpu().numpy()
+        assert np.linalg.norm(got - ref) <= bar * np.linalg.norm(ref)
+
+
+def _attention_f64(rp, ci, q, k, v, g, scale):
+    """O, lse, dQ, dK, dV of one head, entry by entry in fp64."""
+    N, d = q.shape
+    dev = q.device
+    rows = torch.repeat_interleave(torch.arange(N, device=dev),
+                                   torch.from_numpy(np.diff(rp)).to(dev))
+    cols = torch.from_numpy(ci).to(dev).long()
+
+    def spread(to, w, X):
+        return torch.zeros((N, d), dtype=torch.float64, device=dev).index_add_(
+            0, to, X * w[:, None])
+
+    x = (q[rows] * k[cols]).sum(1) * scale
+    top = torch.full((N,), -float("inf"), dtype=torch.float64, device=dev)
+    top = top.scatter_reduce(0, rows, x, "amax")
+    p = torch.exp(x - top[rows])
+    total = torch.zeros(N, dtype=torch.float64, device=dev).index_add_(0, rows, p)
+    p = p / total[rows]
+    O = spread(rows, p, v[cols])
+    ds = p * ((g[rows] * v[cols]).sum(1) - (g * O).sum(1)[rows]) * scale
+    return (O, top + torch.log(total), spread(rows, ds, k[cols]), spread(cols, ds, q[rows]),
+            spread(cols, p, g[rows]))
+
+
 # windows on either side of what one workgroup shapes and sorts (1,024,
 # 4,096, 8,192, 17,408 and 32,768 windows), of the digits the one-workgroup
 # sort covers (pieces of 2,048 blocks), and of the per-window paths (64, 128,
