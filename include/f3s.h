@@ -197,8 +197,8 @@ f3s_status_t f3s_run(f3s_plan_t plan, const void *Q, const void *K, const void *
  * uniform plans four waves share each work item, or two, when a launch would
  * otherwise have too few waves to hide its loads (work items x heads up to
  * the GPU's 1024 SIMDs, or 1536) and as many still fit the GPU at once; on
- * skewed plans four waves
- * share each item that holds more blocks than a resident wave's even share.
+ * skewed plans four waves share each of the heaviest items, as many as
+ * would outlast the launch.
  * Sharing waves combine their partial softmax states (environment
  * F3S_WAVES_PER_ITEM=1, 2 or 4 forces one count for all items; the rounding
  * of the combination differs).

@@ -298,12 +298,19 @@ struct WaveSplit {
 // over 2048, window order: 100, 127, 116 us; backward 238, 318, 298), and at
 // 30,000 tokens, band 512, 3 heads of 64 (5625 over 4096: 117, 170, 131;
 // backward 287, 391, 390).
-// Skewed plans: an item above a resident wave's even share of all blocks
-// would outlast the launch, so 4 waves share it; the lighter ones take one
-// wave each.  (Threshold of the share times 0.75, 1, 1.25, 2 on the hub-heavy
-// graph of 65,536 nodes at d = 64: 31.2, 29.5, 30.0, 33.3 us with one head;
-// on a 200,000-node one of exponent 2.2, forward and backward: 307, 306, 313,
-// 332 us.)
+// Skewed plans: 4 waves share the heavy items, the lighter ones take one wave
+// each.  Left to one wave, items of up to T blocks outlast the launch by about T
+// less a resident wave's even share of all blocks; shared, each costs three
+// more waves' start, Q rows and combination, which the whole GPU pays: 16 items
+// (times heads) cost as much as one block that a lone wave is left with.  T is
+// the table's step with the least sum of both (or nothing is shared).  The 16
+// was fitted, from 12 to 18, to 36 Chung-Lu graphs of 10,000 to 262,147 nodes, 1
+// to 4 heads, d = 32 to 256, forward and backward at ten fixed T each: 1.8% above
+// the best T on average, where T = the even share alone was 7.5% above it and
+// up to 45%: nearly everything was shared where the mean item exceeded the
+// share.  (40,000 nodes, exponent 2.6, d = 64, forward + backward, T = 10, the
+// share: 24.5 + 68.8 us; 28: 19.7 + 48.2; 56: 26.9 + 65.3.  65,536 nodes,
+// exponent 2.1: 14: 25.5 + 69.3, 20: 25.9 + 66.6, 40: 28.7 + 71.9.)
 // F3S_WAVES_PER_ITEM=1, 2 or 4 forces one count for all items (read at launch).
 inline WaveSplit wave_split(const f3s_plan_s &p, int32_t heads, int64_t resident)
 {
@@ -322,10 +329,18 @@ inline WaveSplit wave_split(const f3s_plan_s &p, int32_t heads, int64_t resident
         return WaveSplit{1, p.n_items};
     }
     const int64_t share = p.n_blocks * heads / resident;
-    int j = 0;
-    while (j < kHeavySteps && heavy_blocks(j) < share) ++j;
-    if (j < kHeavySteps && p.heavy[j] > 0) return WaveSplit{4, p.heavy[j]};
-    return WaveSplit{1, p.n_items};
+    const int32_t largest = p.max_blocks < p.piece ? p.max_blocks : p.piece;
+    int64_t least = largest > share ? 16 * (largest - share) : 0;
+    int32_t shared = 0;
+    for (int j = 0; j < kHeavySteps && heavy_blocks(j) < largest; ++j) {
+        const int32_t t = heavy_blocks(j);
+        const int64_t cost = (t > share ? 16 * (t - share) : 0) + (int64_t)p.heavy[j] * heads;
+        if (cost < least) {
+            least = cost;
+            shared = p.heavy[j];
+        }
+    }
+    return shared > 0 ? WaveSplit{4, shared} : WaveSplit{1, p.n_items};
 }
 // Workgroups per head of such a launch.
 inline int64_t wave_groups(const WaveSplit &ws, int32_t n_items)

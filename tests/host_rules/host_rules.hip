@@ -171,16 +171,56 @@ static int wave_rule()
     CHECK(waves(3000, 80, 1, 2048) == 1 && waves(1689, 24, 1, 4096) == 1);
     f3s_plan_s none;
     CHECK(wave_split(none, 4, 2048).nw == 1);
-    // skewed: the items above a resident wave's share, by four waves
-    f3s_plan_s p;
-    p.n_items = p.T = 4207;
-    p.n_blocks = 67341;
-    p.max_blocks = 1465;
-    for (int j = 0; j < kHeavySteps; ++j) p.heavy[j] = heavy_blocks(j) < 132 ? 161 + kHeavySteps - j : 0;
-    const WaveSplit one = wave_split(p, 1, 4096), many = wave_split(p, 8, 2048);
-    CHECK(one.nw == 4 && one.shared > 161 && wave_groups(one, p.n_items) >= 1052);
-    CHECK(many.nw == 1);
     printf("waves per item\n");
+    return 0;
+}
+
+// A skewed plan from its items' block counts.
+static f3s_plan_s skewed(const std::vector<int32_t> &size, int32_t piece)
+{
+    f3s_plan_s p;
+    p.n_items = p.T = (int32_t)size.size();
+    p.piece = piece;
+    for (int32_t n : size) {
+        p.n_blocks += n;
+        p.max_blocks = std::max(p.max_blocks, n);
+        for (int j = 0; j < kHeavySteps; ++j) p.heavy[j] += n > heavy_blocks(j);
+    }
+    return p;
+}
+
+// On skewed plans four waves share the few heaviest items: those whose one
+// wave would outlast the launch, never the bulk of them, and none where every
+// wave has more than the largest item to do anyway.
+static int heavy_rule()
+{
+    // 2,500 items of about 17 blocks, some of up to 84 (40,000 nodes, exponent
+    // 2.6): the even share of 4,096 waves, 10, is below nearly all of them
+    std::vector<int32_t> size;
+    for (int i = 0; i < 2500; ++i)
+        size.push_back(i < 28 ? 60 : i < 54 ? 48 : i < 119 ? 33 : i < 402 ? 24 : i < 1365 ? 17 : 13);
+    const f3s_plan_s mild = skewed(size, 84);
+    const WaveSplit a = wave_split(mild, 1, 4096);
+    CHECK(a.nw == 4 && a.shared >= 54 && a.shared <= 402);
+    CHECK(wave_groups(a, 2500) == a.shared + (2500 - a.shared + 3) / 4);
+    // hubs: 4,200 items of mean 13, up to 106
+    size.clear();
+    for (int i = 0; i < 4200; ++i)
+        size.push_back(i < 49 ? 106 : i < 222 ? 70 : i < 384 ? 40 : i < 751 ? 20 : 7);
+    const f3s_plan_s hubs = skewed(size, 106);
+    const WaveSplit b = wave_split(hubs, 1, 4096), c = wave_split(hubs, 4, 4096);
+    CHECK(b.nw == 4 && b.shared >= 222 && b.shared <= 751);
+    CHECK(c.nw == 1 || c.shared <= b.shared);  // more heads: nothing more to share
+    CHECK(wave_split(hubs, 64, 4096).nw == 1);
+    // the items shared are a prefix of whole levels, at most all
+    for (int32_t heads : {1, 2, 3, 8})
+        for (int64_t resident : {1024, 2048, 3072, 4096, 6144})
+            for (const f3s_plan_s *p : {&mild, &hubs}) {
+                const WaveSplit ws = wave_split(*p, heads, resident);
+                CHECK(ws.nw == 1 ? ws.shared == p->n_items
+                                 : ws.nw == 4 && ws.shared > 0 && ws.shared < p->n_items);
+            }
+    printf("heavy items\n");
     return 0;
 }
 
@@ -228,7 +268,7 @@ static int piece_rule()
 
 int main()
 {
-    if (work_list_check() || wave_rule() || order_rule() || piece_rule()) return 1;
+    if (work_list_check() || wave_rule() || heavy_rule() || order_rule() || piece_rule()) return 1;
     printf("ok\n");
     return 0;
 }
