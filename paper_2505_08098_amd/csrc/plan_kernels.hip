@@ -902,52 +902,61 @@ __global__ __launch_bounds__(256) void k_bin_keys(
 }
 
 // All of launch_shape by one workgroup, for up to kOnePlace windows: wave v
-// owns the windows [v 64 E, (v + 1) 64 E), 64 at a time (coalesced), so each
-// prefix costs one barrier over the wave totals and the block counts stay in
-// registers.  Then the stable sort: each wave ranks its windows in order, a
-// window's rank among the equal keys of its 64 from ballots, added to the
-// wave's running count of that key (16 waves x kPlaceKeys counts in LDS), and
-// a scan over (key descending, wave) gives each wave its first rank of each
-// key.  Bound by the latency of its steps; it replaces eight launches
+// owns the windows [64 v steps, 64 (v + 1) steps), 64 at a time (coalesced), so
+// each prefix costs one barrier over the wave totals.  Then the stable sort:
+// each wave ranks its windows in order, a window's rank among the equal keys
+// of its 64 from ballots, added to the wave's running count of that key (16
+// waves x kPlaceKeys counts in LDS), and a scan over (key descending, wave)
+// gives each wave its first rank of each key.  It replaces eight launches
 // (statistics, keys, two scans, digit count, scan, scatter, placement).
+// Bound by the latency of its steps, which are many for a few waves: the block
+// counts stay in LDS (16 bits each: with at most kOnePlace windows a window has
+// at most kOnePlace blocks, and counts and first ranks are at most kOnePlace
+// too), and four steps' loads and ballots overlap.  8.5 us up to 1,024 windows,
+// 10.0 at 1,920, 18.7 at 7,676, 31.6 at 16,385, 32.8 at 17,409, 52 at 32,768.  (The
+// counts in registers, the steps unrolled in instances of 1, 4, 8, 17 and 32 of
+// them, the longest 10,700 instructions: 7.6, 11.7, 17.0, 27.5, 46.7, 54 us.)
 constexpr int kOnePlace = 32768;
 constexpr int kPlaceKeys = 2048;
 constexpr int kPlaceThreads = 1024;
 constexpr int kPlaceWaves = kPlaceThreads / 64;
 
-template <int E>
 __global__ __launch_bounds__(kPlaceThreads) void k_shape(
-    const int32_t *u, const int32_t *bits, int32_t T, int32_t forced, int32_t slots, bool shared,
-    int order, BuildStats *st, int32_t *blk_off, int32_t *key, int32_t *slot_base, int32_t *split_idx,
-    int32_t *pos)
+    const int32_t *__restrict__ u, const int32_t *__restrict__ bits, int32_t T, int steps,
+    int32_t forced, int32_t slots, bool shared, int order, BuildStats *st, int32_t *blk_off,
+    int32_t *key, int32_t *slot_base, int32_t *split_idx, int32_t *pos)
 {
-    __shared__ int32_t cnt[kPlaceWaves][kPlaceKeys];  // [wave][piece - key]
+    __shared__ uint16_t cnt[kPlaceWaves][kPlaceKeys];  // [wave][piece - key]
+    __shared__ uint16_t blocks[kOnePlace];             // each lane reads what it wrote
     __shared__ unsigned long long ssum[2][kPlaceWaves];
     __shared__ int32_t snb[kPlaceWaves], smax[kPlaceWaves], spc[kPlaceWaves], sone[kPlaceWaves];
     __shared__ int32_t hist[kHeavySteps + 1];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (st->err) return;  // u and bits may not be set
-    const int w0 = wv * 64 * E + lane;
-    int nb[E];
+    const int w0 = wv * 64 * steps + lane;
+    constexpr int U = 4;
+    // f(step) for every step, U of them unrolled together
+    auto each_step = [&](auto f) {
+        int e = 0;
+        for (; e + U <= steps; e += U) {
+#pragma unroll
+            for (int k = 0; k < U; ++k) f(e + k);
+        }
+        for (; e < steps; ++e) f(e);
+    };
     unsigned long long su = 0, sb = 0;
     int sn = 0, mx = 0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
+    each_step([&](int e) {
         const int w = w0 + 64 * e;
-        nb[e] = w < T ? u[w] : 0;
-    }
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int w = w0 + 64 * e;
+        const int uw = w < T ? u[w] : 0;
         sb += (unsigned long long)(w < T ? bits[w] : 0);
-    }
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        su += (unsigned long long)nb[e];
-        nb[e] = (nb[e] + kBlockCols - 1) / kBlockCols;
-        sn += nb[e];
-        mx = max(mx, nb[e]);
-    }
+        const int n = (uw + kBlockCols - 1) / kBlockCols;
+        blocks[w] = (uint16_t)n;
+        su += (unsigned long long)uw;
+        sn += n;
+        mx = max(mx, n);
+    });
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         su += __shfl_xor(su, o);
@@ -976,12 +985,13 @@ __global__ __launch_bounds__(kPlaceThreads) void k_shape(
     int run_pc = 0, run_one = 0, all_pc = 0, all_one = 0;
     if (max_nb > piece) {  // uniform
         int pc = 0, one = 0;
-#pragma unroll
-        for (int e = 0; e < E; ++e)
-            if (nb[e] > piece) {
-                pc += (nb[e] + piece - 1) / piece;
+        each_step([&](int e) {
+            const int n = blocks[w0 + 64 * e];
+            if (n > piece) {
+                pc += (n + piece - 1) / piece;
                 ++one;
             }
+        });
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
             pc += __shfl_xor(pc, o);
@@ -1013,34 +1023,33 @@ __global__ __launch_bounds__(kPlaceThreads) void k_shape(
     }
     const uint64_t below = (1ull << lane) - 1ull;
     const int nbits = 32 - __clz(piece | 1);
-    int rank[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
+    each_step([&](int e) {
         const int w = w0 + 64 * e;
-        const int n = nb[e];
+        const int n = blocks[w];
         const bool split = n > piece, valid = w < T;
-        const int np = split ? (n + piece - 1) / piece : 0;
         const int incl = wave_inclusive_sum(n, lane);
-        int ipc = 0, ione = 0;
-        if (all_one) {  // uniform
-            ipc = wave_inclusive_sum(np, lane);
-            ione = wave_inclusive_sum(split ? 1 : 0, lane);
+        // pieces and number of the split windows before w
+        const uint64_t splits = __ballot(split);
+        int pieces = run_pc, number = run_one;
+        if (splits) {  // few steps have any
+            const int np = split ? (n + piece - 1) / piece : 0;
+            const int ipc = wave_inclusive_sum(np, lane);
+            pieces += ipc - np;
+            number += __popcll(splits & below);
+            run_pc += __builtin_amdgcn_readlane(ipc, 63);
+            run_one += __popcll(splits);
         }
-        // items of the split windows before w, less one for each
-        const int before = run_pc + ipc - np - (run_one + ione - (split ? 1 : 0));
+        const int before = pieces - number;  // their items, less one for each
         if (valid) {
             blk_off[w] = run_nb + incl - n;
-            slot_base[w] = run_pc + ipc - np;
-            split_idx[w] = run_one + ione - (split ? 1 : 0);
+            slot_base[w] = pieces;
+            split_idx[w] = number;
             if (!sorted) {
                 key[w] = split ? piece : n;
                 pos[w] = w + before;
             }
         }
         run_nb += __builtin_amdgcn_readlane(incl, 63);
-        run_pc += __builtin_amdgcn_readlane(ipc, 63);
-        run_one += __builtin_amdgcn_readlane(ione, 63);
-        rank[e] = 0;
         if (sorted) {
             const int d = max(piece - n, 0);
             uint64_t peers = __ballot(valid);
@@ -1049,15 +1058,16 @@ __global__ __launch_bounds__(kPlaceThreads) void k_shape(
                 peers &= ((d >> b) & 1) ? bal : ~bal;
             }
             const int r = __popcll(peers & below);
-            // every lane reads the count before the key's first lane updates
-            // it, and the next 64 windows read it after that
+            // every lane reads the count before the key's first lane
+            // updates it, and the next 64 windows read it after that
             const int prior = valid ? cnt[wv][d] : 0;
             wave_lds_order();
-            if (valid && r == 0) cnt[wv][d] = prior + __popcll(peers);
+            if (valid && r == 0) cnt[wv][d] = (uint16_t)(prior + __popcll(peers));
             wave_lds_order();
-            rank[e] = prior + r + (d == 0 ? before : all_pc - all_one);
+            // the rank within the wave's windows of the key, for now
+            if (valid) pos[w] = prior + r + (d == 0 ? before : all_pc - all_one);
         }
-    }
+    });
     __syncthreads();
     if (sorted) {
         // first rank of each key and wave: a scan over the keys, two per
@@ -1081,14 +1091,26 @@ __global__ __launch_bounds__(kPlaceThreads) void k_shape(
             if (2 * tid + j < nk)
                 for (int v = 0; v < kPlaceWaves; ++v) {
                     const int c = cnt[v][2 * tid + j];
-                    cnt[v][2 * tid + j] = first;
+                    cnt[v][2 * tid + j] = (uint16_t)first;
                     first += c;
                 }
         __syncthreads();
+        int rank[U], e = 0;
+        for (; e + U <= steps; e += U) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
+            for (int k = 0; k < U; ++k) {
+                const int w = w0 + 64 * (e + k);
+                rank[k] = w < T ? pos[w] : 0;
+            }
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int w = w0 + 64 * (e + k);
+                if (w < T) pos[w] = cnt[wv][max(piece - blocks[w], 0)] + rank[k];
+            }
+        }
+        for (; e < steps; ++e) {
             const int w = w0 + 64 * e;
-            if (w < T) pos[w] = cnt[wv][max(piece - nb[e], 0)] + rank[e];
+            if (w < T) pos[w] += cnt[wv][max(piece - blocks[w], 0)];
         }
         if (tid < kHeavySteps) {
             int h = 0;
@@ -1260,30 +1282,16 @@ hipError_t launch_fill_windows(const int32_t *row_ptr, const int32_t *win_row, i
     return hipGetLastError();
 }
 
-template <int E>
-hipError_t launch_shape_one(const int32_t *u, const int32_t *bits, int32_t T, int32_t forced,
-                            int32_t slots, bool shared, int order, BuildStats *st,
-                            int32_t *blk_off, int32_t *key, int32_t *slot_base,
-                            int32_t *split_idx, int32_t *pos, hipStream_t s)
-{
-    k_shape<E><<<1, kPlaceThreads, 0, s>>>(u, bits, T, forced, slots, shared, order, st, blk_off,
-                                           key, slot_base, split_idx, pos);
-    return hipGetLastError();
-}
-
 hipError_t launch_shape(const int32_t *u, const int32_t *bits, int32_t T, int32_t forced,
                         int32_t slots, bool shared, int order, BuildStats *st, int32_t *nb,
                         int32_t *blk_off, int32_t *key, int32_t *slot_base, int32_t *split_idx,
                         int32_t *pos, int32_t *scan_tmp, hipStream_t s)
 {
     if (T <= kOnePlace) {
-        auto one = T <= kPlaceThreads        ? launch_shape_one<1>
-                   : T <= 4 * kPlaceThreads  ? launch_shape_one<4>
-                   : T <= 8 * kPlaceThreads  ? launch_shape_one<8>
-                   : T <= 17 * kPlaceThreads ? launch_shape_one<17>
-                                             : launch_shape_one<32>;
-        return one(u, bits, T, forced, slots, shared, order, st, blk_off, key, slot_base,
-                   split_idx, pos, s);
+        const int steps = (T + kPlaceThreads - 1) / kPlaceThreads;
+        k_shape<<<1, kPlaceThreads, 0, s>>>(u, bits, T, steps, forced, slots, shared, order, st,
+                                            blk_off, key, slot_base, split_idx, pos);
+        return hipGetLastError();
     }
     const unsigned g = grid_for(T, kStatThreads);
     k_window_stats<<<g < kStatBlocks ? g : kStatBlocks, kStatThreads, 0, s>>>(
