@@ -97,7 +97,7 @@ __device__ __forceinline__ void gather_pair(const _Float16 *A, const _Float16 *B
                                             int ld, int lane, h8 *sa, h8 *sb)
 {
     constexpr int LPR = D / 8, NI = D / 16;
-    const int coff = kWide ? c : c * (2 * ld);  // the slot's byte offset (kWide: row id)
+    const int coff = kWide ? c : row_offset(c, 2 * ld);  // the slot's byte offset (kWide: row id)
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
         const int f = lane + 64 * j;

@@ -357,6 +357,12 @@ __device__ __forceinline__ bool wave_item(int g, int wv, int32_t shared_items, i
     *item = *shared ? g : shared_items + (g - shared_items) * NW + wv;
     return *item < n_items;
 }
+// Byte offset of a row of row_bytes bytes in a table of less than 4 GiB, as 32
+// bits (the products are unsigned: offsets of 2 GiB and more use the top bit).
+__host__ __device__ inline int32_t row_offset(int32_t row, int32_t row_bytes)
+{
+    return (int32_t)((uint32_t)row * (uint32_t)row_bytes);
+}
 // First row and row count of window w: rows 16 w .. 16 w + 15 (the last
 // window clipped at N), or those given by win_row (device code).
 __device__ __forceinline__ void window_rows(const int32_t *win_row, int32_t N, int32_t w,

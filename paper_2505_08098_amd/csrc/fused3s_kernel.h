@@ -325,7 +325,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
     // Bitmaps of pair (b, b+1); takes over the columns loaded for it.
     auto load_masks = [&](int b) {
         const int c = pad_cols(ncol);
-        coff = kWide ? c : c * (EB * ld);
+        coff = kWide ? c : row_offset(c, EB * ld);
         const uint32_t *mp = mask + (int64_t)kMaskWords * b;
         mwa = mp[lane >> 3];
         mwb = mp[(b + 1 < b1 ? kMaskWords : 0) + (lane >> 3)];

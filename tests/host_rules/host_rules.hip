@@ -266,9 +266,23 @@ static int piece_rule()
     return 0;
 }
 
+// Offsets up to 4 GiB without overflow (the run checks for undefined
+// behaviour), equal to the 64-bit product's low half.
+static int offset_rule()
+{
+    for (int32_t bytes : {64, 256, 512, 56320})
+        for (uint64_t off = 0; off < 0xFFFFFFF0ull; off += 0x0FFFFFF7ull) {
+            const int32_t row = (int32_t)(off / bytes);
+            CHECK((uint32_t)row_offset(row, bytes) == (uint32_t)((uint64_t)row * bytes));
+        }
+    CHECK((uint32_t)row_offset(16777214, 256) == 16777214u * 256u);
+    printf("row offsets\n");
+    return 0;
+}
+
 int main()
 {
-    if (work_list_check() || wave_rule() || heavy_rule() || order_rule() || piece_rule()) return 1;
+    if (offset_rule() || work_list_check() || wave_rule() || heavy_rule() || order_rule() || piece_rule()) return 1;
     printf("ok\n");
     return 0;
 }

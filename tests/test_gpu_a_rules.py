@@ -342,3 +342,59 @@ def test_symmetric_plans_share_their_arrays(gpu):
         plan.close()
         assert left.export()["cols"].min() >= -1
         left.close()
+
+
+@pytest.mark.parametrize("N,H,d,dtype", [(9_000_000, 1, 128, "f16"), (16_777_213, 1, 128, "bf16"),
+                                         (50_000, 88, 256, "f16")])
+def test_rows_between_2_and_4_gib(gpu, N, H, d, dtype):
+    """32-bit row offsets with the top bit set: a few rows attend to keys all
+    over Q, K and V of 2.1 to 4 GiB each; outputs and gradients of these rows
+    and keys against fp64, everything else zero."""
+    t = torch.float16 if dtype == "f16" else torch.bfloat16
+    size = 2 * N * H * d
+    assert 2**31 < size <= 0xFFFFFFF0
+    if torch.cuda.mem_get_info()[0] < 14 * size:
+        pytest.skip("not enough device memory")
+    rng = np.random.default_rng(N)
+    rows = np.unique(np.concatenate([rng.integers(0, N, size=60), [0, N - 1, N // 2]]))
+    cols = [np.unique(np.concatenate([rng.integers(0, N, size=12), [N - 1 - i % 7, i % 5]]))
+            for i in range(len(rows))]
+    counts = np.zeros(N, dtype=np.int64)
+    counts[rows] = [len(c) for c in cols]
+    rp = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    ci = np.concatenate(cols).astype(np.int32)
+    shape = (N, d) if H == 1 else (N, H, d)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v, g = (torch.randn(shape, generator=gen, device="cuda", dtype=t) for _ in range(4))
+    plan = gpu.Plan(_dev(rp), _dev(ci), N)
+    plan_t = plan.transpose()
+    print("2 to 4 GiB", N, H, d, dtype, flush=True)
+    O, lse = gpu.forward_typed(plan, q, k, v, scale=0.1, want_lse=True)
+    dQ, dK, dV = gpu.backward(plan, plan_t, q, k, v, O, g, lse, scale=0.1)
+    keys = np.unique(ci)
+    r, c = torch.from_numpy(rows).cuda(), torch.from_numpy(keys).cuda()
+    sub_rp = np.zeros(max(len(rows), len(keys)) + 1, dtype=np.int32)
+    sub_rp[1:len(rows) + 1] = np.cumsum([len(x) for x in cols])
+    sub_rp[len(rows) + 1:] = sub_rp[len(rows)]
+    sub_ci = np.searchsorted(keys, ci).astype(np.int32)
+    n = len(sub_rp) - 1
+
+    def part(x, ids, h):
+        out = torch.zeros((n, d), dtype=torch.float64, device="cuda")
+        out[:len(ids)] = x.view(N, H, d)[ids, h].double()
+        return out
+
+    bar = REL if dtype == "f16" else 2e-5
+    for h in sorted({0, H // 2, H - 1}):
+        want = _attention_f64(sub_rp, sub_ci, part(q, r, h), part(k, c, h), part(v, c, h),
+                              part(g, r, h), 0.1)
+        for got, ids, ref in ((O, r, want[0]), (dQ, r, want[2]), (dK, c, want[3]),
+                              (dV, c, want[4])):
+            x = got.view(N, H, d)[ids, h].double()
+            ref = ref[:len(ids)]
+            assert float((x - ref).norm()) <= bar * float(ref.norm())
+        x = lse.view(N, H)[r, h].double()
+        assert float((x - want[1][:len(rows)]).abs().max()) <= 1e-3
+    for got, ids in ((O, r), (dQ, r), (dK, c), (dV, c)):
+        got[ids] = 0
+        assert not got.any()

@@ -1,6 +1,6 @@
 """The library's host-side rules on the CPU: tests/host_rules/host_rules.hip,
-compiled for the host only (it calls no HIP function) against the library's
-internal header."""
+compiled for the host only (it calls no HIP function) with undefined behaviour
+trapped, against the library's internal header."""
 import os
 import subprocess
 
@@ -13,6 +13,8 @@ def test_host_rules(tmp_path):
     from paper_2505_08098_amd import build as lib_build
     exe = tmp_path / "host_rules"
     subprocess.run([lib_build.hipcc(), "-O1", "-std=c++17", "-Wall", "--offload-host-only",
+                    "-Xarch_host", "-fsanitize=undefined",
+                    "-Xarch_host", "-fno-sanitize-recover=all",
                     "-I", os.path.join(ROOT, "include"),
                     "-I", os.path.join(ROOT, "paper_2505_08098_amd", "csrc"),
                     os.path.join(ROOT, "tests", "host_rules", "host_rules.hip"),
