@@ -206,8 +206,12 @@ class _BuildOn:
         if torch.cuda.current_device() != self.device.index:
             self.guard = torch.cuda.device(self.device)
             self.guard.__enter__()
-        if _raw_stream(self.device.index):
-            torch.cuda.current_stream().synchronize()
+        try:
+            if _raw_stream(self.device.index):
+                torch.cuda.current_stream().synchronize()
+        except BaseException:  # (no __exit__ follows)
+            self.__exit__(None, None, None)
+            raise
 
     def __exit__(self, *exc):
         if self.guard is not None:

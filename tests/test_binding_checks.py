@@ -68,3 +68,41 @@ def test_results_are_new_contiguous_tensors(form, dtype):
     assert type(out) is torch.Tensor and not out.requires_grad
     assert out.is_contiguous() and out.shape == t.shape and out.dtype == dtype
     assert out.device == t.device
+
+
+@pytest.mark.parametrize("other_device", [False, True])
+@pytest.mark.parametrize("fails", [False, True])
+def test_build_leaves_the_current_device_as_it_was(monkeypatch, other_device, fails):
+    """A plan build on another device than the current one leaves it current
+    again, also when waiting for the current stream raises (a capture, an error
+    of earlier work)."""
+    current = [0 if other_device else 1]
+
+    class Guard:
+        def __init__(self, device):
+            self.to = device.index
+
+        def __enter__(self):
+            self.back, current[0] = current[0], self.to
+
+        def __exit__(self, *exc):
+            current[0] = self.back
+
+    def wait():
+        assert current[0] == 1
+        if fails:
+            raise RuntimeError("stream is capturing")
+
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: current[0])
+    monkeypatch.setattr(torch.cuda, "device", Guard)
+    monkeypatch.setattr(torch.cuda, "current_stream",
+                        lambda *a: types.SimpleNamespace(synchronize=wait))
+    monkeypatch.setattr(binding, "_raw_stream", lambda index: 1234)
+    before = current[0]
+    built = False
+    try:
+        with binding._BuildOn(torch.device("cuda", 1)):
+            built = current[0] == 1
+    except RuntimeError:
+        assert fails
+    assert current[0] == before and built == (not fails)
