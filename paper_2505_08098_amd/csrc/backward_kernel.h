@@ -87,6 +87,12 @@ template <> struct BwdWaves<128> { static constexpr int value = 2; };
 template <int D> struct BwdDqWaves { static constexpr int value = BwdWaves<D>::value; };
 template <> struct BwdDqWaves<32> { static constexpr int value = 6; };
 template <> struct BwdDqWaves<64> { static constexpr int value = 4; };
+// With 64-bit addresses its waves that share items (d = 64) have no room for
+// the fourth one's registers.
+template <int D, bool kWide, int NW> constexpr int dq_waves()
+{
+    return BwdDqWaves<D>::value - (D == 64 && kWide && NW > 1 ? 1 : 0);
+}
 
 // Row-contiguous gather of the 32 rows (two blocks) of a block pair from two
 // row-major fp16 matrices A and B (same rows): chunk f = lane + 64 j is row
@@ -138,7 +144,7 @@ __device__ __forceinline__ float masked_exp2(float x, uint32_t sel)
 // dQ^T += K_hat^T dS^T with K_hat read transposed from LDS.
 template <int D, bool kWide, bool kBF16, int NW = 1>
 __global__ __launch_bounds__(64 * NW)
-__attribute__((amdgpu_waves_per_eu(BwdDqWaves<D>::value, 8))) void k_bwd_dq(
+__attribute__((amdgpu_waves_per_eu(dq_waves<D, kWide, NW>(), 8))) void k_bwd_dq(
     const WorkItem *__restrict__ items, const int32_t *__restrict__ cols,
     const uint32_t *__restrict__ mask, const int32_t *__restrict__ win_row,
     const _Float16 *__restrict__ Q, const _Float16 *__restrict__ K,

@@ -101,9 +101,10 @@ constexpr int waves_per_simd()
 // a sequence's rows stay in the caches (2 heads of 16,001 tokens, d = 128: 66.0
 // against 65.2), and more with narrower rows or the half-size fp8 ones (fp8,
 // d = 128, 24,000 tokens: 96.8 against 93.2; f16, d = 160: 164.5 against 161.4).
-template <int D, int kIn> constexpr bool joint_rows()
+// (f16, d = 96, 64-bit addresses: the order whose registers do not spill.)
+template <int D, bool kWide, int kIn> constexpr bool joint_rows()
 {
-    return kIn != kInFP8 && (D == 128 || D >= 192);
+    return kIn != kInFP8 && (D == 128 || D >= 192 || (D == 96 && kWide && kIn == kInF16));
 }
 // Score product for the input storage type (16-bit operands as raw bits).
 template <int kIn>
@@ -198,10 +199,10 @@ __device__ __forceinline__ void store4(void *base, int64_t idx, f4 v)
 // where one wave per window leaves the GPU with too few waves) -- and of the
 // others each wave takes one.
 // kTrace (a measurement instance): the first thread of each
-// item (its first wave) also records, after its outputs, when the item's work
-// started and ended (the 100 MHz constant clock) and on which compute unit it
-// ran, as one 32-byte record per item, in launch order, in `trace` (ordinary
-// vector stores).
+// item (its first wave) also records when the item's work started and, after
+// its outputs, when it ended (the 100 MHz constant clock) and on which compute
+// unit it ran, as one 32-byte record per item, in launch order, in `trace`
+// (ordinary vector stores).
 template <int D, bool kWide, int kIn, bool kOutH, bool kNarrow = false, int NW = 1,
           bool kTrace = false>
 __global__ __launch_bounds__(64 * NW)
@@ -214,7 +215,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
     int32_t h0, int32_t nh, float sl2, uint32_t order, int32_t n_items, int32_t shared_items,
     uint32_t *__restrict__ trace)
 {
-    uint64_t t_start = 0;
+    [[maybe_unused]] uint64_t t_start = 0;
     if constexpr (kTrace) t_start = wall_clock64();
     constexpr int NC = D / 32;  // 32-deep chunks of the score reduction
     constexpr int NT = D / 16;  // 16-wide output tiles of the value product
@@ -253,6 +254,12 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
     if (!wave_item<NW>(group, wv, shared_items, n_items, &item, &shared)) return;
     const int head = h0 + hl;
     const WorkItem it = items[item];
+    typedef uint32_t u2t __attribute__((ext_vector_type(2)));
+    if constexpr (kTrace) {  // (kept until the end, the time would cost d = 96 a spill)
+        if (lane == 0 && (wv == 0 || !shared))
+            *reinterpret_cast<u2t *>(trace + 8 * (int64_t)(shared ? blockIdx.x : (uint32_t)item)) =
+                u2t{(uint32_t)t_start, (uint32_t)(t_start >> 32)};
+    }
     // Row r of head h starts at r * ld + h * D (elements) in Q, K, V and O.
     constexpr int EB = elem_bytes<kIn>();
     const char *Q = static_cast<const char *>(Qv) + (int64_t)head * D * EB;
@@ -352,7 +359,11 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
             }
             return __builtin_bit_cast(h8, w);
         } else if constexpr (kWide) {
-            return *reinterpret_cast<const h8 *>(X + (int64_t)cj * ld * EB + 16 * (f % LPR));
+            int64_t off = (int64_t)cj * ld * EB + 16 * (f % LPR);
+            // (kept whole: added up from the other end, a pointer per chunk and
+            // table stays in registers, which at d = 96 then spill)
+            asm("" : "+v"(off));
+            return *reinterpret_cast<const h8 *>(X + off);
         } else {
             // byte offset < 2^32 (checked on the host): the load takes
             // the uniform base from SGPRs and a 32-bit VGPR offset
@@ -368,7 +379,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
 #pragma unroll
         for (int j = 0; j < NI; ++j) st[j] = load_chunk(X, chunk_row(j), j);
     };
-    constexpr bool kJoint = joint_rows<D, kIn>();
+    constexpr bool kJoint = joint_rows<D, kWide, kIn>() && !(kNarrow && kWide);
     auto load_joint = [&]() {
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
@@ -602,10 +613,9 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
             const uint32_t xcc = __builtin_amdgcn_s_getreg((15 << 11) | 20);
             typedef uint32_t u4t __attribute__((ext_vector_type(4)));
             const uint32_t k = shared ? blockIdx.x : (uint32_t)item;
-            u4t *rec = reinterpret_cast<u4t *>(trace + 8 * (int64_t)k);
-            rec[0] = u4t{(uint32_t)t_start, (uint32_t)(t_start >> 32), (uint32_t)t_end,
-                         (uint32_t)(t_end >> 32)};
-            rec[1] = u4t{hw, xcc, k, 0u};
+            uint32_t *rec = trace + 8 * (int64_t)k;
+            *reinterpret_cast<u2t *>(rec + 2) = u2t{(uint32_t)t_end, (uint32_t)(t_end >> 32)};
+            *reinterpret_cast<u4t *>(rec + 4) = u4t{hw, xcc, k, 0u};
         }
     }
 }
