@@ -73,7 +73,8 @@ typedef struct {
                               (f3s_plan_segments);
                               bit 3: split-row forward (ablation)                */
     int64_t bsb_bytes;     /* window offsets + column lists + bitmaps            */
-    int64_t device_bytes;  /* everything the plan holds on the device            */
+    int64_t device_bytes;  /* everything the plan holds on the device; arrays
+                              shared with a transposed plan count in both       */
     double build_ms;       /* wall time of f3s_plan                              */
 } f3s_plan_info_t;
 

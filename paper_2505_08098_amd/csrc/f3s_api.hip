@@ -98,20 +98,9 @@ void free_plan_arrays(f3s_plan_s *p)
 // once (at most 33 MB, 67 MB for a transposed plan).
 constexpr int32_t kWidePartPieces = 512;
 
-// Partial-result buffers of split windows: part_row floats per piece row
-// for O (kMaxD for a plan, 2 * kMaxD for a transposed plan, which holds the
-// dK and dV partials; four times that with few pieces, so that more heads
-// go in one launch), and the (m, l) records.  Replaces any previous ones.
-hipError_t alloc_parts(f3s_plan_s *p, int32_t part_row)
+// Partial-result buffers of split windows, part_row floats per piece row for O.
+hipError_t alloc_parts_of(f3s_plan_s *p, int32_t part_row)
 {
-    if (p->n_pieces <= kWidePartPieces) part_row *= 4;
-    if (p->part_store) {
-        (void)hipFree(p->part_store);
-        p->device_bytes -= (int64_t)p->part_bytes;
-        p->part_store = nullptr;
-        p->part_o = p->part_ml = nullptr;
-        p->part_bytes = 0;
-    }
     p->part_row = part_row;
     if (p->n_pieces == 0) return hipSuccess;
     Arena a;
@@ -127,6 +116,19 @@ hipError_t alloc_parts(f3s_plan_s *p, int32_t part_row)
     p->part_o = a.take<float>((int64_t)p->n_pieces * f3s::kWindowRows * part_row);
     p->part_ml = a.take<float>((int64_t)p->n_pieces * 32 * (part_row / 32));
     return hipSuccess;
+}
+
+// The partial buffers of a plan that has none, of part_row floats (kMaxD for
+// a plan, 2 * kMaxD for a transposed plan, which holds the dK and dV
+// partials), or four times that with few pieces, so that more heads go in one
+// launch -- unless only the smaller ones are to be had.
+hipError_t alloc_parts(f3s_plan_s *p, int32_t part_row)
+{
+    if (p->n_pieces <= kWidePartPieces) {
+        if (alloc_parts_of(p, 4 * part_row) == hipSuccess) return hipSuccess;
+        (void)hipGetLastError();
+    }
+    return alloc_parts_of(p, part_row);
 }
 
 // The plan's arrays in one allocation, laid out from its counts (T, blocks,

@@ -124,3 +124,44 @@ def test_segment_plan_allocation_failing_leaks_nothing(gpu, monkeypatch):
         failures += not res[0]
         print(f"  limit {lim}: plan {'built' if res[0] else 'out of memory'}", flush=True)
     assert failures >= 2 and res[-1]
+
+
+def test_partial_buffers_fall_back_to_one_launch_group(gpu, monkeypatch):
+    """Plans with few pieces hold the partial results of four launch groups'
+    heads where that much memory is to be had, and of one group where it is
+    not: the plan is built all the same, and heads in more launches give the
+    same results."""
+    L = gpu.load_library()
+    c = W.make_config(2, with_features=False)
+    rp, ci, N = _dev(c["row_ptr"]), _dev(c["col_idx"]), c["N"]
+    ws = torch.empty(L.f3s_plan_workspace_bytes(N, ci.numel()), dtype=torch.uint8, device=DEV)
+
+    def build(limit):
+        if limit:
+            monkeypatch.setenv("F3S_ALLOC_LIMIT_BYTES", str(limit))
+        h = L.f3s_plan_ws(rp.data_ptr(), ci.data_ptr(), N, ws.data_ptr(), ws.numel())
+        assert h, limit
+        plan = gpu.Plan._from_handle(h, DEV, N)
+        plan_t = plan.transpose()
+        monkeypatch.delenv("F3S_ALLOC_LIMIT_BYTES", raising=False)
+        return plan, plan_t
+
+    wide, wide_t = build(0)
+    i = wide.info
+    assert 0 < i["n_pieces"] <= 512
+    group = i["n_pieces"] * 16 * 4 * 256           # bytes of one launch group
+    store = i["device_bytes"] - 4 * (group + i["n_pieces"] * 32 * 4 * 8)
+    limit = 7 * group // 2
+    assert store < limit                           # the plan's own arrays fit
+    few, few_t = build(limit)
+    assert few.info["device_bytes"] <= wide.info["device_bytes"] - 3 * group
+    assert few_t.info["device_bytes"] <= wide_t.info["device_bytes"] - 6 * group
+    H, d = 5, 128
+    gen = torch.Generator(device=DEV).manual_seed(2)
+    q, k, v, g = (torch.randn((N, H, d), generator=gen, device=DEV).half() for _ in range(4))
+    res = []
+    for p, t in ((wide, wide_t), (few, few_t)):
+        O, lse = gpu.forward(p, q, k, v)
+        res.append((O, lse) + gpu.backward(p, t, q, k, v, O, g, lse))
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
