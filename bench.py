@@ -351,10 +351,9 @@ def dram_check(args, stream, dev, reps=10):
 
 
 def cu_balance(rec, khz):
-    """Per compute unit busy time from f3s_run_trace records (one per
-    workgroup): busy = the union of its workgroups' [start, end] intervals,
-    end = its last workgroup's end, both in microseconds from the kernel's
-    first start."""
+    """Per compute unit busy time from f3s_run_trace records (one per work
+    item): busy = the union of its items' [start, end] intervals, end = its
+    last item's end, both in microseconds from the kernel's first start."""
     import numpy as np
     rec = rec.astype(np.uint64)
     t0 = rec[:, 0] | (rec[:, 1] << np.uint64(32))

@@ -83,17 +83,18 @@ f3s_status_t f3s_probe_rows(const void *table, int64_t rows, int32_t row_bytes,
 
 /*
  * f3s_run(plan, Q, K, V, O, d, scale, stream) with a record of where and when
- * each workgroup ran: the load-balance view of the paper's per-SM active
+ * each work item ran (its workgroup, or of the items that a workgroup's waves
+ * take one each, its wave): the load-balance view of the paper's per-SM active
  * time (Section 4.3, row-window reordering), for one head, fp16 in, fp32 out.
  * O receives exactly f3s_run's result.  trace: device memory of at least
- * 32 * n_items bytes (f3s_plan_info), 16-byte aligned; record k (workgroup
- * k = work item k of the launch order) holds eight uint32:
+ * 32 * n_items bytes (f3s_plan_info), 16-byte aligned; record k (work item k
+ * of the launch order) holds eight uint32:
  *   [0], [1]  start time, low and high word   (constant clock; see
  *   [2], [3]  end time, low and high word      f3s_wall_clock_khz)
  *   [4]       the HW_ID register: CU id bits 8-11, shader array bit 12,
  *             shader engine bits 13-15
  *   [5]       the XCC_ID register (bits 0-3: which accelerator die)
- *   [6]       workgroup index, [7] 0
+ *   [6]       k, [7] 0
  * Patterns whose Q, K, V exceed 4 GiB give F3S_ERR_UNSUPPORTED; a short or
  * misaligned trace buffer F3S_ERR_INVALID_VALUE.  Otherwise as f3s_run.
  */

@@ -583,7 +583,7 @@ def probe_rows(table, rows, row_bytes, sink, in_flight=8, workgroups=2048, round
 
 def run_trace(plan, Q, K, V, scale=None, out=None, stream=None):
     """f3s_run_trace: one-head fp16 -> fp32 forward (O as f3s_run) plus one
-    record per workgroup (start, end, compute unit); returns (O, records)
+    record per work item (start, end, compute unit); returns (O, records)
     with records a uint32 device tensor [n_items, 8]."""
     shape = tuple(Q.shape)
     for t, n in ((Q, "Q"), (K, "K"), (V, "V")):

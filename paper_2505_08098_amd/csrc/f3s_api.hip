@@ -537,10 +537,10 @@ size_t transpose_workspace_bytes(const f3s_plan_s *src, bool with_build)
 }
 
 // Plan of A^T from a plan of A: an exact symmetry check (on the plan, or for
-// large patterns on the CSR of A^T); if A^T = A the plan is copied,
-// otherwise the plan of A^T is built from its CSR (radix sort).  Its split-window partials hold two
-// rows (dK, dV) per piece row, so a launch group still holds heads with
-// nh * d <= kMaxD.
+// large patterns on the CSR of A^T); if A^T = A the new plan shares the
+// plan's arrays, otherwise the plan of A^T is built from its CSR (radix sort).
+// Its split-window partials hold two rows (dK, dV) per piece row, so its launch
+// groups hold as many heads as a plan's (nh * 2 d <= part_row).
 f3s_plan_t make_transpose(f3s_plan_t src, void *workspace, size_t workspace_bytes)
 {
     const auto t0 = std::chrono::steady_clock::now();

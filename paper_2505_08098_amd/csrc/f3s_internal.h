@@ -430,15 +430,11 @@ hipError_t launch_windows(const int32_t *row_ptr, const int32_t *col_idx, int32_
                           int32_t *tmp_cols, uint32_t *tmp_mask, int32_t *u, int32_t *bits,
                           hipStream_t s);
 // Exclusive scan of n int32 into out[0..n], out[n] = total (in == out ok).
-// Element i is in[i], or in[gather[i]] when gather is given.  With list
-// given, every nonzero element i is also listed: list[out[i]] = i (flag
-// compaction).  total (may be null) also receives the total.
+// total (may be null) also receives the total.
 struct ScanArray {
     const int32_t *in = nullptr;
-    const int32_t *gather = nullptr;
     int32_t *out = nullptr;
     int32_t *total = nullptr;
-    int32_t *list = nullptr;
     int32_t *tile_sums = nullptr;  // set by the launcher (from tmp)
 };
 // tmp: scan_tmp_ints(n) ints of workspace.
@@ -515,9 +511,10 @@ hipError_t launch_transpose_csr(const f3s_plan_s &p, void *scratch, size_t scrat
 // on small patterns); win: scratch of n_blocks ints.
 hipError_t launch_check_symmetric(const f3s_plan_s &p, int32_t *win, int32_t *asym,
                                   hipStream_t s);
-// The same decision given the CSR of A^T, *asym zeroed by the caller (every row of A compared with the
-// same row of A^T, position by position; cheaper on large patterns once A^T
-// is sorted anyway).  win: n_blocks ints, pre: 16 * n_blocks ints of scratch.
+// The same decision given the CSR of A^T, *asym zeroed by the caller (every
+// row of A compared with the same row of A^T, position by position; cheaper on
+// large patterns once A^T is sorted anyway).  win: n_blocks ints, pre: 16 *
+// n_blocks ints of scratch.
 hipError_t launch_compare_rows(const f3s_plan_s &p, const int32_t *rpt, const int32_t *cit,
                                int32_t *win, int32_t *pre, int32_t *asym, hipStream_t s);
 
@@ -539,8 +536,8 @@ hipError_t launch_fused_bf16(const f3s_plan_s &p, const void *Q, const void *K,
                              const void *V, void *O, bool out_f16, float *lse, int32_t H,
                              int32_t d, float scale_log2, hipStream_t s);
 // Measurement instance of the one-head fp16 -> fp32 forward: the same result
-// in O, plus a 32-byte record per workgroup in trace (start and end times on
-// the constant clock, hardware ids of the compute unit, workgroup index).
+// in O, plus a 32-byte record per work item in trace (start and end times on
+// the constant clock, hardware ids of the compute unit, record index).
 hipError_t launch_fused_trace(const f3s_plan_s &p, const void *Q, const void *K,
                               const void *V, void *O, int32_t d, float sl2, uint32_t *trace,
                               hipStream_t s);

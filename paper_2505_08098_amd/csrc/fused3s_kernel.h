@@ -698,7 +698,7 @@ __global__ __launch_bounds__(256) void k_merge(const int32_t *__restrict__ merge
 // (nh * D <= part_row floats per piece row); without split windows all heads go
 // in one launch.
 // trace (the measurement instance, fp16 -> fp32 with 32-bit addressing and
-// one head only): one 32-byte record per workgroup.
+// one head only): one 32-byte record per work item.
 template <int D, int kIn, bool kOutH, bool kNarrow = false>
 hipError_t launch_d(const f3s_plan_s &p, const void *Q, const void *K,
                     const void *V, void *O, float *lse, int32_t H, float sl2,
@@ -706,7 +706,6 @@ hipError_t launch_d(const f3s_plan_s &p, const void *Q, const void *K,
 {
     const int32_t ld = H * D;
     const bool wide = (uint64_t)p.N * ld * elem_bytes<kIn>() > 0xFFFFFFF0ull;
-    // the narrow-gather ablation keeps one wave per item
     // the narrow-gather ablation keeps one wave per item
     const WaveSplit ws =
         kNarrow ? WaveSplit{1, p.n_items}

@@ -771,11 +771,6 @@ constexpr int kScanOneLaunch = kScanThreads * 16;
 // Up to this many elements the tile totals fit one workgroup's threads.
 constexpr int64_t kScanTwoPass = (int64_t)kScanTile * kScanThreads;
 
-__device__ __forceinline__ int scan_element(const ScanArray &a, int64_t i)
-{
-    return a.gather ? a.in[a.gather[i]] : a.in[i];
-}
-
 // tile_sums[tile] = sum of the tile's elements.  blockIdx.y selects one of
 // two independent arrays.
 __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(ScanArray a0, ScanArray a1,
@@ -787,7 +782,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(ScanArray a0, Scan
     const int64_t first = ((int64_t)blockIdx.x * kScanThreads + tid) * kScanItems;
     int own = 0;
 #pragma unroll
-    for (int j = 0; j < kScanItems; ++j) own += first + j < n ? scan_element(a, first + j) : 0;
+    for (int j = 0; j < kScanItems; ++j) own += first + j < n ? a.in[first + j] : 0;
     const int incl = wave_inclusive_sum(own, lane);
     if (lane == 63) wave_sum[wv] = incl;
     __syncthreads();
@@ -805,8 +800,8 @@ enum ScanCarry { kCarryNone, kCarrySumBefore, kCarryScanned };
 // and one barrier cover the tile.  The carry into the tile is 0 (a single
 // tile), the sum of the totals of the tiles before it (at most kScanThreads
 // of them), or the tile's entry of the already scanned totals.  The last
-// tile writes out[n] = total (and *total).  Nonzero elements are listed when
-// a list is given.  blockIdx.y selects one of two independent arrays.
+// tile writes out[n] = total (and *total).  blockIdx.y selects one of two
+// independent arrays.
 template <int K, ScanCarry C>
 __global__ __launch_bounds__(kScanThreads) void k_scan(ScanArray a0, ScanArray a1, int32_t n)
 {
@@ -816,7 +811,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(ScanArray a0, ScanArray a
     const int64_t first = ((int64_t)blockIdx.x * kScanThreads + tid) * K;
     int v[K];
 #pragma unroll
-    for (int j = 0; j < K; ++j) v[j] = first + j < n ? scan_element(a, first + j) : 0;
+    for (int j = 0; j < K; ++j) v[j] = first + j < n ? a.in[first + j] : 0;
     int carry_part = 0;
     if (C == kCarrySumBefore && tid < (int)blockIdx.x) carry_part = a.tile_sums[tid];
     int own = 0;
@@ -841,10 +836,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(ScanArray a0, ScanArray a
     int run = carry + before + incl - own;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        if (first + j < n) {
-            a.out[first + j] = run;
-            if (a.list && v[j] && run < n) a.list[run] = (int32_t)(first + j);
-        }
+        if (first + j < n) a.out[first + j] = run;
         run += v[j];
     }
     if (tid == 0 && blockIdx.x == gridDim.x - 1) {

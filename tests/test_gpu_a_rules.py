@@ -291,7 +291,7 @@ def test_window_entry_classes(gpu, n):
 
 
 def test_symmetry_of_patterns_that_differ_in_one_entry(gpu):
-    """The transposed plan copies a symmetric pattern's plan and builds its own
+    """The transposed plan shares a symmetric pattern's arrays and builds its own
     when one entry, in a dense or a sparse block, lacks its mirror."""
     rng = np.random.default_rng(4)
     N = 530
