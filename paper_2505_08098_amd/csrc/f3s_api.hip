@@ -331,7 +331,7 @@ f3s_status_t build_plan(f3s_plan_s *p, const int32_t *row_ptr, const int32_t *co
     p->flags = (reorder ? 0 : 1) | (env_int("F3S_NARROW_GATHER", 0) ? 2 : 0) | (wr ? 4 : 0) |
                (env_int("F3S_SPLIT_ROW", 0) ? 8 : 0);
     HIP_TRY(launch_shape(b.u, b.bits, T, env_int("F3S_PIECE_BLOCKS", 0), slots,
-                         !(p->flags & 10), !reorder ? kOrderWindow : order_forced ? kOrderSorted : kOrderAuto, st,
+                         !reorder ? kOrderWindow : order_forced ? kOrderSorted : kOrderAuto, st,
                          b.nb, b.blk_off, b.key, b.slot_base, b.split_idx, b.pos, b.scan_tmp,
                          s));
     HIP_TRY(hipMemcpy(&hs, st, sizeof hs, hipMemcpyDeviceToHost));

@@ -246,19 +246,19 @@ inline bool xcd_chunks(const f3s_plan_s &p, int32_t heads, bool head_major = fal
 // 4 bf16 heads forward and backward 421 -> 372 us; sequence of 16,001 tokens, 2
 // heads of d = 128, forward and backward 303 -> 233 us; ER graph of 10,007
 // nodes, 16 neighbours, 2 heads 56 -> 37 us.
-// Where no workgroup shares a heavy item -- the ablations of one wave per item
-// (shared false), and skewed windows listed in window order -- the pieces stay
-// n_blocks / slots, at least 16: nothing else shortens a hub there.
+// Skewed windows listed in window order have no heavy items in front for a
+// workgroup to share: the pieces stay n_blocks / slots, at least 16.  (The
+// gather and split-row ablations take the pieces of the plans that they are
+// compared with, bit for bit.)
 __host__ __device__ inline int32_t plan_piece(int64_t n_blocks, int32_t max_blocks, int32_t T,
-                                              int32_t forced, int32_t slots, bool shared,
-                                              bool window_order)
+                                              int32_t forced, int32_t slots, bool window_order)
 {
     const int64_t cap = ((int64_t)(max_blocks > 2 ? max_blocks : 2) + 1) & ~1LL;
     int64_t piece;
     const bool uniform = (int64_t)max_blocks * T <= 2 * n_blocks;
     if (forced >= 2) {
         piece = forced & ~1;
-    } else if (!shared || (window_order && !uniform)) {
+    } else if (window_order && !uniform) {
         piece = (n_blocks + slots - 1) / slots;
         if (piece < 16) piece = 16;
         piece = (piece + 1) & ~1LL;
@@ -455,8 +455,8 @@ hipError_t launch_fill_windows(const int32_t *row_ptr, const int32_t *win_row, i
                                hipStream_t s);
 // Blocks per window and the shape of the work list, from u and bits: nb[w] =
 // ceil(u[w] / 16) and its prefix blk_off[0..T]; the statistics (st->n_unique,
-// nnz, n_blocks, max_blocks); the piece size (see plan_piece for forced, slots
-// and shared) in st->piece; per window the sort key, and
+// nnz, n_blocks, max_blocks); the piece size (see plan_piece for forced and
+// slots) in st->piece; per window the sort key, and
 // over the split windows the prefixes of their pieces (slot_base[0..T]) and
 // of their number (split_idx[0..T]); st->n_pieces and n_split.  order:
 // kOrderAuto keeps window order for nearly uniform windows and sorts others,
@@ -466,7 +466,7 @@ hipError_t launch_fill_windows(const int32_t *row_ptr, const int32_t *win_row, i
 // scan_tmp: scan_tmp_ints(T) ints.
 constexpr int kOrderAuto = 0, kOrderSorted = 1, kOrderWindow = 2;
 hipError_t launch_shape(const int32_t *u, const int32_t *bits, int32_t T, int32_t forced,
-                        int32_t slots, bool shared, int order, BuildStats *st, int32_t *nb,
+                        int32_t slots, int order, BuildStats *st, int32_t *nb,
                         int32_t *blk_off, int32_t *key, int32_t *slot_base, int32_t *split_idx,
                         int32_t *pos, int32_t *scan_tmp, hipStream_t s);
 

@@ -878,12 +878,11 @@ __global__ __launch_bounds__(256) void k_fill_windows(
 // Keys, pieces and split flags per window.
 __global__ __launch_bounds__(256) void k_bin_keys(
     const int32_t *nb, int32_t T, const int32_t *n_blocks, const int32_t *max_blocks,
-    int32_t forced, int32_t slots, bool shared, bool window_order, int32_t *piece_out,
+    int32_t forced, int32_t slots, bool window_order, int32_t *piece_out,
     int32_t *key, int32_t *split_pieces, int32_t *split_one)
 {
     const int w = blockIdx.x * blockDim.x + threadIdx.x;
-    const int32_t piece =
-        plan_piece(*n_blocks, *max_blocks, T, forced, slots, shared, window_order);
+    const int32_t piece = plan_piece(*n_blocks, *max_blocks, T, forced, slots, window_order);
     if (w == 0) *piece_out = piece;
     if (w >= T) return;
     const int n = nb[w];
@@ -915,7 +914,7 @@ constexpr int kPlaceWaves = kPlaceThreads / 64;
 
 __global__ __launch_bounds__(kPlaceThreads) void k_shape(
     const int32_t *__restrict__ u, const int32_t *__restrict__ bits, int32_t T, int steps,
-    int32_t forced, int32_t slots, bool shared, int order, BuildStats *st, int32_t *blk_off,
+    int32_t forced, int32_t slots, int order, BuildStats *st, int32_t *blk_off,
     int32_t *key, int32_t *slot_base, int32_t *split_idx, int32_t *pos)
 {
     __shared__ uint16_t cnt[kPlaceWaves][kPlaceKeys];  // [wave][piece - key]
@@ -971,8 +970,7 @@ __global__ __launch_bounds__(kPlaceThreads) void k_shape(
         total += snb[k];
         max_nb = max(max_nb, smax[k]);
     }
-    const int32_t piece =
-        plan_piece(total, max_nb, T, forced, slots, shared, order == kOrderWindow);
+    const int32_t piece = plan_piece(total, max_nb, T, forced, slots, order == kOrderWindow);
     // this wave's pieces of split windows
     int run_pc = 0, run_one = 0, all_pc = 0, all_one = 0;
     if (max_nb > piece) {  // uniform
@@ -1275,14 +1273,14 @@ hipError_t launch_fill_windows(const int32_t *row_ptr, const int32_t *win_row, i
 }
 
 hipError_t launch_shape(const int32_t *u, const int32_t *bits, int32_t T, int32_t forced,
-                        int32_t slots, bool shared, int order, BuildStats *st, int32_t *nb,
+                        int32_t slots, int order, BuildStats *st, int32_t *nb,
                         int32_t *blk_off, int32_t *key, int32_t *slot_base, int32_t *split_idx,
                         int32_t *pos, int32_t *scan_tmp, hipStream_t s)
 {
     if (T <= kOnePlace) {
         const int steps = (T + kPlaceThreads - 1) / kPlaceThreads;
-        k_shape<<<1, kPlaceThreads, 0, s>>>(u, bits, T, steps, forced, slots, shared, order, st,
-                                            blk_off, key, slot_base, split_idx, pos);
+        k_shape<<<1, kPlaceThreads, 0, s>>>(u, bits, T, steps, forced, slots, order, st, blk_off,
+                                            key, slot_base, split_idx, pos);
         return hipGetLastError();
     }
     const unsigned g = grid_for(T, kStatThreads);
@@ -1291,8 +1289,8 @@ hipError_t launch_shape(const int32_t *u, const int32_t *bits, int32_t T, int32_
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     k_bin_keys<<<grid_for(T, 256), 256, 0, s>>>(nb, T, &st->n_blocks, &st->max_blocks, forced,
-                                                slots, shared, order == kOrderWindow, &st->piece,
-                                                key, slot_base, split_idx);
+                                                slots, order == kOrderWindow, &st->piece, key,
+                                                slot_base, split_idx);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     ScanArray sp, so;
     sp.in = sp.out = slot_base;

@@ -241,24 +241,22 @@ static int order_rule()
 static int piece_rule()
 {
     const int32_t slots = 2048;
-    // the hub-heavy graph: pieces for workgroups that share them, or not
-    CHECK(plan_piece(67341, 1465, 4096, 0, slots, true, false) == 132);
-    for (bool order : {false, true}) CHECK(plan_piece(67341, 1465, 4096, 0, slots, false, order) == 34);
-    CHECK(plan_piece(67341, 1465, 4096, 0, slots, true, true) == 34);
-    // nearly uniform windows stay whole in either order, unless a wave has
-    // each item for itself
-    for (bool order : {false, true}) CHECK(plan_piece(81081, 81, 1001, 0, slots, true, order) == 82);
-    CHECK(plan_piece(81081, 81, 1001, 0, slots, false, true) == 40);
-    for (bool shared : {false, true}) {
+    // the hub-heavy graph: pieces for workgroups that share them, or, in window
+    // order, for one wave each
+    CHECK(plan_piece(67341, 1465, 4096, 0, slots, false) == 132);
+    CHECK(plan_piece(67341, 1465, 4096, 0, slots, true) == 34);
+    for (bool order : {false, true}) {
+        // nearly uniform windows stay whole in either order
+        CHECK(plan_piece(81081, 81, 1001, 0, slots, order) == 82);
         for (int32_t forced : {2, 7, 40}) {
-            CHECK(plan_piece(67341, 1465, 4096, forced, slots, shared, true) == (forced & ~1));
-            CHECK(plan_piece(10, 5, 4, forced, slots, shared, true) == (forced < 6 ? forced & ~1 : 6));
+            CHECK(plan_piece(67341, 1465, 4096, forced, slots, order) == (forced & ~1));
+            CHECK(plan_piece(10, 5, 4, forced, slots, order) == (forced < 6 ? forced & ~1 : 6));
         }
         // even, at least 2, at most the largest window; also at the limits
         for (int64_t n : {0ll, 1ll, 100ll, 1ll << 20, 2147483647ll})
             for (int32_t T : {1, 3, 1000, 134217728})
                 for (int32_t m : {0, 1, 2, 17, 65536, 134217727}) {
-                    const int32_t piece = plan_piece(n, m, T, 0, slots, shared, false);
+                    const int32_t piece = plan_piece(n, m, T, 0, slots, order);
                     CHECK(piece >= 2 && piece % 2 == 0 && piece <= (m > 2 ? m + (m & 1) : 2));
                 }
     }
