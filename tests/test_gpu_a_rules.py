@@ -140,6 +140,12 @@ def test_heavy_items_shared_by_four_waves(gpu, N, hubs, hub_deg, H, d, dtype, mo
         for h in range(H):
             q1, k1, v1 = (x[:, h].numpy() for x in (Q, K, V))
             _check(got[0][:, h], oracle.attention_f64(rp, ci, q1, k1, v1, 0.1))
+    # results and gradients of both types against fp64 (f16: probabilities and
+    # score gradients in 11 bits; bf16: in two 8-bit terms)
+    for h in range(H):
+        ref = _attention_f64(rp, ci, *(x[:, h].double() for x in (q, k, v, g)), 0.1)
+        for a, b in zip(got, ref):
+            assert float((a[:, h] - b).norm()) <= (REL if dtype == "f16" else 2e-5) * float(b.norm())
 
 
 def test_uniform_windows_stay_whole(gpu):
