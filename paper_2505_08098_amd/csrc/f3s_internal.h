@@ -353,7 +353,12 @@ template <int NW>
 __device__ __forceinline__ bool wave_item(int g, int wv, int32_t shared_items, int32_t n_items,
                                           int *item, bool *shared)
 {
-    *shared = NW == 1 || g < shared_items;
+    if constexpr (NW == 1) {  // a workgroup per item: no count to load first
+        *shared = true;
+        *item = g;
+        return true;
+    }
+    *shared = g < shared_items;
     *item = *shared ? g : shared_items + (g - shared_items) * NW + wv;
     return *item < n_items;
 }
