@@ -286,8 +286,8 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
     // Q_i: lane (i, g) holds Q[row][32c + 8g .. +7] for each chunk c.  Pad
     // rows (past the window's last row) read its first row: their results
     // are never written and rows do not interact, so any finite values do.
-    h8 q[NC];
-    {
+    h8 q[NC] = {};
+    auto load_q = [&]() {
         const char *qp = Q + ((int64_t)(live ? row : r0) * ld + 8 * g) * EB;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
@@ -296,7 +296,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
             else
                 q[c] = *reinterpret_cast<const h8 *>(qp + 64 * c);
         }
-    }
+    };
 
     f4 o[NT];
 #pragma unroll
@@ -519,7 +519,17 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<D, kIn, kNarrow>(), 8))) void 
     };
 
     if (b0 < b1) {
+        // The columns first: the gathers wait for them, and loads return in
+        // order.  With Q's rows ahead of them, d = 64: 1,021 nodes 4.58 us
+        // (now 4.43), molecule batches of 1,920 windows 5.69 (5.54) and of
+        // 7,680 15.6 (15.35).  joint_rows' kernels lose up to 2% by it (48,000
+        // keys, 4 heads of d = 128: 478 us, 491), so Q stays ahead there.
+        if constexpr (kJoint) load_q();
         load_cols(b0);
+        if constexpr (!kJoint) {
+            __builtin_amdgcn_sched_barrier(0);
+            load_q();
+        }
         load_masks(b0);
         load_cols(b0 + 2);
         // loads return in issue order: the loop waits for each group in turn
