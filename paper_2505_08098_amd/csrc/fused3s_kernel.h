@@ -99,8 +99,10 @@ constexpr int waves_per_simd()
 // turn, 515 with the rescale alone); million-node graph 1,266 against 1,272;
 // one head of 48,000 tokens at d = 256: 253 against 268.  It costs up to 2% where
 // a sequence's rows stay in the caches (2 heads of 16,001 tokens, d = 128: 66.0
-// against 65.2), and more with narrower rows or the half-size fp8 ones (fp8,
-// d = 128, 24,000 tokens: 96.8 against 93.2; f16, d = 160: 164.5 against 161.4).
+// against 65.2) and on power-law graphs of 131,072 to 400,000 nodes at d = 128
+// (262,147: 301.2 against 294.8), and more with narrower rows or the half-size
+// fp8 ones (fp8, d = 128, 24,000 tokens: 96.8 against 93.2; f16, d = 160: 164.5
+// against 161.4).
 // (f16, d = 96, 64-bit addresses: the order whose registers do not spill.)
 template <int D, bool kWide, int kIn> constexpr bool joint_rows()
 {
